@@ -82,6 +82,17 @@ __device__ inline WorkRange work_range(int first, int n_work)
     return r;
 }
 
+// floor(n / d) for 0 <= n, d < 2^16 as a multiply-high: m = floor(2^32 / d) + 1
+// makes (n m) >> 32 exact while n d < 2^32.
+__device__ inline unsigned long long fast_recip(int d)
+{
+    return (1ull << 32) / (unsigned long long)d + 1ull;
+}
+__device__ inline int fast_div(int n, unsigned long long m)
+{
+    return (int)(((unsigned long long)(unsigned)n * m) >> 32);
+}
+
 // ---------------------------------------------------------------------------
 // Axis geometry.  An affine axis (host-verified: x_k = k * step + lo exactly
 // for k < n-1, x_{n-1} = hi) needs no coordinate loads.
@@ -274,31 +285,40 @@ __device__ inline double trig_arg(const DevInst &I, const double *tf, int a, dou
     return x;
 }
 
+// The kinds of one dimension only: branches that end in stores to different
+// entries are merged into one store through a selected address, which keeps
+// the array out of registers.
 template <int D>
 __device__ inline void drift(const DevInst &I, const double *tf, const double2 *trig,
                              const int *idx, double *b)
 {
 #pragma clang fp contract(off)
-    if (I.coef_kind == 0) {
+    if (D == 1 || I.coef_kind == 0) {
 #pragma unroll
         for (int a = 0; a < D; ++a) b[a] = I.coef[a];
-    } else if (I.coef_kind == 1) {
+        return;
+    }
+    if constexpr (D == 2) {
         const double2 t0 = trig[I.coord_off[0] + idx[0]];
         const double2 t1 = trig[I.coord_off[1] + idx[1]];
-        const double sa = t0.x, ca = t0.y, sy = t1.x, cy = t1.y;
-        const double Api = I.coef[0] * M_PI;
-        b[0] = -(Api * sa * cy);
-        b[1] = Api * ca * sy;
-    } else if (I.coef_kind == 3) {
-        // rolls: Pe v with v_1 = -pi cos(pi y) (sin(n x) + e cos(n x)),
-        // v_2 = n sin(pi y) (cos(n x) - e sin(n x)), e = eps cos(omega t)
-        const double2 t0 = trig[I.coord_off[0] + idx[0]];
-        const double2 t1 = trig[I.coord_off[1] + idx[1]];
-        const double s1 = t0.x, c1 = t0.y, s2 = t1.x, c2 = t1.y;
-        const double e = tf[0];
-        b[0] = -(I.coef[0] * M_PI * c2 * (s1 + e * c1));
-        b[1] = I.coef[0] * I.coef[3] * s2 * (c1 - e * s1);
-    } else {
+        double b0, b1;
+        if (I.coef_kind == 1) {
+            const double sa = t0.x, ca = t0.y, sy = t1.x, cy = t1.y;
+            const double Api = I.coef[0] * M_PI;
+            b0 = -(Api * sa * cy);
+            b1 = Api * ca * sy;
+        } else {
+            // rolls: Pe v with v_1 = -pi cos(pi y) (sin(n x) + e cos(n x)),
+            // v_2 = n sin(pi y) (cos(n x) - e sin(n x)), e = eps cos(omega t)
+            const double s1 = t0.x, c1 = t0.y, s2 = t1.x, c2 = t1.y;
+            const double e = tf[0];
+            b0 = -(I.coef[0] * M_PI * c2 * (s1 + e * c1));
+            b1 = I.coef[0] * I.coef[3] * s2 * (c1 - e * s1);
+        }
+        b[0] = b0;
+        b[1] = b1;
+    }
+    if constexpr (D == 3) {
         const double2 tx = trig[I.coord_off[0] + idx[0]];
         const double2 ty = trig[I.coord_off[1] + idx[1]];
         const double2 tz = trig[I.coord_off[2] + idx[2]];
@@ -317,40 +337,45 @@ __device__ inline int drift_dtheta(const DevInst &I, const double *tf, const dou
 {
 #pragma unroll
     for (int k = 0; k < 12; ++k) db[k] = 0.0;
-    if (I.coef_kind == 0) {
+    if (D == 1 || I.coef_kind == 0) {
 #pragma unroll
         for (int a = 0; a < D; ++a) db[a * 3 + a] = 1.0;
         return D;
-    } else if (I.coef_kind == 1) {
-        const double A = I.coef[0], eps = I.coef[1];
-        const double swt = tf[1], cwt = tf[2], t = tf[3];
+    }
+    if constexpr (D == 2) {
         const double2 t0 = trig[I.coord_off[0] + idx[0]];
         const double2 t1 = trig[I.coord_off[1] + idx[1]];
-        const double sphi = t0.x, cphi = t0.y, sy = t1.x, cy = t1.y;
-        const double db0 = -A * M_PI * cphi * cy;   // d b0 / d phi
-        const double db1 = -A * M_PI * sphi * sy;   // d b1 / d phi
-        const double dpe = M_PI * swt;              // d phi / d eps
-        const double dpo = M_PI * eps * t * cwt;    // d phi / d omega
-        db[0] = -M_PI * sphi * cy;  db[1] = M_PI * cphi * sy;
-        db[3] = db0 * dpe;          db[4] = db1 * dpe;
-        db[6] = db0 * dpo;          db[7] = db1 * dpo;
+        double e0, e1, f0, f1, g0, g1;
+        if (I.coef_kind == 1) {
+            const double A = I.coef[0], eps = I.coef[1];
+            const double swt = tf[1], cwt = tf[2], t = tf[3];
+            const double sphi = t0.x, cphi = t0.y, sy = t1.x, cy = t1.y;
+            const double db0 = -A * M_PI * cphi * cy;   // d b0 / d phi
+            const double db1 = -A * M_PI * sphi * sy;   // d b1 / d phi
+            const double dpe = M_PI * swt;              // d phi / d eps
+            const double dpo = M_PI * eps * t * cwt;    // d phi / d omega
+            e0 = -M_PI * sphi * cy;  e1 = M_PI * cphi * sy;
+            f0 = db0 * dpe;          f1 = db1 * dpe;
+            g0 = db0 * dpo;          g1 = db1 * dpo;
+        } else {
+            // rolls: theta = (Pe, eps, omega); e = eps cos(omega t)
+            const double Pe = I.coef[0], eps = I.coef[1], nn = I.coef[3];
+            const double e = tf[0], cwt = tf[1], swt = tf[2], t = tf[3];
+            const double s1 = t0.x, c1 = t0.y, s2 = t1.x, c2 = t1.y;
+            const double db0 = -(Pe * M_PI * c2 * c1);   // d b0 / d e
+            const double db1 = -(Pe * nn * s2 * s1);     // d b1 / d e
+            const double dee = cwt;                      // d e / d eps
+            const double deo = -(eps * t * swt);         // d e / d omega
+            e0 = -(M_PI * c2 * (s1 + e * c1));  e1 = nn * s2 * (c1 - e * s1);
+            f0 = db0 * dee;                     f1 = db1 * dee;
+            g0 = db0 * deo;                     g1 = db1 * deo;
+        }
+        db[0] = e0;  db[1] = e1;
+        db[3] = f0;  db[4] = f1;
+        db[6] = g0;  db[7] = g1;
         return 3;
-    } else if (I.coef_kind == 3) {
-        // rolls: theta = (Pe, eps, omega); e = eps cos(omega t)
-        const double Pe = I.coef[0], eps = I.coef[1], nn = I.coef[3];
-        const double e = tf[0], cwt = tf[1], swt = tf[2], t = tf[3];
-        const double2 t0 = trig[I.coord_off[0] + idx[0]];
-        const double2 t1 = trig[I.coord_off[1] + idx[1]];
-        const double s1 = t0.x, c1 = t0.y, s2 = t1.x, c2 = t1.y;
-        const double db0 = -(Pe * M_PI * c2 * c1);   // d b0 / d e
-        const double db1 = -(Pe * nn * s2 * s1);     // d b1 / d e
-        const double dee = cwt;                      // d e / d eps
-        const double deo = -(eps * t * swt);         // d e / d omega
-        db[0] = -(M_PI * c2 * (s1 + e * c1));  db[1] = nn * s2 * (c1 - e * s1);
-        db[3] = db0 * dee;                     db[4] = db1 * dee;
-        db[6] = db0 * deo;                     db[7] = db1 * deo;
-        return 3;
-    } else {
+    }
+    if constexpr (D == 3) {
         const double A = I.coef[0], B = I.coef[1], C = I.coef[2];
         const double f = tf[0], st = tf[1];
         const double2 tx = trig[I.coord_off[0] + idx[0]];
@@ -363,8 +388,8 @@ __device__ inline int drift_dtheta(const DevInst &I, const double *tf, const dou
         db[9] = st * (A * sz + C * cy);                        // amp
         db[10] = st * (B * sx + A * cz);
         db[11] = st * (C * sy + B * cx);
-        return 4;
     }
+    return D == 3 ? 4 : D;
 }
 
 template <int D>
@@ -706,35 +731,35 @@ __global__ void __launch_bounds__(kBlock) k_init_field(const unsigned char *cls,
 }
 
 // Stencil of the PCHIP slope along axis a at index i (Eq. (e300) and the end
-// rule after it): the three nodes along the axis and the two spacings.
+// rule after it): the three nodes along the axis and the two inverse spacings.
+// An end node takes the stencil of its inner neighbour.
+template <typename T>
 __device__ inline void slope_stencil(const DevInst &I, const double *coords, int a, int i,
-                                     int &il, int &ic, int &ir, double &hl, double &hr)
+                                     int &il, int &ic, int &ir, T &rl, T &rr)
 {
     const int na = I.n[a];
     if (I.periodic[a]) {
         ic = (i == na - 1) ? 0 : i;
         il = (ic == 0) ? na - 2 : ic - 1;
-        ir = ic + 1;
-    } else if (i == 0) {
-        il = 0; ic = 1; ir = 2;
-    } else if (i == na - 1) {
-        il = na - 3; ic = na - 2; ir = na - 1;
     } else {
-        il = i - 1; ic = i; ir = i + 1;
+        ic = min(max(i, 1), na - 2);
+        il = ic - 1;
     }
+    ir = ic + 1;
     if (I.affine[a]) {
-        hl = I.step[a];
-        hr = I.step[a];
+        rl = rr = (T)I.inv_h[a];
     } else {
         const double *x = coords + I.coord_off[a];
-        hl = (ic == 0) ? x[na - 1] - x[na - 2] : x[ic] - x[il];
-        hr = x[ir] - x[ic];
+        rl = T(1) / (T)((ic == 0) ? x[na - 1] - x[na - 2] : x[ic] - x[il]);
+        rr = T(1) / (T)(x[ir] - x[ic]);
     }
 }
 
+// PCHIP slope from the three values and the two inverse spacings.
 template <typename T>
-__device__ inline T pchip_slope(T dl, T dr)
+__device__ inline T pchip(T ul, T uc, T ur, T rl, T rr)
 {
+    const T dl = (uc - ul) * rl, dr = (ur - uc) * rr;
     return (dl * dr > T(0)) ? T(2) * dl * dr / (dl + dr) : T(0);
 }
 
@@ -745,16 +770,14 @@ template <typename T>
 __device__ inline T twist_2d(const DevInst &I, const double *coords, const T *ui, const int *idx)
 {
     int il0, ic0, ir0, il1, ic1, ir1;
-    double hl0, hr0, hl1, hr1;
-    slope_stencil(I, coords, 0, idx[0], il0, ic0, ir0, hl0, hr0);
-    slope_stencil(I, coords, 1, idx[1], il1, ic1, ir1, hl1, hr1);
-    const long long s0 = I.stride[0];
+    T rl0, rr0, rl1, rr1;
+    slope_stencil<T>(I, coords, 0, idx[0], il0, ic0, ir0, rl0, rr0);
+    slope_stencil<T>(I, coords, 1, idx[1], il1, ic1, ir1, rl1, rr1);
+    const int s0 = (int)I.stride[0];
     auto g0 = [&](int j) -> T {
-        const T ul = ui[il0 * s0 + j], uc = ui[ic0 * s0 + j], ur = ui[ir0 * s0 + j];
-        return pchip_slope<T>((uc - ul) / (T)hl0, (ur - uc) / (T)hr0);
+        return pchip<T>(ui[il0 * s0 + j], ui[ic0 * s0 + j], ui[ir0 * s0 + j], rl0, rr0);
     };
-    const T gl = g0(il1), gc = g0(ic1), gr = g0(ir1);
-    return pchip_slope<T>((gc - gl) / (T)hl1, (gr - gc) / (T)hr1);
+    return pchip<T>(g0(il1), g0(ic1), g0(ir1), rl1, rr1);
 }
 
 // R2 twist fields in 3D at node idx: t01 = D_1(D_0 u), t02 = D_2(D_0 u),
@@ -766,115 +789,27 @@ __device__ inline void twist_3d(const DevInst &I, const double *coords, const T 
                                 T *tw)
 {
     int l[3][3];
-    double hl[3], hr[3];
-    for (int a = 0; a < 3; ++a) slope_stencil(I, coords, a, idx[a], l[a][0], l[a][1], l[a][2], hl[a], hr[a]);
-    const long long s0 = I.stride[0], s1 = I.stride[1];
+    T rl[3], rr[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        slope_stencil<T>(I, coords, a, idx[a], l[a][0], l[a][1], l[a][2], rl[a], rr[a]);
+    const int s0 = (int)I.stride[0], s1 = (int)I.stride[1];
     auto at = [&](int i0, int i1, int i2) -> T { return ui[i0 * s0 + i1 * s1 + i2]; };
     // slope along axis 0 at (i0 = idx0's stencil, i1, i2)
     auto g0 = [&](int i1, int i2) -> T {
-        const T ul = at(l[0][0], i1, i2), uc = at(l[0][1], i1, i2), ur = at(l[0][2], i1, i2);
-        return pchip_slope<T>((uc - ul) / (T)hl[0], (ur - uc) / (T)hr[0]);
+        return pchip<T>(at(l[0][0], i1, i2), at(l[0][1], i1, i2), at(l[0][2], i1, i2), rl[0], rr[0]);
     };
     auto g1 = [&](int i2) -> T {
-        const T ul = at(idx[0], l[1][0], i2), uc = at(idx[0], l[1][1], i2), ur = at(idx[0], l[1][2], i2);
-        return pchip_slope<T>((uc - ul) / (T)hl[1], (ur - uc) / (T)hr[1]);
+        return pchip<T>(at(idx[0], l[1][0], i2), at(idx[0], l[1][1], i2), at(idx[0], l[1][2], i2), rl[1], rr[1]);
     };
     auto t01 = [&](int i2) -> T {
-        const T gl = g0(l[1][0], i2), gc = g0(l[1][1], i2), gr = g0(l[1][2], i2);
-        return pchip_slope<T>((gc - gl) / (T)hl[1], (gr - gc) / (T)hr[1]);
+        return pchip<T>(g0(l[1][0], i2), g0(l[1][1], i2), g0(l[1][2], i2), rl[1], rr[1]);
     };
-    auto along2 = [&](T fl, T fc, T fr) -> T {
-        return pchip_slope<T>((fc - fl) / (T)hl[2], (fr - fc) / (T)hr[2]);
-    };
+    auto along2 = [&](T fl, T fc, T fr) -> T { return pchip<T>(fl, fc, fr, rl[2], rr[2]); };
     tw[0] = t01(idx[2]);
     tw[1] = along2(g0(idx[1], l[2][0]), g0(idx[1], l[2][1]), g0(idx[1], l[2][2]));
     tw[2] = along2(g1(l[2][0]), g1(l[2][1]), g1(l[2][2]));
     tw[3] = along2(t01(l[2][0]), t01(l[2][1]), t01(l[2][2]));
-}
-
-// Slope pass for step n over work items [first, first + count): table items
-// (kind 1 + a) fill the (sin, cos) table of axis a; node items (kind 0) write
-// record[node] = (u, g_0, .., g_{d-1}).
-template <typename T, int D>
-__global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, int count,
-                                                   const T *__restrict__ u,
-                                                   T *__restrict__ packed)
-{
-    constexpr int PS = RecStride<D>::value;
-    using R = typename RecT<T, PS>::type;
-    R *rec = reinterpret_cast<R *>(packed);
-    const WorkRange wr = work_range(first, count);
-    for (int w = wr.begin; w < wr.end; w += wr.step) {
-        const WorkItem it = P.slope_work[w];
-        if ((int)threadIdx.x >= it.count) continue;
-        const DevInst &I = P.inst[it.inst];
-        if (it.kind > 0) {
-            const int a = it.kind - 1;
-            const int i = it.first + threadIdx.x;
-            const double arg = trig_arg(I, time_factors(P, n, it.inst), a,
-                                        P.coords[I.coord_off[a] + i]);
-            P.trig[I.coord_off[a] + i] = make_double2(sin(arg), cos(arg));
-            continue;
-        }
-        const int node = it.first + threadIdx.x;
-        int idx[3];
-        split_node<D>(I, node, idx);
-        const T *ui = u + I.node_off;
-        T out[4] = {ui[node], T(0), T(0), T(0)};
-        for (int a = 0; a < D; ++a) {
-            const int na = I.n[a];
-            const int i = idx[a];
-            int il, ic, ir;
-            if (I.periodic[a]) {
-                ic = (i == na - 1) ? 0 : i;
-                il = (ic == 0) ? na - 2 : ic - 1;
-                ir = ic + 1;
-            } else if (i == 0) {
-                il = 0; ic = 1; ir = 2;
-            } else if (i == na - 1) {
-                il = na - 3; ic = na - 2; ir = na - 1;
-            } else {
-                il = i - 1; ic = i; ir = i + 1;
-            }
-            double hl, hr;
-            if (I.affine[a]) {
-                hl = I.step[a];
-                hr = I.step[a];
-            } else {
-                const double *x = P.coords + I.coord_off[a];
-                hl = (ic == 0) ? x[na - 1] - x[na - 2] : x[ic] - x[il];
-                hr = x[ir] - x[ic];
-            }
-            const long long base = node - (long long)i * I.stride[a];
-            const T ul = ui[base + (long long)il * I.stride[a]];
-            const T uc = ui[base + (long long)ic * I.stride[a]];
-            const T ur = ui[base + (long long)ir * I.stride[a]];
-            const T dl = (uc - ul) / (T)hl;
-            const T dr = (ur - uc) / (T)hr;
-            out[1 + a] = (dl * dr > T(0)) ? T(2) * dl * dr / (dl + dr) : T(0);
-        }
-        if constexpr (D == 2) {
-            // R2 twist: the PCHIP slope along axis 1 of the axis-0 slope field
-            // (the one-dimensional rule composed in increasing axis order)
-            if (P.hermite2) out[3] = twist_2d<T>(I, P.coords, ui, idx);
-        } else if constexpr (D == 3) {
-            // R2: the four twist fields in the node's second record
-            if (P.hermite2) {
-                T tw[4];
-                twist_3d<T>(I, P.coords, ui, idx, tw);
-                R q;
-                q.x = tw[0]; q.y = tw[1]; q.z = tw[2]; q.w = tw[3];
-                reinterpret_cast<R *>(P.packed2)[I.node_off + node] = q;
-            }
-        }
-        R r;
-        if constexpr (PS == 2) {
-            r.x = out[0]; r.y = out[1];
-        } else {
-            r.x = out[0]; r.y = out[1]; r.z = out[2]; r.w = out[3];
-        }
-        rec[I.node_off + node] = r;
-    }
 }
 
 // Per-axis data of one landing coordinate, shared through LDS by the lanes of
@@ -1253,72 +1188,6 @@ __global__ void __launch_bounds__(kBlock, (FC && sizeof(T) == 4 && QS <= 4) ? 3 
 // o_a is the (unwrapped) cell of the smallest landing coordinate, and every
 // landing cell lies in [o_a, o_a + L - 2] (host bound).
 // ---------------------------------------------------------------------------
-struct AxisBox {
-    int o;       // unwrapped cell of the first GH point
-    int n;       // nodes on the axis
-    int per;     // periodic
-};
-
-// Cell of a landing coordinate, unwrapped across a periodic seam.
-template <bool AFF>
-__device__ inline AxisEval eval_axis_unwrapped(const DevInst &I, const double *coords, int a,
-                                               double c, double ga, int &ku)
-{
-#pragma clang fp contract(off)
-    const AxisEval e = eval_axis_t<AFF>(I, coords, a, c, ga);
-    ku = e.k;
-    if (I.periodic[a]) {
-        const double z = c + I.S * ga;
-        if (z >= I.hi[a]) ku += I.n[a] - 1;
-        else if (z < I.lo[a]) ku -= I.n[a] - 1;
-    }
-    return e;
-}
-
-// Per-axis weight vectors of one node; returns false if a landing cell left
-// the box (cannot happen when the host bound holds).
-template <typename T, int QS, int L, bool AFF, bool DERIV>
-__device__ inline bool axis_vectors(const DevInst &I, const double *coords, const double *ga,
-                                    const T *w1, int a, double c, int &o, T &m, T *V, T *Sv,
-                                    T *dV, T *dS, T *aV, T *aS)
-{
-    bool ok = true;
-    m = T(0);
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        V[j] = T(0); Sv[j] = T(0);
-        if (DERIV) { dV[j] = T(0); dS[j] = T(0); aV[j] = T(0); aS[j] = T(0); }
-    }
-#pragma unroll
-    for (int q = 0; q < QS; ++q) {
-        int ku;
-        const AxisEval e = eval_axis_unwrapped<AFF>(I, coords, a, c, ga[q], ku);
-        if (q == 0) o = ku;
-        const int l = ku - o;
-        if (l < 0 || l > L - 2) { ok = false; continue; }
-        if (e.ex) continue;
-        const T w = w1[q];
-        m += w;
-        const Basis<T> B = hermite<T>(e.s, e.h);
-        Basis<T> Bz;
-        if (DERIV) Bz = hermite_dz<T>(e.s, e.h);
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-            const bool a0 = (j == l), a1 = (j == l + 1);
-            V[j] += a0 ? w * B.v0 : (a1 ? w * B.v1 : T(0));
-            Sv[j] += a0 ? w * B.d0 : (a1 ? w * B.d1 : T(0));
-            if (DERIV) {
-                const T wa = w * (T)ga[q];
-                dV[j] += a0 ? w * Bz.v0 : (a1 ? w * Bz.v1 : T(0));
-                dS[j] += a0 ? w * Bz.d0 : (a1 ? w * Bz.d1 : T(0));
-                aV[j] += a0 ? wa * Bz.v0 : (a1 ? wa * Bz.v1 : T(0));
-                aS[j] += a0 ? wa * Bz.d0 : (a1 ? wa * Bz.d1 : T(0));
-            }
-        }
-    }
-    return ok;
-}
-
 // Node index of footprint position i on an axis: wrapped across the seam of a
 // periodic axis, clamped to the axis otherwise.  Footprint positions past the
 // last node carry zero weight (no landing cell reaches them); clamping keeps
@@ -1332,119 +1201,6 @@ __device__ inline int wrap_index(int i, int n, int per)
         i = i < 0 ? 0 : (i > n - 1 ? n - 1 : i);
     }
     return i;
-}
-
-// Box contraction: value and slope-weighted sum over the footprint box of
-// the records, with per-axis vector sets (Va, Sa) for each axis.
-template <typename T, int D, int L, typename R>
-__device__ inline T box_contract(const R *rec, const DevInst &I, const int *o, T uref,
-                                 const T (*V)[L], const T (*Sv)[L], bool tw = false)
-{
-    if constexpr (D == 1) {
-        T acc = T(0);
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-            const R r = rec[I.node_off + wrap_index(o[0] + i, I.n[0], I.periodic[0])];
-            acc += V[0][i] * (r.x - uref) + Sv[0][i] * r.y;
-        }
-        return acc;
-    } else if constexpr (D == 2) {
-        int j1[L];
-#pragma unroll
-        for (int j = 0; j < L; ++j) j1[j] = wrap_index(o[1] + j, I.n[1], I.periodic[1]);
-        T acc = T(0);
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-            const long long row = I.node_off +
-                (long long)wrap_index(o[0] + i, I.n[0], I.periodic[0]) * I.stride[0];
-            T tv = T(0), tg = T(0);
-#pragma unroll
-            for (int j = 0; j < L; ++j) {
-                const R r = rec[row + j1[j]];
-                tv += V[1][j] * (r.x - uref) + Sv[1][j] * r.z;
-                tg += V[1][j] * r.y;
-                if (tw) tg += Sv[1][j] * r.w;   // R2 twist
-            }
-            acc += V[0][i] * tv + Sv[0][i] * tg;
-        }
-        return acc;
-    } else {
-        int j2[L], j1[L];
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-            j2[j] = wrap_index(o[2] + j, I.n[2], I.periodic[2]);
-            j1[j] = wrap_index(o[1] + j, I.n[1], I.periodic[1]);
-        }
-        T acc = T(0);
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-            const long long b0 = I.node_off +
-                (long long)wrap_index(o[0] + i, I.n[0], I.periodic[0]) * I.stride[0];
-            T sv = T(0), sg0 = T(0);
-#pragma unroll
-            for (int j = 0; j < L; ++j) {
-                const long long b1 = b0 + (long long)j1[j] * I.stride[1];
-                T tv = T(0), tg0 = T(0), tg1 = T(0);
-#pragma unroll
-                for (int kk = 0; kk < L; ++kk) {
-                    const R r = rec[b1 + j2[kk]];
-                    tv += V[2][kk] * (r.x - uref) + Sv[2][kk] * r.w;
-                    tg0 += V[2][kk] * r.y;
-                    tg1 += V[2][kk] * r.z;
-                }
-                sv += V[1][j] * tv + Sv[1][j] * tg1;
-                sg0 += V[1][j] * tg0;
-            }
-            acc += V[0][i] * sv + Sv[0][i] * sg0;
-        }
-        return acc;
-    }
-}
-
-template <typename T, int D, int QS, int L, bool AFF>
-__global__ void __launch_bounds__(kBlock) k_step_box(
-    const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
-    const WorkItem *__restrict__ work, const int *__restrict__ nodes,
-    const double2 *__restrict__ trig, const double *__restrict__ coords,
-    const T *__restrict__ packed, T *__restrict__ u_out)
-{
-    constexpr int PS = RecStride<D>::value;
-    using R = typename RecT<T, PS>::type;
-    const R *rec = reinterpret_cast<const R *>(packed);
-    const double *ga = P.gh_a;
-    const T *w1 = weights1<T>(P);
-    T wsum = T(0);
-#pragma unroll
-    for (int q = 0; q < QS; ++q) wsum += w1[q];
-    const WorkRange wr = work_range(0, n_work);
-    for (int w = wr.begin; w < wr.end; w += wr.step) {
-        const WorkItem it = work[w];
-        if ((int)threadIdx.x >= it.count) continue;
-        const DevInst &I = insts[it.inst];
-        const int node = nodes[it.first + threadIdx.x];
-        int idx[3];
-        split_node<D>(I, node, idx);
-        const T uref = rec[I.node_off + node].x;
-        double c[3];
-        node_centre<D>(I, coords, time_factors(P, n, it.inst), trig, idx, P.dt, c);
-        T V[D][L], Sv[D][L];
-        int o[3];
-        T m[3];
-        bool ok = true;
-#pragma unroll
-        for (int a = 0; a < D; ++a)
-            ok = axis_vectors<T, QS, L, AFF, false>(I, coords, ga, w1, a, c[a], o[a], m[a], V[a],
-                                                    Sv[a], nullptr, nullptr, nullptr, nullptr) && ok;
-        if (!ok) atomicOr(P.flags, 2);
-        T prod = m[0], wd = wsum;
-#pragma unroll
-        for (int a = 1; a < D; ++a) { prod *= m[a]; wd *= wsum; }
-        const T emass = wd - prod;
-        const T acc = box_contract<T, D, L, R>(rec, I, o, uref, V, Sv, P.hermite2 != 0);
-        const T v = uref + acc + emass * (T(1) - uref);
-        flag_nonfinite(P.flags, v);
-        store_node<D, T>(I, idx, node, v, u_out);
-    }
 }
 
 // Landing cells and exit flags of one instance (index parity checks).
@@ -1647,17 +1403,6 @@ __global__ void __launch_bounds__(kBlock) k_assemble_ell(PlanDev P, int n,
         }
         __syncthreads();
     }
-}
-
-// floor(n / d) for 0 <= n, d < 2^16 as a multiply-high: m = floor(2^32 / d) + 1
-// makes (n m) >> 32 exact while n d < 2^32.
-__device__ inline unsigned long long fast_recip(int d)
-{
-    return (1ull << 32) / (unsigned long long)d + 1ull;
-}
-__device__ inline int fast_div(int n, unsigned long long m)
-{
-    return (int)(((unsigned long long)(unsigned)n * m) >> 32);
 }
 
 // Assembly of separable rows (no landing point can reach a curved exit
@@ -2312,16 +2057,18 @@ struct MuTile {
 __device__ inline void reduce_theta(double (*red)[kThetaSlots], const double *gth,
                                     double *grad, int inst)
 {
+    constexpr int kUsed = 5;   // parameters of any kind of drift, and D
     const int wave = threadIdx.x / 64, wl = threadIdx.x % 64;
-    for (int kk = 0; kk < kThetaSlots; ++kk) {
+#pragma unroll
+    for (int kk = 0; kk < kUsed; ++kk) {
         double v = gth[kk];
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
         if (wl == 0) red[wave][kk] = v;
     }
     __syncthreads();
-    if (threadIdx.x < kThetaSlots) {
+    if (threadIdx.x < kUsed) {
         double v = 0.0;
-        for (int wv = 0; wv < kBlock / 64; ++wv) v += red[wv][threadIdx.x];
+        for (int wv = 0; wv < (int)blockDim.x / 64; ++wv) v += red[wv][threadIdx.x];
         if (v != 0.0) atomicAdd(&grad[inst * kThetaSlots + threadIdx.x], v);
     }
 }
@@ -2377,17 +2124,16 @@ __device__ inline void node_theta(const PlanDev &P, const DevInst &I, const doub
     gth[4] = nt == 4 ? gD : 0.0;
 }
 
-// Thread-per-node adjoint step.  Lane = active node.  For each inside landing
-// point the kernel adds the transposed interpolation weights (2^D corners x
-// (value, D slopes)) times lam_j w_q to mu, and accumulates the interpolant's
-// gradient for the theta-derivative.  The innermost axis' landing data (cell,
-// in-cell position, width, exit flag, ball distance) are evaluated once per
-// node; the Hermite bases are rebuilt from them per point, which keeps the
-// kernel's registers low enough for several waves per SIMD.  The scatter goes
-// to the work item's LDS tile (field planes, padded rows), flushed once.  IN
-// (2D): the host has shown that no landing point of the work item's nodes can
-// exit (reach bound), so the exit tests and their per-point data are left out.
-template <typename T, int D, int QS, bool AFF, bool IN>
+// Thread-per-node adjoint step (1D, 3D, and 2D plans on axes that are not
+// affine).  Lane = active node.  For each inside landing point the kernel adds
+// the transposed interpolation weights (2^D corners x (value, D slopes)) times
+// lam_j w_q to mu, and accumulates the interpolant's gradient for the
+// theta-derivative.  The innermost axis' landing data (cell, in-cell position,
+// width, exit flag, ball distance) are evaluated once per node; the Hermite
+// bases are rebuilt from them per point, which keeps the kernel's registers
+// low enough for several waves per SIMD.  The scatter goes to the work item's
+// LDS tile (field planes, padded rows), flushed once.
+template <typename T, int D, int QS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) k_adjoint_node(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
     const WorkItem *__restrict__ work, const TileBox *__restrict__ tiles,
@@ -2395,6 +2141,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
     const double *__restrict__ coords, const T *__restrict__ packed,
     const T *__restrict__ lam, T *__restrict__ mu, double *__restrict__ grad)
 {
+    constexpr bool AFF = false;   // axes of any kind
     constexpr int PS = RecStride<D>::value;
     using R = typename RecT<T, PS>::type;
     extern __shared__ unsigned char smem_raw[];
@@ -2439,107 +2186,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
                 din[q] = e.dz2;
             }
             T Gz[3] = {T(0), T(0), T(0)}, Hz[3] = {T(0), T(0), T(0)};
-            if constexpr (D == 2) {
-                const long long s0 = I.stride[0];
-                const int pl = tile.plane, pitch = tile.pitch;
-                // one row of landing points at a time (unrolled rows would hold
-                // every row's gathers in registers)
-#pragma unroll 1
-                for (int q0 = 0; q0 < QS; ++q0) {
-                    const AxisEval e0 = eval_axis_t<AFF>(I, coords, 0, c[0], ga[q0]);
-                    if (!IN && e0.ex) continue;
-                    const Basis<T> X = hermite<T>(e0.s, e0.h), Xz = hermite_dz<T>(e0.s, e0.h);
-                    const T w0 = w1[q0], a0 = (T)ga[q0];
-                    const T Lw0 = Lm * w0;
-                    // the row's LDS offset (cell k0, innermost cell 0) when the
-                    // whole row of cells k0 fits the tile along axis 0
-                    const int l0 = e0.k - tile.lo[0];
-                    const bool row_in = tile.use && l0 >= 0 && l0 + 1 < tile.ext[0];
-                    const int row_off = l0 * pitch - tile.lo[1];
-                    const long long row = I.node_off + (long long)e0.k * s0;
-#pragma unroll
-                    for (int q1 = 0; q1 < QS; ++q1) {
-                        if constexpr (!IN) {
-                            bool ex = exin[q1];
-                            if (ball) ex = ex || ball_exit2(e0.dz2, din[q1], r2);
-                            if (ex) continue;
-                        }
-                        T s = sin_[q1], h = hin[q1];
-                        // the bases below depend on q1 only: keep them from being
-                        // hoisted out of the q0 loop for all q1 at once (that
-                        // would hold 8 x 12 values in registers and spill)
-                        int k1 = kin[q1];
-                        asm volatile("" : "+v"(s), "+v"(h), "+v"(k1));
-                        // interior points have valid cells; the (never taken)
-                        // branch keeps each point's code in its own block
-                        if (IN && k1 < 0) continue;
-                        const T om = T(1) - s;
-                        const T yv0 = (T(1) + T(2) * s) * om * om, yv1 = s * s * (T(3) - T(2) * s);
-                        const T yd0 = h * s * om * om, yd1 = h * s * s * (s - T(1));
-                        const T zv0 = (T(6) * s * s - T(6) * s) / h, zv1 = (T(6) * s - T(6) * s * s) / h;
-                        const T zd0 = T(1) - T(4) * s + T(3) * s * s, zd1 = T(3) * s * s - T(2) * s;
-                        const long long b = row + k1;
-                        const R p00 = rec[b], p01 = rec[b + 1], p10 = rec[b + s0], p11 = rec[b + s0 + 1];
-                        // interpolant gradient: d/dz0 (Xz, Y) and d/dz1 (X, Yz)
-                        const T A0z = p00.x * Xz.v0 + p10.x * Xz.v1 + p00.y * Xz.d0 + p10.y * Xz.d1;
-                        const T A1z = p01.x * Xz.v0 + p11.x * Xz.v1 + p01.y * Xz.d0 + p11.y * Xz.d1;
-                        const T C0z = p00.z * Xz.v0 + p10.z * Xz.v1;
-                        const T C1z = p01.z * Xz.v0 + p11.z * Xz.v1;
-                        const T g0 = yv0 * A0z + yv1 * A1z + yd0 * C0z + yd1 * C1z;
-                        const T A0 = p00.x * X.v0 + p10.x * X.v1 + p00.y * X.d0 + p10.y * X.d1;
-                        const T A1 = p01.x * X.v0 + p11.x * X.v1 + p01.y * X.d0 + p11.y * X.d1;
-                        const T C0 = p00.z * X.v0 + p10.z * X.v1;
-                        const T C1 = p01.z * X.v0 + p11.z * X.v1;
-                        const T g1 = zv0 * A0 + zv1 * A1 + zd0 * C0 + zd1 * C1;
-                        const T wq = w0 * w1[q1];
-                        Gz[0] += wq * g0;
-                        Gz[1] += wq * g1;
-                        Hz[0] += wq * a0 * g0;
-                        Hz[1] += wq * (T)ga[q1] * g1;
-                        // transposed weights: corner (e0, e1) gets
-                        // value X.v Y.v, slope-0 X.d Y.v, slope-1 X.v Y.d
-                        const T w1q = Lw0 * w1[q1];
-                        const T v0 = w1q * yv0, v1 = w1q * yv1, d0 = w1q * yd0, d1 = w1q * yd1;
-                        const T e00 = X.v0 * v0, e01 = X.v0 * v1, e10 = X.v1 * v0, e11 = X.v1 * v1;
-                        const T f00 = X.d0 * v0, f01 = X.d0 * v1, f10 = X.d1 * v0, f11 = X.d1 * v1;
-                        const T g00 = X.v0 * d0, g01 = X.v0 * d1, g10 = X.v1 * d0, g11 = X.v1 * d1;
-                        const int l1 = k1 - tile.lo[1];
-                        if (row_in && l1 >= 0 && l1 + 1 < tile.ext[1]) {
-                            double *t = tmem + row_off + k1;
-                            lds_add(t, e00);
-                            lds_add(t + 1, e01);
-                            lds_add(t + pitch, e10);
-                            lds_add(t + pitch + 1, e11);
-                            t += pl;
-                            lds_add(t, f00);
-                            lds_add(t + 1, f01);
-                            lds_add(t + pitch, f10);
-                            lds_add(t + pitch + 1, f11);
-                            t += pl;
-                            lds_add(t, g00);
-                            lds_add(t + 1, g01);
-                            lds_add(t + pitch, g10);
-                            lds_add(t + pitch + 1, g11);
-                        } else {
-                            T *m = mu + b * PS;
-                            const long long sp = s0 * PS;
-                            atomicAdd(m, e00);
-                            atomicAdd(m + PS, e01);
-                            atomicAdd(m + sp, e10);
-                            atomicAdd(m + sp + PS, e11);
-                            atomicAdd(m + 1, f00);
-                            atomicAdd(m + PS + 1, f01);
-                            atomicAdd(m + sp + 1, f10);
-                            atomicAdd(m + sp + PS + 1, f11);
-                            atomicAdd(m + 2, g00);
-                            atomicAdd(m + PS + 2, g01);
-                            atomicAdd(m + sp + 2, g10);
-                            atomicAdd(m + sp + PS + 2, g11);
-                        }
-                    }
-                }
-            } else {
-                // d = 1 and d = 3: one landing point at a time
+            {
+                // one landing point at a time
                 auto point = [&](const int *k, const Basis<T> *B, const Basis<T> *Bz, const T *aq, T wq) {
                     R p[1 << D];
                     gather_corners<D, R>(rec, I, k, p);
@@ -2610,6 +2258,21 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
                         const T aq[1] = {(T)ga[q]};
                         point(k, &B, &Bz, aq, w1[q]);
                     }
+                } else if constexpr (D == 2) {
+                    for (int q0 = 0; q0 < QS; ++q0) {
+                        const AxisEval e0 = eval_axis_t<AFF>(I, coords, 0, c[0], ga[q0]);
+                        if (e0.ex) continue;
+                        const Basis<T> X = hermite<T>(e0.s, e0.h), dX = hermite_dz<T>(e0.s, e0.h);
+#pragma unroll
+                        for (int q1 = 0; q1 < QS; ++q1) {
+                            if (exin[q1] || (ball && ball_exit2(e0.dz2, din[q1], r2))) continue;
+                            int k[2] = {e0.k, kin[q1]};
+                            const Basis<T> B[2] = {X, hermite<T>(sin_[q1], hin[q1])};
+                            const Basis<T> Bz[2] = {dX, hermite_dz<T>(sin_[q1], hin[q1])};
+                            const T aq[2] = {(T)ga[q0], (T)ga[q1]};
+                            point(k, B, Bz, aq, w1[q0] * w1[q1]);
+                        }
+                    }
                 } else {
                     for (int q0 = 0; q0 < QS; ++q0) {
                         const AxisEval e0 = eval_axis_t<AFF>(I, coords, 0, c[0], ga[q0]);
@@ -2635,343 +2298,6 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
                             }
                         }
                     }
-                }
-            }
-            node_theta<D, T>(P, I, tf, trig, idx, Lm, Gz, Hz, gth);
-        }
-        __syncthreads();
-        tile.template flush<PS>(I, mu, (T *)P.adj.stage);
-        reduce_theta(red, gth, grad, it.inst);
-        __syncthreads();
-    }
-}
-
-// Box-form adjoint step in 2D for separable nodes (affine axes).  The
-// transposed row of A_n over the footprint box [o0, o0+L) x [o1, o1+L) is
-// the outer product of the per-axis weight vectors: entry (i, j) gets
-// lam_j (V0[i] V1[j], S0[i] V1[j], V0[i] S1[j]) for (value, slope-0, slope-1),
-// i.e. 3 L^2 scatter adds per node against 12 per landing point in the
-// per-point form.  The theta-gradient is the same box contraction of the
-// records with the derivative vectors (dV, dS: z-derivative bases; aV, aS:
-// the same times the GH node) on one axis at a time.  The axis-1 vectors live
-// in registers; the axis-0 entries of row i are rebuilt inside the (rolled)
-// row loop from the hoisted axis-0 landing data, which keeps the registers
-// within a few waves per SIMD for L up to 12.
-template <typename T, int QS, int L>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : (L <= 8 ? 3 : 2)))) k_adjoint_box2(
-    const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
-    const WorkItem *__restrict__ work, const TileBox *__restrict__ tiles,
-    const int *__restrict__ nodes, const double2 *__restrict__ trig,
-    const double *__restrict__ coords, const T *__restrict__ packed,
-    const T *__restrict__ lam, T *__restrict__ mu, double *__restrict__ grad)
-{
-    constexpr int D = 2;
-    constexpr int PS = RecStride<D>::value;
-    using R = typename RecT<T, PS>::type;
-    extern __shared__ unsigned char smem_raw[];
-    __shared__ double red[kBlock / 64][kThetaSlots];
-    const R *rec = reinterpret_cast<const R *>(packed);
-    const double *ga = P.gh_a;
-    const T *w1 = weights1<T>(P);
-    const WorkRange wr = work_range(0, n_work);
-    for (int w = wr.begin; w < wr.end; w += wr.step) {
-        const WorkItem it = work[w];
-        const DevInst &I = insts[it.inst];
-        double *const tmem = reinterpret_cast<double *>(smem_raw);
-        MuTile<T, D> tile;
-        tile.init(tmem, tiles[w]);
-        tile.clear();
-        __syncthreads();
-        double gth[kThetaSlots];
-        for (int kk = 0; kk < kThetaSlots; ++kk) gth[kk] = 0.0;
-        const bool valid = (int)threadIdx.x < it.count;
-        const int node = valid ? nodes[it.first + threadIdx.x] : 0;
-        const T Lm = valid ? lam[I.node_off + node] : T(0);
-        if (valid && Lm != T(0)) {
-            int idx[3];
-            split_node<D>(I, node, idx);
-            const double *tf = time_factors(P, n, it.inst);
-            double c[3];
-            node_centre<D>(I, coords, tf, trig, idx, P.dt, c);
-            // axis 1: weight vectors over the footprint
-            T V1[L], S1[L], dV1[L], dS1[L], aV1[L], aS1[L];
-            int o1;
-            T m1;
-            bool ok = axis_vectors<T, QS, L, true, true>(I, coords, ga, w1, 1, c[1], o1, m1, V1, S1,
-                                                         dV1, dS1, aV1, aS1);
-            // axis 0: landing data per GH node
-            int l0[QS];
-            T s0[QS];
-            bool in0[QS];
-            int o0 = 0;
-            T h0 = T(1);
-#pragma unroll
-            for (int q = 0; q < QS; ++q) {
-                int ku;
-                const AxisEval e = eval_axis_unwrapped<true>(I, coords, 0, c[0], ga[q], ku);
-                if (q == 0) {
-                    o0 = ku;
-                    h0 = (T)e.h;
-                }
-                l0[q] = ku - o0;
-                s0[q] = (T)e.s;
-                in0[q] = !e.ex;
-                ok = ok && l0[q] >= 0 && l0[q] <= L - 2;
-            }
-            if (!ok) atomicOr(P.flags, 2);
-            const int b0 = o0 - tile.lo[0], b1 = o1 - tile.lo[1];
-            const bool lds = tile.use && b0 >= 0 && b0 + L <= tile.ext[0] && b1 >= 0 &&
-                             b1 + L <= tile.ext[1];
-            T Gz0 = T(0), Gz1 = T(0), Hz0 = T(0), Hz1 = T(0);
-            for (int i = 0; i < L; ++i) {
-                // axis-0 entries of row o0 + i
-                T v0 = T(0), sv0 = T(0), dv0 = T(0), ds0 = T(0), av0 = T(0), as0 = T(0);
-                bool hit = false;
-#pragma unroll
-                for (int q = 0; q < QS; ++q) {
-                    const bool lo = l0[q] == i, hi = l0[q] + 1 == i;
-                    if (!in0[q] || !(lo || hi)) continue;
-                    hit = true;
-                    // the bases depend on q only: rebuilt per row rather than hoisted
-                    // out of the row loop for every q at once (registers)
-                    T sq = s0[q];
-                    asm volatile("" : "+v"(sq));
-                    const Basis<T> B = hermite<T>(sq, h0), Bz = hermite_dz<T>(sq, h0);
-                    const T wq = w1[q], wa = wq * (T)ga[q];
-                    v0 += wq * (lo ? B.v0 : B.v1);
-                    sv0 += wq * (lo ? B.d0 : B.d1);
-                    dv0 += wq * (lo ? Bz.v0 : Bz.v1);
-                    ds0 += wq * (lo ? Bz.d0 : Bz.d1);
-                    av0 += wa * (lo ? Bz.v0 : Bz.v1);
-                    as0 += wa * (lo ? Bz.d0 : Bz.d1);
-                }
-                if (!hit) continue;
-                const int ci = wrap_index(o0 + i, I.n[0], I.periodic[0]);
-                const long long row = I.node_off + (long long)ci * I.stride[0];
-                const T lv0 = Lm * v0, lsv0 = Lm * sv0;
-                T tA = T(0), tB = T(0), tC = T(0), tD = T(0), tE = T(0), tF = T(0);
-                if (lds) {
-                    double *t = tmem + (b0 + i) * tile.pitch + b1;
-#pragma unroll
-                    for (int j = 0; j < L; ++j) {
-                        const R r = rec[row + o1 + j];
-                        tA += V1[j] * r.x + S1[j] * r.z;
-                        tB += V1[j] * r.y;
-                        tC += dV1[j] * r.x + dS1[j] * r.z;
-                        tD += dV1[j] * r.y;
-                        tE += aV1[j] * r.x + aS1[j] * r.z;
-                        tF += aV1[j] * r.y;
-                        lds_add(t + j, lv0 * V1[j]);
-                        lds_add(t + tile.plane + j, lsv0 * V1[j]);
-                        lds_add(t + 2 * tile.plane + j, lv0 * S1[j]);
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < L; ++j) {
-                        const int cj = wrap_index(o1 + j, I.n[1], I.periodic[1]);
-                        const R r = rec[row + cj];
-                        tA += V1[j] * r.x + S1[j] * r.z;
-                        tB += V1[j] * r.y;
-                        tC += dV1[j] * r.x + dS1[j] * r.z;
-                        tD += dV1[j] * r.y;
-                        tE += aV1[j] * r.x + aS1[j] * r.z;
-                        tF += aV1[j] * r.y;
-                        T *m = mu + (row + cj) * PS;
-                        atomicAdd(m, lv0 * V1[j]);
-                        atomicAdd(m + 1, lsv0 * V1[j]);
-                        atomicAdd(m + 2, lv0 * S1[j]);
-                    }
-                }
-                Gz0 += dv0 * tA + ds0 * tB;
-                Hz0 += av0 * tA + as0 * tB;
-                Gz1 += v0 * tC + sv0 * tD;
-                Hz1 += v0 * tE + sv0 * tF;
-            }
-            const T Gz[3] = {Gz0, Gz1, T(0)}, Hz[3] = {Hz0, Hz1, T(0)};
-            node_theta<D, T>(P, I, tf, trig, idx, Lm, Gz, Hz, gth);
-        }
-        __syncthreads();
-        tile.template flush<PS>(I, mu, (T *)P.adj.stage);
-        reduce_theta(red, gth, grad, it.inst);
-        __syncthreads();
-    }
-}
-
-// Box-form adjoint step for separable nodes: the transposed row of A_n is the
-// outer product of the per-axis weight vectors, and the theta-gradient needs
-// the same box contraction with the derivative vectors (dV, dS) and the
-// GH-node-weighted derivative vectors (aV, aS) on one axis at a time.
-template <typename T, int D, int QS, int L, bool AFF>
-__global__ void __launch_bounds__(kBlock) k_adjoint_box(
-    const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
-    const WorkItem *__restrict__ work, const TileBox *__restrict__ tiles,
-    const int *__restrict__ nodes, const double2 *__restrict__ trig,
-    const double *__restrict__ coords, const T *__restrict__ packed,
-    const T *__restrict__ lam, T *__restrict__ mu, double *__restrict__ grad)
-{
-    constexpr int PS = RecStride<D>::value;
-    using R = typename RecT<T, PS>::type;
-    extern __shared__ unsigned char smem_raw[];
-    __shared__ double red[kBlock / 64][kThetaSlots];
-    const R *rec = reinterpret_cast<const R *>(packed);
-    const double *ga = P.gh_a;
-    const T *w1 = weights1<T>(P);
-    const WorkRange wr = work_range(0, n_work);
-    for (int w = wr.begin; w < wr.end; w += wr.step) {
-        const WorkItem it = work[w];
-        const DevInst &I = insts[it.inst];
-        double *const tmem = reinterpret_cast<double *>(smem_raw);
-        MuTile<T, D> tile;
-        tile.init(tmem, tiles[w]);
-        tile.clear();
-        __syncthreads();
-        // uidx: unwrapped box indices (the tile's), cidx: the grid's
-        auto scatter = [&](const int *uidx, const int *cidx, int f, T v) {
-            const int off = tile.node_offset(uidx);
-            if (off >= 0) {
-                lds_add(&tmem[f * tile.plane + off], v);
-                return;
-            }
-            long long o = I.node_off;
-            for (int a = 0; a < D; ++a) o += (long long)cidx[a] * I.stride[a];
-            atomicAdd(&mu[o * PS + f], v);
-        };
-        double gth[kThetaSlots];
-        for (int kk = 0; kk < kThetaSlots; ++kk) gth[kk] = 0.0;
-        const bool valid = (int)threadIdx.x < it.count;
-        const int node = valid ? nodes[it.first + threadIdx.x] : 0;
-        const T Lm = valid ? lam[I.node_off + node] : T(0);
-        if (valid && Lm != T(0)) {
-            int idx[3];
-            split_node<D>(I, node, idx);
-            const double *tf = time_factors(P, n, it.inst);
-            double c[3];
-            node_centre<D>(I, coords, tf, trig, idx, P.dt, c);
-            T V[D][L], Sv[D][L], dV[D][L], dS[D][L], aV[D][L], aS[D][L];
-            int o[3];
-            T m[3];
-            bool ok = true;
-#pragma unroll
-            for (int a = 0; a < D; ++a)
-                ok = axis_vectors<T, QS, L, AFF, true>(I, coords, ga, w1, a, c[a], o[a], m[a],
-                                                       V[a], Sv[a], dV[a], dS[a], aV[a], aS[a]) && ok;
-            if (!ok) atomicOr(P.flags, 2);
-            T Gz[3] = {T(0), T(0), T(0)}, Hz[3] = {T(0), T(0), T(0)};
-            if constexpr (D == 1) {
-#pragma unroll
-                for (int i = 0; i < L; ++i) {
-                    const int ci = wrap_index(o[0] + i, I.n[0], I.periodic[0]);
-                    const R r = rec[I.node_off + ci];
-                    Gz[0] += dV[0][i] * r.x + dS[0][i] * r.y;
-                    Hz[0] += aV[0][i] * r.x + aS[0][i] * r.y;
-                    int cidx[1] = {ci}, uidx[1] = {o[0] + i};
-                    scatter(uidx, cidx, 0, Lm * V[0][i]);
-                    scatter(uidx, cidx, 1, Lm * Sv[0][i]);
-                }
-            } else if constexpr (D == 2) {
-#pragma unroll
-                for (int i = 0; i < L; ++i) {
-                    const int ci = wrap_index(o[0] + i, I.n[0], I.periodic[0]);
-#pragma unroll
-                    for (int j = 0; j < L; ++j) {
-                        const int cj = wrap_index(o[1] + j, I.n[1], I.periodic[1]);
-                        const R r = rec[I.node_off + (long long)ci * I.stride[0] + cj];
-                        Gz[0] += dV[0][i] * (V[1][j] * r.x + Sv[1][j] * r.z) + dS[0][i] * V[1][j] * r.y;
-                        Gz[1] += V[0][i] * (dV[1][j] * r.x + dS[1][j] * r.z) + Sv[0][i] * dV[1][j] * r.y;
-                        Hz[0] += aV[0][i] * (V[1][j] * r.x + Sv[1][j] * r.z) + aS[0][i] * V[1][j] * r.y;
-                        Hz[1] += V[0][i] * (aV[1][j] * r.x + aS[1][j] * r.z) + Sv[0][i] * aV[1][j] * r.y;
-                        int cidx[2] = {ci, cj}, uidx[2] = {o[0] + i, o[1] + j};
-                        scatter(uidx, cidx, 0, Lm * V[0][i] * V[1][j]);
-                        scatter(uidx, cidx, 1, Lm * Sv[0][i] * V[1][j]);
-                        scatter(uidx, cidx, 2, Lm * V[0][i] * Sv[1][j]);
-                    }
-                }
-            } else {
-                // theta-gradient first, contracting along the innermost axis: per
-                // box row (i, j) twelve sums of the records against the axis-2
-                // vectors, then the axis-0 and axis-1 factors once per row
-                int ck[L];
-#pragma unroll
-                for (int kk = 0; kk < L; ++kk) ck[kk] = wrap_index(o[2] + kk, I.n[2], I.periodic[2]);
-#pragma unroll
-                for (int i = 0; i < L; ++i) {
-                    const int ci = wrap_index(o[0] + i, I.n[0], I.periodic[0]);
-#pragma unroll
-                    for (int j = 0; j < L; ++j) {
-                        const int cj = wrap_index(o[1] + j, I.n[1], I.periodic[1]);
-                        const R *rr = rec + I.node_off + (long long)ci * I.stride[0] +
-                                      (long long)cj * I.stride[1];
-                        T uV = T(0), udV = T(0), uaV = T(0), g0V = T(0), g0dV = T(0), g0aV = T(0);
-                        T g1V = T(0), g1dV = T(0), g1aV = T(0), g2S = T(0), g2dS = T(0), g2aS = T(0);
-#pragma unroll
-                        for (int kk = 0; kk < L; ++kk) {
-                            const R r = rr[ck[kk]];
-                            uV += V[2][kk] * r.x;
-                            udV += dV[2][kk] * r.x;
-                            uaV += aV[2][kk] * r.x;
-                            g0V += V[2][kk] * r.y;
-                            g0dV += dV[2][kk] * r.y;
-                            g0aV += aV[2][kk] * r.y;
-                            g1V += V[2][kk] * r.z;
-                            g1dV += dV[2][kk] * r.z;
-                            g1aV += aV[2][kk] * r.z;
-                            g2S += Sv[2][kk] * r.w;
-                            g2dS += dS[2][kk] * r.w;
-                            g2aS += aS[2][kk] * r.w;
-                        }
-                        // d/dz_a of (V0 V1 V2 u + S0 V1 V2 g0 + V0 S1 V2 g1 + V0 V1 S2 g2)
-                        const T in0 = V[1][j] * (uV + g2S) + Sv[1][j] * g1V, s0 = V[1][j] * g0V;
-                        Gz[0] += dV[0][i] * in0 + dS[0][i] * s0;
-                        Hz[0] += aV[0][i] * in0 + aS[0][i] * s0;
-                        const T in1 = V[0][i] * (uV + g2S) + Sv[0][i] * g0V, s1 = V[0][i] * g1V;
-                        Gz[1] += dV[1][j] * in1 + dS[1][j] * s1;
-                        Hz[1] += aV[1][j] * in1 + aS[1][j] * s1;
-                        const T v01 = V[0][i] * V[1][j], s0v1 = Sv[0][i] * V[1][j], v0s1 = V[0][i] * Sv[1][j];
-                        Gz[2] += v01 * (udV + g2dS) + s0v1 * g0dV + v0s1 * g1dV;
-                        Hz[2] += v01 * (uaV + g2aS) + s0v1 * g0aV + v0s1 * g1aV;
-                    }
-                }
-                // transposed weights of box node (i, j, k): row factors
-                // Lm (V0 V1, S0 V1, V0 S1) times V2, and Lm V0 V1 times S2
-                const int b0 = o[0] - tile.lo[0], b1 = o[1] - tile.lo[1], b2 = o[2] - tile.lo[2];
-                if (tile.use && b0 >= 0 && b0 + L <= tile.ext[0] && b1 >= 0 && b1 + L <= tile.ext[1] &&
-                    b2 >= 0 && b2 + L <= tile.pitch) {
-#pragma unroll
-                    for (int i = 0; i < L; ++i)
-#pragma unroll
-                        for (int j = 0; j < L; ++j) {
-                            const T fa = Lm * V[0][i] * V[1][j], fb = Lm * Sv[0][i] * V[1][j];
-                            const T fc = Lm * V[0][i] * Sv[1][j];
-                            double *t = tmem + ((b0 + i) * tile.ext[1] + (b1 + j)) * tile.pitch + b2;
-#pragma unroll
-                            for (int kk = 0; kk < L; ++kk) {
-                                lds_add(t + kk, fa * V[2][kk]);
-                                lds_add(t + tile.plane + kk, fb * V[2][kk]);
-                                lds_add(t + 2 * tile.plane + kk, fc * V[2][kk]);
-                                lds_add(t + 3 * tile.plane + kk, fa * Sv[2][kk]);
-                            }
-                        }
-                } else {
-                    for (int i = 0; i < L; ++i)
-                        for (int j = 0; j < L; ++j)
-                            for (int kk = 0; kk < L; ++kk) {
-                                T v0 = T(0), s0 = T(0), v1 = T(0), s1 = T(0), v2 = T(0), s2 = T(0);
-#pragma unroll
-                                for (int t = 0; t < L; ++t) {
-                                    if (t == i) { v0 = V[0][t]; s0 = Sv[0][t]; }
-                                    if (t == j) { v1 = V[1][t]; s1 = Sv[1][t]; }
-                                    if (t == kk) { v2 = V[2][t]; s2 = Sv[2][t]; }
-                                }
-                                const int cidx[3] = {wrap_index(o[0] + i, I.n[0], I.periodic[0]),
-                                                     wrap_index(o[1] + j, I.n[1], I.periodic[1]),
-                                                     wrap_index(o[2] + kk, I.n[2], I.periodic[2])};
-                                const int uidx[3] = {o[0] + i, o[1] + j, o[2] + kk};
-                                const T fa = Lm * v0 * v1;
-                                scatter(uidx, cidx, 0, fa * v2);
-                                scatter(uidx, cidx, 1, Lm * s0 * v1 * v2);
-                                scatter(uidx, cidx, 2, Lm * v0 * s1 * v2);
-                                scatter(uidx, cidx, 3, fa * s2);
-                            }
                 }
             }
             node_theta<D, T>(P, I, tf, trig, idx, Lm, Gz, Hz, gth);

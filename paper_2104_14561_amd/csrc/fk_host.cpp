@@ -159,7 +159,7 @@ struct fk_plan {
     std::vector<double> gh_a, gh_w, gh_w1;
     std::vector<float> gh_wf, gh_w1f;
     std::vector<double> tfac;
-    std::vector<fk::WorkItem> slope_work, node_work, act_work, row_work, split_work;
+    std::vector<fk::WorkItem> slope_work, run_work, node_work, act_work, row_work, split_work;
     std::vector<fk::WorkItem> ell_work;   // non-separable ELL rows by width class
     std::vector<fk::WorkItem> ell_sep_work;   // separable ELL rows, runs of up to 64, by class
     int ell_lmax = 1;                     // longest row box axis
@@ -169,14 +169,15 @@ struct fk_plan {
     int n_ell_cls = 0;
     int ell_cls_off[fk::kEllClasses] = {}, ell_cls_n[fk::kEllClasses] = {},
         ell_cls_w[fk::kEllClasses] = {};
-    int tile_elems = 0;
     // adjoint step lists (per-node form and box form by class) with LDS tiles
     struct {
         std::vector<int> fw_nodes, box_nodes;
         std::vector<fk::WorkItem> fw_work, box_work;
         std::vector<fk::TileBox> fw_tiles, box_tiles;
         int box_work_off[fk::kBoxClasses] = {0}, n_box_work[fk::kBoxClasses] = {0};
-        int n_in_work = 0;
+        int box_lds[fk::kBoxClasses] = {0};
+        int fw_work_off[fk::kTileClasses] = {0}, n_fw_work[fk::kTileClasses] = {0};
+        int fw_lds[fk::kTileClasses] = {0};
         // tile staging (see stage_tiles)
         long long stage_entries = 0;
         std::vector<int> cov_node, cov_ptr, cov_base;
@@ -186,6 +187,7 @@ struct fk_plan {
     std::vector<fk::WorkItem> fw_work, fw_split_work, box_work;
     int box_work_off[fk::kBoxClasses] = {0}, n_box_work[fk::kBoxClasses] = {0};
     bool use_box = false;
+    bool wraps = false;   // some landing point can lie more than one period away
     bool faces = false;   // face kinds other than exit-1, or node-dependent diffusion
     int step_kind = 0;
     int n_table_work = 0;
@@ -428,6 +430,13 @@ void runaway_bounds(const fk_problem &pr, double *bmax, double *smax)
     for (int a = 0; a < 3; ++a) { bmax[a] *= 2.0; smax[a] *= 2.0; }
 }
 
+// Nodes per axis that the landing cells of one node can touch, the GH nodes
+// spreading over 2 reach (the largest over the smallest landing coordinate).
+int footprint(double reach, double hmin)
+{
+    return (int)std::floor(std::min(2.0 * reach / hmin, 1e6)) + 3;
+}
+
 void add_region(fk_plan *p, const char *name, size_t bytes)
 {
     Region r;
@@ -588,10 +597,10 @@ fk_status build_plan(fk_plan *p)
     std::vector<fk::WorkItem> tables, runs;
     long long ell_total = 0, ell_wmax = 0, ell_rows_w = 0;
     std::vector<std::vector<int>> inst_sep, inst_rest;
-    std::vector<int> inst_cls, inst_lneed;
+    std::vector<int> inst_cls, inst_lneed, inst_wraps;
     std::vector<std::vector<unsigned char>> inst_inner;   // per node: no landing point can exit
     std::vector<std::vector<unsigned char>> inst_seprow;  // per active row: separable
-    std::vector<std::array<int, 3>> inst_dils;
+    std::vector<std::array<int, 3>> inst_dils, inst_halo;
     p->node_off.assign(p->n_inst + 1, 0);
     p->act_count.assign(p->n_inst, 0);
     long long coord_total = 0;
@@ -687,7 +696,7 @@ fk_status build_plan(fk_plan *p)
         // slope records are needed only where landing cells of active nodes can
         // reach: the active bounding box widened by the reach plus the corner
         int blo[3] = {0, 0, 0}, bhi[3] = {0, 0, 0};
-        int dils[3] = {0, 0, 0};
+        int dils[3] = {0, 0, 0}, halo[3] = {0, 0, 0};
         for (int a = 0; a < pr.d; ++a) {
             double hmin = 1e300;
             for (int k = 1; k < pr.ax[a].n; ++k)
@@ -700,6 +709,9 @@ fk_status build_plan(fk_plan *p)
             // a landing cell lies within ceil(reach / h) cells of its node, and
             // its upper corner one further: the adjoint tile's halo
             dils[a] = std::min(dil - 1, pr.ax[a].n);
+            // the nodes of the landing cells themselves lie within floor(reach / h) + 1
+            // (with a margin for the rounding of the positions)
+            halo[a] = (int)std::min<double>(std::floor(reach / hmin * (1.0 + 1e-9) + 1e-9) + 1.0, pr.ax[a].n);
             if (pr.ax[a].periodic || na == 0) {
                 blo[a] = 0;
                 bhi[a] = pr.ax[a].n - 1;
@@ -707,6 +719,10 @@ fk_status build_plan(fk_plan *p)
                 blo[a] = std::max(0, amin[a] - dil);
                 bhi[a] = (int)std::min<long long>(pr.ax[a].n - 1, (long long)amax_i[a] + dil);
             }
+        }
+        for (int a = 0; a < pr.d && na > 0; ++a) {
+            I.blo[a] = blo[a];
+            I.blen[a] = bhi[a] - blo[a] + 1;
         }
         if (na > 0) {
             const int dl = pr.d - 1;
@@ -740,16 +756,19 @@ fk_status build_plan(fk_plan *p)
             }
             const double reach = std::sqrt(reach2);
             int Lneed = 0;
+            bool wraps = false;   // a landing cell more than one period away
             for (int a = 0; a < pr.d; ++a) {
                 double hmin = 1e300;
                 for (int k = 1; k < pr.ax[a].n; ++k)
                     hmin = std::min(hmin, pr.ax[a].nodes[k] - pr.ax[a].nodes[k - 1]);
-                Lneed = std::max(Lneed, (int)std::floor(2.0 * I.S * amax / hmin) + 3);
+                const int La = footprint(I.S * amax, hmin);
+                Lneed = std::max(Lneed, La);
+                wraps = wraps || (pr.ax[a].periodic && dils[a] + La > pr.ax[a].n - 2);
             }
-            static const int kL[fk::kBoxClasses] = {3, 4, 5, 6, 8};
+            p->wraps = p->wraps || wraps;
             int cls_box = -1;
-            for (int c2 = 0; c2 < fk::kBoxClasses; ++c2)
-                if (Lneed <= kL[c2]) { cls_box = c2; break; }
+            for (int c2 = 0; c2 < fk::kBoxClasses && !wraps; ++c2)
+                if (Lneed <= fk::box_len(pr.d, c2)) { cls_box = c2; break; }
             std::vector<int> sep, rest;
             std::vector<unsigned char> inner(J, 0);
             std::vector<unsigned char> seprow(na, 0);
@@ -789,9 +808,11 @@ fk_status build_plan(fk_plan *p)
             inst_rest.push_back(rest);
             inst_cls.push_back(cls_box);
             inst_lneed.push_back(Lneed);
+            inst_wraps.push_back(wraps ? 1 : 0);
         }
         build_work(p->row_work, i, na, kBlock);
         inst_dils.push_back({dils[0], dils[1], dils[2]});
+        inst_halo.push_back({halo[0], halo[1], halo[2]});
         build_work(p->split_work, i, na, kBlock / std::max(2, group_of(p->qs)));
         p->n_nodes += J;
         p->n_active += na;
@@ -803,7 +824,8 @@ fk_status build_plan(fk_plan *p)
                 double hmin = 1e300;
                 for (int k = 1; k < pr.ax[a].n; ++k)
                     hmin = std::min(hmin, pr.ax[a].nodes[k] - pr.ax[a].nodes[k - 1]);
-                int L = (int)std::floor(2.0 * I.S * amax / hmin) + 3;
+                int L = footprint(I.S * amax, hmin);
+                p->inst.back().sep_l[a] = L;
                 L = std::min(L, pr.ax[a].n);
                 p->inst.back().ell_box[a] = L;
                 box[a] = std::max(box[a], L);
@@ -838,14 +860,10 @@ fk_status build_plan(fk_plan *p)
         if (sk == 2 || !node_ok || faces_r2) p->step_kind = 1;
         else if (sk == 3 || (sk == 0 && !large)) p->step_kind = 2;
         else p->step_kind = 0;
-        // the separable form by default in 3D only: there a node's Q*^3
-        // points gather 8 corners each, against L^3 records of its footprint;
-        // in 2D (Q*^2 points x 4 corners vs L^2) the per-point gather is faster
-        // the R2 interpolant in 3D: thread-per-node kernels only (the 2D box
-        // and lane-group forms carry the 2D twist)
-        const bool r2 = p->opt.hermite == FK_HERMITE_R2 && p->d == 3;
-        p->use_box = node_ok && affine && !p->faces && !r2 && fk::box_compiled(p->d, p->qs) &&
-                     (sk == 4 || (sk == 0 && large && p->d == 3));
+        // the separable form by default: a node's Q*^d points gather 2^d
+        // corners each, against the product of its footprint's lengths
+        p->use_box = node_ok && affine && !p->faces && fk::box_compiled(p->d, p->qs) &&
+                     (sk == 4 || (sk == 0 && large));
         const int gs = std::max(2, group_of(p->qs));
         std::vector<std::vector<fk::WorkItem>> bw(fk::kBoxClasses);
         // node lists in patch order (16x16 in 2D, 4x8x8 in 3D, 256 in 1D):
@@ -853,8 +871,8 @@ fk_status build_plan(fk_plan *p)
         // the adjoint's LDS tile of mu) stays compact
         static const int kPatch[3][3] = {{256, 1, 1}, {16, 16, 1}, {4, 8, 8}};
         auto patch_sort = [&](std::vector<int> &list, const fk_problem &pr,
-                              std::vector<long long> &keys) {
-            const int *pd = kPatch[pr.d - 1];
+                              std::vector<long long> &keys, const int *pd = nullptr) {
+            if (!pd) pd = kPatch[pr.d - 1];
             std::vector<std::pair<long long, int>> kv;
             kv.reserve(list.size());
             for (int j : list) {
@@ -896,25 +914,30 @@ fk_status build_plan(fk_plan *p)
         for (int i = 0; i < p->n_inst; ++i) {
             const fk_problem &pr = p->probs[i];
             std::vector<int> fw = inst_rest[i];
-            // the box form up to 5-node footprints: from L = 6 on the box step's
-            // vectors no longer fit the registers (measured on 65^3 ABC flows:
-            // L = 3 and 5 six and four times faster than a thread per node, L = 6
-            // five times slower)
-            if (!p->use_box || inst_cls[i] < 0 || inst_cls[i] > 2) {
+            if (!p->use_box || inst_cls[i] < 0) {
                 fw.insert(fw.end(), inst_sep[i].begin(), inst_sep[i].end());
             } else {
                 std::vector<int> sep = inst_sep[i];
                 patch_sort(sep, pr, keys);
                 const int f0 = (int)p->box_nodes.size();
                 p->box_nodes.insert(p->box_nodes.end(), sep.begin(), sep.end());
-                patch_work(bw[inst_cls[i]], i, keys, f0, kBlock);
+                std::vector<fk::WorkItem> &bi = bw[inst_cls[i]];
+                const size_t b0 = bi.size();
+                // full workgroups, across patches (the step keeps no tile)
+                build_work(bi, i, (int)sep.size(), kBlock, f0);
+                for (size_t t = b0; t < bi.size(); ++t) {
+                    bool all = true;
+                    for (int u = 0; u < bi[t].count && all; ++u)
+                        all = inst_inner[i][p->box_nodes[bi[t].first + u]] != 0;
+                    bi[t].kind = all ? 1 : 0;
+                }
             }
             patch_sort(fw, pr, keys);
             const int f1 = (int)p->fw_nodes.size();
             p->fw_nodes.insert(p->fw_nodes.end(), fw.begin(), fw.end());
             const size_t w0 = p->fw_work.size(), ws0 = p->fw_split_work.size();
-            patch_work(p->fw_work, i, keys, f1, kBlock);
-            patch_work(p->fw_split_work, i, keys, f1, kBlock / gs);
+            build_work(p->fw_work, i, (int)fw.size(), kBlock, f1);
+            build_work(p->fw_split_work, i, (int)fw.size(), kBlock / gs, f1);
             // kind 1: no landing point of any node of the item can exit
             auto mark = [&](std::vector<fk::WorkItem> &v, size_t from) {
                 for (size_t t = from; t < v.size(); ++t) {
@@ -939,8 +962,11 @@ fk_status build_plan(fk_plan *p)
         const size_t elt_b = 8;   // tiles accumulate in FP64 in both precisions
         const size_t budget = 60 * 1024;   // plus static LDS, within 64 KB per workgroup
         // wrap: a periodic axis' tile may run past the seam (unwrapped indices,
-        // less than one period long); the kernel then indexes it unwrapped
-        auto tile_of = [&](const fk::WorkItem &it, const std::vector<int> &list, bool wrap) {
+        // less than one period long); the kernel then indexes it unwrapped.
+        // ext: the node box widened by h; pitch of the innermost axis chosen by
+        // the caller's rule when that keeps the tile within `limit` bytes
+        auto tile_of = [&](const fk::WorkItem &it, const std::vector<int> &list, bool wrap,
+                           const std::array<int, 3> &h, auto &&pitch_of, size_t limit, size_t *bytes) {
             const fk_problem &pr = p->probs[it.inst];
             int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-1, -1, -1};
             for (int t = 0; t < it.count; ++t) {
@@ -957,8 +983,7 @@ fk_status build_plan(fk_plan *p)
             bool ok = it.count > 0;
             size_t elems = NF;
             for (int a = 0; a < pr.d; ++a) {
-                const int dil = inst_dils[it.inst][a];
-                int lo = mn[a] - dil, hi = mx[a] + dil;
+                int lo = mn[a] - h[a], hi = mx[a] + h[a];
                 if (pr.ax[a].periodic && (lo < 0 || hi > pr.ax[a].n - 1)) {
                     if (!wrap || hi - lo + 1 > pr.ax[a].n - 1) ok = false;
                 } else {
@@ -970,85 +995,155 @@ fk_status build_plan(fk_plan *p)
                 if (a < pr.d - 1) elems *= (size_t)tb.ext[a];
             }
             for (int a = pr.d; a < 3; ++a) tb.ext[a] = 1;
-            // pitch of the innermost axis: in 2D and 3D, the next length that is
-            // 16 (2D) or 8 (3D) modulo 32 words, unless that breaks the budget
             const int last = tb.ext[pr.d - 1];
             int pitch = last;
             if (pr.d >= 2) {
-                const int want = pr.d == 2 ? 16 : 8;
-                int padded = last;
-                while (padded % 32 != want) ++padded;
-                if (elems * (size_t)padded * elt_b <= budget) pitch = padded;
+                const int padded = pitch_of(last);
+                if (elems * (size_t)padded * elt_b <= limit) pitch = padded;
             }
             tb.pad = pitch;
             elems *= (size_t)pitch;
-            if (elems * elt_b > budget) ok = false;
+            if (elems * elt_b > limit) ok = false;
             tb.use_lds = ok ? 1 : 0;
-            if (ok) p->tile_elems = std::max<int>(p->tile_elems, (int)elems);
+            *bytes = elems * elt_b;
             return tb;
         };
-        // adjoint lists: separable nodes in box form when their footprint fits
-        // a class (the transposed row then scatters 3 L^2 (2D) entries instead
-        // of 12 per landing point), the others per landing point
+        // the pitch, at most a quarter longer than the row, whose rows (16 nodes
+        // by 4 in 2D, 8 by 8 in 3D: a wave's part of a patch) fall on the 32
+        // double-wide LDS banks most evenly
+        auto pitch_wave = [&](int last) {
+            const int nc = p->d == 2 ? 16 : 8, nr = 64 / nc;
+            int best = last, bl = 1 << 30;
+            for (int c = last; c <= std::max(last + 3, last * 5 / 4); ++c) {
+                int load[32] = {0}, mx = 0;
+                for (int r = 0; r < nr; ++r)
+                    for (int k = 0; k < nc; ++k) mx = std::max(mx, ++load[(r * c + k) % 32]);
+                if (mx < bl) {
+                    bl = mx;
+                    best = c;
+                }
+            }
+            return best;
+        };
+        // adjoint lists: separable nodes by footprint class in the separable
+        // form, up to 15 nodes per axis in 2D (wider footprints add more
+        // entries than 12 per landing point) and 12 in 3D, the others per
+        // landing point
         if (p->opt.ckpt_every > 0) {
-            // 2D: footprints up to 6 nodes; wider ones scatter faster per point
-            // (measured: the box form's vector building and L^2 gathers cost
-            // more than the FP64 LDS atomics they save from L = 8 on)
-            static const int kLA[2][fk::kBoxClasses] = {{4, 6, 0, 0, 0}, {3, 4, 5, 6, 8}};
             const bool abox = node_ok && affine && p->d >= 2 && fk::box_compiled(p->d, p->qs) &&
-                              sk != 1 && sk != 2;
+                              sk != 1 && sk != 2 && p->step_kind != 1;
             std::vector<std::vector<fk::WorkItem>> abw(fk::kBoxClasses);
+            std::vector<std::vector<fk::TileBox>> abt(fk::kBoxClasses);
             for (int i = 0; i < p->n_inst; ++i) {
                 const fk_problem &pr = p->probs[i];
-                int ac = -1;
-                if (abox)
-                    for (int c2 = 0; c2 < fk::kBoxClasses && ac < 0; ++c2)
-                        if (inst_lneed[i] <= kLA[p->d - 2][c2]) ac = c2;
+                const int cls = inst_cls[i];
+                bool sep_form = abox && cls >= 0 && !inst_sep[i].empty();
                 std::vector<int> fw = inst_rest[i];
-                if (ac < 0) {
-                    fw.insert(fw.end(), inst_sep[i].begin(), inst_sep[i].end());
-                } else {
-                    std::vector<int> sep = inst_sep[i];
-                    patch_sort(sep, pr, keys);
-                    const int f0 = (int)p->adj.box_nodes.size();
-                    p->adj.box_nodes.insert(p->adj.box_nodes.end(), sep.begin(), sep.end());
-                    patch_work(abw[ac], i, keys, f0, kBlock);
+                // the columns of a workgroup's threads; patches halved along their
+                // longest axis until columns, tile and slack fit the LDS
+                size_t cols = 0;
+                if (sep_form) {
+                    const int Lc = fk::box_len(p->d, cls), *L = p->inst[i].sep_l;
+                    const bool un = p->d == 3 && Lc <= 4;
+                    const int l0 = un ? Lc : std::min(L[0], Lc), l1 = un ? Lc : std::min(L[1], Lc);
+                    const int l2 = p->d < 3 ? 0 : (un ? Lc : std::min(L[2], Lc));
+                    const int entries = p->d == 2 ? std::max(l0, l1) + 2
+                                                  : std::max(l0, l2) + 2 + (un ? 1 : 2) * (l1 + 2);
+                    cols = (size_t)entries * fk::adj_threads(p->d, Lc, p->f32) * 2 * (p->f32 ? 4 : 8);
                 }
+                const size_t slack = 16 * elt_b;
+                int pd[3] = {kPatch[p->d - 1][0], kPatch[p->d - 1][1], kPatch[p->d - 1][2]};
+                while (sep_form) {
+                    std::vector<int> sep = inst_sep[i];
+                    std::vector<fk::WorkItem> items;
+                    std::vector<fk::TileBox> tiles;
+                    patch_sort(sep, pr, keys, pd);
+                    const int f0 = (int)p->adj.box_nodes.size();
+                    patch_work(items, i, keys, 0, kBlock);
+                    size_t need = 0;
+                    bool fit = cols + slack < (size_t)fk::kAdjLdsMax;
+                    for (fk::WorkItem &it : items) {
+                        size_t b = 0;
+                        tiles.push_back(tile_of(it, sep, true, inst_halo[i], pitch_wave,
+                                                (size_t)fk::kAdjLdsMax - std::min((size_t)fk::kAdjLdsMax, cols + slack), &b));
+                        need = std::max(need, cols + b + slack);
+                        fit = fit && tiles.back().use_lds;
+                        bool all = true;
+                        for (int u = 0; u < it.count && all; ++u) all = inst_inner[i][sep[it.first + u]] != 0;
+                        it.kind = all ? 1 : 0;
+                        it.first += f0;
+                    }
+                    if (!fit) {
+                        int *m = std::max_element(pd, pd + p->d);
+                        if (*m <= 2) sep_form = false;
+                        *m /= 2;
+                        continue;
+                    }
+                    p->adj.box_nodes.insert(p->adj.box_nodes.end(), sep.begin(), sep.end());
+                    abw[cls].insert(abw[cls].end(), items.begin(), items.end());
+                    abt[cls].insert(abt[cls].end(), tiles.begin(), tiles.end());
+                    p->adj.box_lds[cls] = std::max(p->adj.box_lds[cls], (int)need);
+                    break;
+                }
+                if (!sep_form) fw.insert(fw.end(), inst_sep[i].begin(), inst_sep[i].end());
                 patch_sort(fw, pr, keys);
                 const int f1 = (int)p->adj.fw_nodes.size();
                 p->adj.fw_nodes.insert(p->adj.fw_nodes.end(), fw.begin(), fw.end());
                 patch_work(p->adj.fw_work, i, keys, f1, kBlock);
             }
-            // 2D: work items none of whose nodes has a landing point that can
-            // exit go first (their kernel has no exit tests)
-            if (p->d == 2) {
-                std::vector<fk::WorkItem> in, rest;
-                for (fk::WorkItem it : p->adj.fw_work) {
-                    bool all = true;
-                    for (int u = 0; u < it.count && all; ++u)
-                        all = inst_inner[it.inst][p->adj.fw_nodes[it.first + u]] != 0;
-                    it.kind = all ? 1 : 0;
-                    (all ? in : rest).push_back(it);
-                }
-                p->adj.n_in_work = (int)in.size();
-                in.insert(in.end(), rest.begin(), rest.end());
-                p->adj.fw_work.swap(in);
+            // kind 1: no landing point of any node of the item can exit
+            for (fk::WorkItem &it : p->adj.fw_work) {
+                bool all = true;
+                for (int u = 0; u < it.count && all; ++u)
+                    all = inst_inner[it.inst][p->adj.fw_nodes[it.first + u]] != 0;
+                it.kind = all ? 1 : 0;
             }
             for (int c2 = 0; c2 < fk::kBoxClasses; ++c2) {
                 p->adj.box_work_off[c2] = (int)p->adj.box_work.size();
                 p->adj.n_box_work[c2] = (int)abw[c2].size();
                 p->adj.box_work.insert(p->adj.box_work.end(), abw[c2].begin(), abw[c2].end());
+                p->adj.box_tiles.insert(p->adj.box_tiles.end(), abt[c2].begin(), abt[c2].end());
             }
-            for (const fk::WorkItem &it : p->adj.fw_work)
-                p->adj.fw_tiles.push_back(tile_of(it, p->adj.fw_nodes, false));
-            for (const fk::WorkItem &it : p->adj.box_work)
-                // the box kernels index their tiles with unwrapped indices
-                p->adj.box_tiles.push_back(tile_of(it, p->adj.box_nodes, true));
+            // per landing point: by tile bytes (eight, four and two workgroups per
+            // CU), a tile that does not fit in the last class
+            static const size_t kTileLds[fk::kTileClasses] = {20 * 1024, 40 * 1024, 60 * 1024};
+            std::vector<std::vector<fk::WorkItem>> fww(fk::kTileClasses);
+            std::vector<std::vector<fk::TileBox>> fwt(fk::kTileClasses);
+            for (const fk::WorkItem &it : p->adj.fw_work) {
+                size_t b = 0;
+                const fk::TileBox tb = tile_of(it, p->adj.fw_nodes, false, inst_halo[it.inst], pitch_wave, budget, &b);
+                int c2 = 0;
+                while (c2 < fk::kTileClasses - 1 && (!tb.use_lds || b > kTileLds[c2])) ++c2;
+                fww[c2].push_back(it);
+                fwt[c2].push_back(tb);
+                if (tb.use_lds) p->adj.fw_lds[c2] = std::max(p->adj.fw_lds[c2], (int)b);
+            }
+            p->adj.fw_work.clear();
+            for (int c2 = 0; c2 < fk::kTileClasses; ++c2) {
+                p->adj.fw_work_off[c2] = (int)p->adj.fw_work.size();
+                p->adj.n_fw_work[c2] = (int)fww[c2].size();
+                p->adj.fw_work.insert(p->adj.fw_work.end(), fww[c2].begin(), fww[c2].end());
+                p->adj.fw_tiles.insert(p->adj.fw_tiles.end(), fwt[c2].begin(), fwt[c2].end());
+            }
             stage_tiles(p);
         }
     }
-    p->slope_work = tables;
-    p->slope_work.insert(p->slope_work.end(), runs.begin(), runs.end());
+    // slope pass: pieces of the reachable boxes, 1024 nodes each (four per
+    // thread) when that still gives every CU its eight workgroups, else 256
+    {
+        long long box_nodes_all = 0;
+        std::vector<long long> box_n(p->n_inst, 0);
+        for (int i = 0; i < p->n_inst; ++i) {
+            if (p->inst[i].blen[0] == 0) continue;
+            box_n[i] = 1;
+            for (int a = 0; a < p->d; ++a) box_n[i] *= p->inst[i].blen[a];
+            box_nodes_all += box_n[i];
+        }
+        const int piece = box_nodes_all >= 1024LL * 256 * 8 ? 4 * kBlock : kBlock;
+        p->slope_work = tables;
+        for (int i = 0; i < p->n_inst; ++i) build_work(p->slope_work, i, (int)box_n[i], piece);
+        p->run_work = runs;
+    }
     p->n_table_work = (int)tables.size();
 
     // per-(step, instance) time factors
@@ -1203,6 +1298,7 @@ fk_status build_plan(fk_plan *p)
     add_region(p, "tfac", sizeof(double) * p->tfac.size());
     add_region(p, "trig", sizeof(double) * 2 * std::max<size_t>(p->coords.size(), 1));
     add_region(p, "slope_work", sizeof(fk::WorkItem) * std::max<size_t>(p->slope_work.size(), 1));
+    add_region(p, "run_work", sizeof(fk::WorkItem) * std::max<size_t>(p->run_work.size(), 1));
     add_region(p, "node_work", sizeof(fk::WorkItem) * std::max<size_t>(p->node_work.size(), 1));
     add_region(p, "act_work", sizeof(fk::WorkItem) * std::max<size_t>(p->act_work.size(), 1));
     add_region(p, "ell_work", sizeof(fk::WorkItem) * std::max<size_t>(p->ell_work.size(), 1));
@@ -1267,6 +1363,9 @@ void fill_dev(fk_plan *p)
     D.tfac = (const double *)p->at("tfac");
     D.trig = (double2 *)p->at("trig");
     D.slope_work = (const fk::WorkItem *)p->at("slope_work");
+    D.run_work = (const fk::WorkItem *)p->at("run_work");
+    D.n_run_work = (int)p->run_work.size();
+    D.run_grid = grid_for(p->run_work.size());
     D.node_work = (const fk::WorkItem *)p->at("node_work");
     D.act_work = (const fk::WorkItem *)p->at("act_work");
     D.ell_work = (const fk::WorkItem *)p->at("ell_work");
@@ -1300,10 +1399,12 @@ void fill_dev(fk_plan *p)
     D.adj.fw_nodes = (const int *)p->at("afw_nodes");
     D.adj.fw_work = (const fk::WorkItem *)p->at("afw_work");
     D.adj.fw_tiles = (const fk::TileBox *)p->at("afw_tiles");
-    D.adj.n_in_work = p->adj.n_in_work;
-    D.adj.n_fw_work = (int)p->adj.fw_work.size() - p->adj.n_in_work;
-    D.adj.in_grid = grid_for(p->adj.n_in_work);
-    D.adj.fw_grid = grid_for(D.adj.n_fw_work);
+    for (int c = 0; c < fk::kTileClasses; ++c) {
+        D.adj.fw_work_off[c] = p->adj.fw_work_off[c];
+        D.adj.n_fw_work[c] = p->adj.n_fw_work[c];
+        D.adj.fw_grid[c] = grid_for(p->adj.n_fw_work[c]);
+        D.adj.fw_lds[c] = p->adj.fw_lds[c];
+    }
     D.adj.box_nodes = (const int *)p->at("abox_nodes");
     D.adj.box_work = (const fk::WorkItem *)p->at("abox_work");
     D.adj.box_tiles = (const fk::TileBox *)p->at("abox_tiles");
@@ -1317,6 +1418,7 @@ void fill_dev(fk_plan *p)
         D.adj.box_work_off[c2] = p->adj.box_work_off[c2];
         D.adj.n_box_work[c2] = p->adj.n_box_work[c2];
         D.adj.box_grid[c2] = grid_for(p->adj.n_box_work[c2]);
+        D.adj.box_lds[c2] = p->adj.box_lds[c2];
     }
     D.fw_nodes = (const int *)p->at("fw_nodes");
     D.fw_work = (const fk::WorkItem *)p->at("fw_work");
@@ -1332,7 +1434,6 @@ void fill_dev(fk_plan *p)
         D.n_box_work[c2] = p->n_box_work[c2];
         D.box_grid[c2] = grid_for(p->n_box_work[c2]);
     }
-    D.tile_elems = p->tile_elems;
     D.n_split_work = (int)p->split_work.size();
     D.split_grid = grid_for(p->split_work.size());
     D.flags = (int *)p->at("flags");
@@ -1355,6 +1456,7 @@ void fill_dev(fk_plan *p)
     for (const fk::DevInst &I : p->inst)
         for (int a = 0; a < p->d; ++a)
             if (!I.affine[a]) D.all_affine = 0;
+    D.rel_ok = D.all_affine && !p->wraps ? 1 : 0;
     D.step_kind = p->step_kind;
     D.slope_grid = grid_for(p->slope_work.size());
     D.node_grid = grid_for(p->node_work.size());
@@ -1826,6 +1928,7 @@ fk_status upload_tables(fk_plan *p, hipStream_t s)
     FK_TRY(up("gh_w1f", p->gh_w1f.data(), sizeof(float) * p->gh_w1f.size()));
     FK_TRY(up("tfac", p->tfac.data(), sizeof(double) * p->tfac.size()));
     FK_TRY(up("slope_work", p->slope_work.data(), sizeof(fk::WorkItem) * p->slope_work.size()));
+    FK_TRY(up("run_work", p->run_work.data(), sizeof(fk::WorkItem) * p->run_work.size()));
     FK_TRY(up("node_work", p->node_work.data(), sizeof(fk::WorkItem) * p->node_work.size()));
     FK_TRY(up("act_work", p->act_work.data(), sizeof(fk::WorkItem) * p->act_work.size()));
     FK_TRY(up("ell_work", p->ell_work.data(), sizeof(fk::WorkItem) * p->ell_work.size()));

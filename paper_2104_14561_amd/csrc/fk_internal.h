@@ -11,7 +11,30 @@ namespace fk {
 constexpr int kMaxDim = 3;
 constexpr int kTimeFactors = 4;   // per (step, instance) time table entries
 constexpr int kThetaSlots = 8;    // gradient entries per instance (FK_MAX_THETA)
-constexpr int kBoxClasses = 5;    // separable-form box sizes L = 3, 4, 5, 6, 8
+constexpr int kBoxClasses = 5;    // separable-form footprint classes
+
+constexpr int kTileClasses = 3;   // classes of the per-point transposed step's tiles
+constexpr int kAdjLdsMax = 159 * 1024;   // dynamic LDS of a transposed step, of a CU's 160 KB
+
+// Longest footprint (nodes per axis) of a class of the separable form, and the
+// threads of a workgroup that takes its 256-node work items.  Forward: 128 for
+// the wide classes in FP64 (3D: from 9 nodes on in FP32 too), so that their LDS
+// columns leave room for more than one workgroup per CU.  Transposed: 256 share
+// a tile, except in 3D in FP64 from 9 nodes on, whose columns would not fit
+// beside it.
+inline int box_len(int d, int c)
+{
+    constexpr int l2[kBoxClasses] = {6, 9, 12, 15, 0}, l3[kBoxClasses] = {3, 4, 6, 9, 12};
+    return d == 2 ? l2[c] : l3[c];
+}
+constexpr int adj_threads(int d, int L, bool f32)
+{
+    return d == 3 && L > 6 && !f32 ? 128 : 256;
+}
+constexpr int box_threads(int d, int L, bool f32)
+{
+    return d == 2 ? (L > 6 && !f32 ? 128 : 256) : (L > 6 || (L > 4 && !f32) ? 128 : 256);
+}
 
 // Per-instance record read by every kernel (one per instance of a plan).
 struct DevInst {
@@ -48,7 +71,9 @@ struct DevInst {
     long long out_off;
     int face[kMaxDim][2];          // FK_FACE_* per axis and side
     int sdiff;                     // diffusion depends on the node (runaway model)
-    int pad1;
+    int blo[kMaxDim];              // reachable box (the nodes a step's gathers can touch):
+    int blen[kMaxDim];             // first node and length per axis (0 without active nodes)
+    int sep_l[kMaxDim];            // footprint nodes per axis of one node's landing cells
 };
 
 // A contiguous chunk of one instance's nodes (slope pass) or active nodes
@@ -73,17 +98,16 @@ struct TileBox {
 };
 
 // The adjoint's work lists: active nodes handled per landing point (fw) and
-// separable nodes handled in box form by footprint class, each work item with
-// its LDS tile.  Box classes: L = 4, 6 in 2D; 3, 4, 5, 6, 8 in 3D.
+// separable nodes by footprint class (box), each work item with its LDS tile.
 struct AdjLists {
     const int *fw_nodes;
     const WorkItem *fw_work;
     const TileBox *fw_tiles;
-    int n_fw_work;
-    int fw_grid;
-    // the first n_in_work items: no landing point of any of their nodes can exit
-    int n_in_work;
-    int in_grid;
+    // by class of tile bytes, each launch's dynamic LDS its largest tile
+    int fw_work_off[kTileClasses];
+    int n_fw_work[kTileClasses];
+    int fw_grid[kTileClasses];
+    int fw_lds[kTileClasses];
     // tile staging: each tile's entries (fields interleaved) at its soff; per
     // node the staging entries (field 0) of the tiles that cover it
     void *stage;                // T, or null when the tiles flush with atomics
@@ -91,12 +115,15 @@ struct AdjLists {
     const int *cov_node;        // [n_cov] packed node index
     const int *cov_ptr;         // [n_cov + 1] into cov_base
     const int *cov_base;        // staging index of field 0, per (node, covering tile)
+    // separable nodes by footprint class (box_len), each launch's dynamic LDS
+    // the largest of its work items'
     const int *box_nodes;
     const WorkItem *box_work;
     const TileBox *box_tiles;
     int box_work_off[kBoxClasses];
     int n_box_work[kBoxClasses];
     int box_grid[kBoxClasses];
+    int box_lds[kBoxClasses];
 };
 
 // Pointers into the workspace that every launch needs.
@@ -112,7 +139,8 @@ struct PlanDev {
     const float *gh_w1f;        // 1D weights (Q*), float
     const double *tfac;         // [n_steps][n_inst][kTimeFactors]
     double2 *trig;              // per-axis (sin, cos) of the drift arguments at t_n
-    const WorkItem *slope_work; // trig table items, then node runs near active nodes
+    const WorkItem *slope_work; // trig table items, then pieces of the reachable boxes
+    const WorkItem *run_work;   // the reachable boxes as node runs along the last axis (adjoint)
     const WorkItem *node_work;  // all nodes (adjoint passes)
     const WorkItem *act_work;   // step pass work list (block / G active nodes each)
     const WorkItem *row_work;   // row-per-thread work list (block active nodes each)
@@ -120,6 +148,7 @@ struct PlanDev {
     int n_inst;
     int n_slope_work;
     int n_table_work;
+    int n_run_work;
     int n_node_work;
     int n_act_work;
     int n_row_work;
@@ -131,6 +160,7 @@ struct PlanDev {
     int group;                  // lanes per active node in the step passes
     int step_kind;              // 0: thread per node, 1: lane group, 2: split node
     int all_affine;             // every axis of every instance is affine
+    int rel_ok;                 // all_affine, and no landing point more than one period away
     int hermite2;               // R2 interpolant: 2D twist field in the records' fourth entry,
                                 // 3D twist fields in a second record per node (packed2)
     void *packed2;              // 3D R2: (t01, t02, t12, t012) per node, or null
@@ -150,11 +180,11 @@ struct PlanDev {
     int n_box_work[kBoxClasses];
     int box_grid[kBoxClasses];
     AdjLists adj;               // adjoint step work
-    int tile_elems;             // LDS entries (FP64) of the largest adjoint tile in use
     const WorkItem *split_work; // chunks of block / pow2(Q*) active nodes
     int n_split_work;
     int split_grid;
     int slope_grid;             // workgroups of the slope pass
+    int run_grid;               // workgroups of passes over run_work
     int node_grid;              // workgroups of all-node passes
     int act_grid;               // workgroups of the step pass
     int row_grid;               // workgroups of row-per-thread passes

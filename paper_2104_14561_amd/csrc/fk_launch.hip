@@ -1,5 +1,4 @@
-// fk_launch.hip -- launchers of the slope pass, the lane-group step and
-// adjoint (any Q*), the assembled (ELL) form, exports and utility fills.  The
+// fk_launch.hip -- launchers of the lane-group step and adjoint (any Q*), the assembled (ELL) form, exports and utility fills.  The
 // thread-per-node and separable-box launchers live in the fk_node_inst.hip
 // instances; launch_step_fused and launch_adjoint_step pick one of them when
 // the plan's Q* has a compiled specialisation and fall back to the lane-group
@@ -50,24 +49,6 @@ hipError_t launch_init_field(const PlanDev &P, bool f32, void *u, hipStream_t s)
         k_init_field<float><<<flat_grid(P.n_nodes), kBlock, 0, s>>>(P.chi, P.n_nodes, (float *)u);
     else
         k_init_field<double><<<flat_grid(P.n_nodes), kBlock, 0, s>>>(P.chi, P.n_nodes, (double *)u);
-    return hipGetLastError();
-}
-
-hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void *packed,
-                         hipStream_t s)
-{
-    FK_DISPATCH_D(P.d,
-        if (f32) k_slopes<float, D><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const float *)u, (float *)packed);
-        else k_slopes<double, D><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const double *)u, (double *)packed));
-    return hipGetLastError();
-}
-
-hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s)
-{
-    if (P.n_table_work == 0) return hipSuccess;
-    const int g = P.n_table_work >= 8 ? (P.n_table_work + 7) / 8 * 8 : P.n_table_work;
-    FK_DISPATCH_D(P.d,
-        k_slopes<double, D><<<g, kBlock, 0, s>>>(P, n, 0, P.n_table_work, nullptr, nullptr));
     return hipGetLastError();
 }
 
@@ -242,7 +223,8 @@ hipError_t launch_adjoint_step(const PlanDev &P0, bool f32, int n, const void *p
         PlanDev P = P0;
         if (part == 1)
             for (int c = 0; c < kBoxClasses; ++c) P.adj.n_box_work[c] = 0;
-        if (part == 2) P.adj.n_fw_work = P.adj.n_in_work = 0;
+        if (part == 2)
+            for (int c = 0; c < kTileClasses; ++c) P.adj.n_fw_work[c] = 0;
         bool ok = false;
         switch (P.d) {
         case 1: ok = f32 ? adjoint_node_f32_d1(P, n, packed, lam, mu, grad, s) : adjoint_node_f64_d1(P, n, packed, lam, mu, grad, s); break;
@@ -273,10 +255,10 @@ hipError_t launch_adjoint_slopes_T(const PlanDev &P, bool f32, const void *u, vo
 {
     // every node an adjoint step can touch lies in the slope pass' node runs
     // (the active region widened by the reach and the slope stencil)
-    const WorkItem *runs = P.slope_work;
-    const int r0 = P.n_table_work, nr = P.n_slope_work - P.n_table_work;
+    const WorkItem *runs = P.run_work;
+    const int r0 = 0, nr = P.n_run_work;
     if (nr <= 0) return hipSuccess;
-    const int g = P.slope_grid;
+    const int g = P.run_grid;
     FK_DISPATCH_D(P.d,
         if (f32) {
             k_mu_value<float, D><<<g, kBlock, 0, s>>>(P, (float *)mu, (float *)lam_next, runs, r0, nr);

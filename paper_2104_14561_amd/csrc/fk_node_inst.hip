@@ -12,10 +12,8 @@
 // The separable-box kernels are compiled for d >= 2 on affine axes only: in
 // one dimension the thread-per-node kernel already contracts a single axis,
 // and the plan builder enables the box form only for plans whose axes are all
-// affine (box_compiled).  The adjoint has its own lists (P.adj): in 2D its box
-// classes are L = 4 and 6, where the saved scatter adds outweigh the cost of
-// building the weight vectors.
-#include "fk_device.h"
+// affine (box_compiled).  The adjoint has its own lists (P.adj).
+#include "fk_adj_sep.h"
 
 #if !defined(FK_INST_F32) || !defined(FK_INST_D) || !defined(FK_INST_ADJ) || !defined(FK_INST_NAME)
 #error "fk_node_inst.hip needs FK_INST_F32, FK_INST_D, FK_INST_ADJ and FK_INST_NAME"
@@ -55,6 +53,19 @@ void step_node_launch(const PlanDev &P, int n, const void *packed, void *u_out, 
         if (P.step_kind == 2) {
             if (P.all_affine) FK_NODE(GS, true, P.fw_split_grid, P.n_fw_split_work, P.fw_split_work);
             else FK_NODE(GS, false, P.fw_split_grid, P.n_fw_split_work, P.fw_split_work);
+        } else if constexpr (D == 2) {
+            // affine axes, no landing point further than one period away: the
+            // per-point form relative to the node
+            if (P.rel_ok && !P.faces) {
+                if (P.hermite2)
+                    k_step_pt2<T, QS, true><<<P.fw_split_grid, kBlock, 0, s>>>(
+                        P, n, P.n_fw_split_work, P.inst, P.fw_split_work, P.fw_nodes, P.trig, (const T *)packed, (T *)u_out);
+                else
+                    k_step_pt2<T, QS, false><<<P.fw_split_grid, kBlock, 0, s>>>(
+                        P, n, P.n_fw_split_work, P.inst, P.fw_split_work, P.fw_nodes, P.trig, (const T *)packed, (T *)u_out);
+            } else {
+                FK_NODE(1, false, P.fw_grid, P.n_fw_work, P.fw_work);
+            }
         } else {
             if (P.all_affine) FK_NODE(1, true, P.fw_grid, P.n_fw_work, P.fw_work);
             else FK_NODE(1, false, P.fw_grid, P.n_fw_work, P.fw_work);
@@ -63,14 +74,32 @@ void step_node_launch(const PlanDev &P, int n, const void *packed, void *u_out, 
 #undef FK_NODE
 #undef FK_NODE_TW
     if constexpr (D >= 2) {
-        // separable nodes, one launch per footprint class
-#define FK_BOX(c_, L_)                                                                         \
-        if (P.n_box_work[c_] > 0)                                                              \
-            k_step_box<T, D, QS, L_, true><<<P.box_grid[c_], kBlock, 0, s>>>(                  \
-                P, n, P.n_box_work[c_], P.inst, P.box_work + P.box_work_off[c_], P.box_nodes,  \
-                P.trig, P.coords, (const T *)packed, (T *)u_out);
-        FK_BOX(0, 3) FK_BOX(1, 4) FK_BOX(2, 5) FK_BOX(3, 6) FK_BOX(4, 8)
-#undef FK_BOX
+        // separable nodes, one launch per footprint class (box_len, box_threads)
+#define FK_SEP(c_, L_, TW_)                                                                    \
+        do {                                                                                   \
+            constexpr int BS_ = box_threads(D, L_, sizeof(T) == 4);                            \
+            const int nw_ = P.n_box_work[c_], g_ = P.box_grid[c_] * (kBlock / BS_);            \
+            const WorkItem *wk_ = P.box_work + P.box_work_off[c_];                             \
+            if constexpr (D == 2)                                                              \
+                k_step_sep2<T, QS, L_, BS_, TW_><<<g_, BS_, 0, s>>>(                           \
+                    P, n, nw_, P.inst, wk_, P.box_nodes, P.trig, (const T *)packed, (T *)u_out); \
+            else                                                                               \
+                k_step_sep3<T, QS, L_, BS_, TW_><<<g_, BS_, 0, s>>>(                           \
+                    P, n, nw_, P.inst, wk_, P.box_nodes, P.trig, (const T *)packed, (T *)u_out); \
+        } while (0)
+#define FK_SEP_CLASS(c_, L_)                                                                   \
+        if (P.n_box_work[c_] > 0) {                                                            \
+            if (P.hermite2) FK_SEP(c_, L_, true);                                              \
+            else FK_SEP(c_, L_, false);                                                        \
+        }
+        if constexpr (D == 2) {
+            FK_SEP_CLASS(0, 6) FK_SEP_CLASS(1, 9) FK_SEP_CLASS(2, 12) FK_SEP_CLASS(3, 15)
+        } else {
+            FK_SEP_CLASS(0, 3) FK_SEP_CLASS(1, 4) FK_SEP_CLASS(2, 6) FK_SEP_CLASS(3, 9)
+            FK_SEP_CLASS(4, 12)
+        }
+#undef FK_SEP_CLASS
+#undef FK_SEP
     }
 }
 
@@ -80,49 +109,52 @@ template <typename T, int D, int QS>
 void adjoint_node_launch(const PlanDev &P, int n, const void *packed, const void *lam, void *mu,
                          double *grad, hipStream_t s)
 {
-    const size_t lds = (size_t)P.tile_elems * sizeof(double);   // FP64 tiles
     const AdjLists &A = P.adj;
-    // interior items (no exit tests; 2D plans only) first, then the rest
-    if constexpr (D == 2) if (A.n_in_work > 0) {
-        if (P.all_affine)
-            k_adjoint_node<T, D, QS, true, true><<<A.in_grid, kBlock, lds, s>>>(
-                P, n, A.n_in_work, P.inst, A.fw_work, A.fw_tiles, A.fw_nodes, P.trig, P.coords,
-                (const T *)packed, (const T *)lam, (T *)mu, grad);
-        else
-            k_adjoint_node<T, D, QS, false, true><<<A.in_grid, kBlock, lds, s>>>(
-                P, n, A.n_in_work, P.inst, A.fw_work, A.fw_tiles, A.fw_nodes, P.trig, P.coords,
-                (const T *)packed, (const T *)lam, (T *)mu, grad);
-    }
-    if (A.n_fw_work > 0) {
-        const WorkItem *wk = A.fw_work + A.n_in_work;
-        const TileBox *tl = A.fw_tiles + A.n_in_work;
-        if (P.all_affine)
-            k_adjoint_node<T, D, QS, true, false><<<A.fw_grid, kBlock, lds, s>>>(
-                P, n, A.n_fw_work, P.inst, wk, tl, A.fw_nodes, P.trig, P.coords,
-                (const T *)packed, (const T *)lam, (T *)mu, grad);
-        else
-            k_adjoint_node<T, D, QS, false, false><<<A.fw_grid, kBlock, lds, s>>>(
-                P, n, A.n_fw_work, P.inst, wk, tl, A.fw_nodes, P.trig, P.coords,
+    for (int c = 0; c < kTileClasses; ++c) {
+        if (A.n_fw_work[c] == 0) continue;
+        const WorkItem *wk = A.fw_work + A.fw_work_off[c];
+        const TileBox *tl = A.fw_tiles + A.fw_work_off[c];
+        bool done = false;
+        if constexpr (D == 2)
+            if (P.rel_ok) {
+                // the rows' static LDS on top of the tile: raise the limit past 64 KB
+                if (A.fw_lds[c] + 40 * 1024 > 64 * 1024)
+                    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_adjoint_pt2<T, QS>),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, A.fw_lds[c]);
+                k_adjoint_pt2<T, QS><<<A.fw_grid[c], 64 * QS, A.fw_lds[c], s>>>(
+                    P, n, A.n_fw_work[c], P.inst, wk, tl, A.fw_nodes, P.trig, (const T *)packed,
+                    (const T *)lam, (T *)mu, grad);
+                done = true;
+            }
+        if (!done)
+            k_adjoint_node<T, D, QS><<<A.fw_grid[c], kBlock, A.fw_lds[c], s>>>(
+                P, n, A.n_fw_work[c], P.inst, wk, tl, A.fw_nodes, P.trig, P.coords,
                 (const T *)packed, (const T *)lam, (T *)mu, grad);
     }
-    if constexpr (D == 2) {
-#define FK_ABOX(c_, L_)                                                                        \
-        if (A.n_box_work[c_] > 0)                                                              \
-            k_adjoint_box2<T, QS, L_><<<A.box_grid[c_], kBlock, lds, s>>>(                     \
+    if constexpr (D >= 2) {
+        // separable nodes, one launch per footprint class; above 64 KB of LDS the
+        // kernel's limit is raised first
+#define FK_ASEP(c_, L_)                                                                        \
+        if (A.n_box_work[c_] > 0) {                                                            \
+            constexpr int BS_ = adj_threads(D, L_, sizeof(T) == 4);                            \
+            const auto k_ = [] {                                                               \
+                if constexpr (D == 2) return &k_adjoint_sep2<T, QS, L_, BS_>;                  \
+                else return &k_adjoint_sep3<T, QS, L_, BS_>;                                   \
+            }();                                                                               \
+            if (A.box_lds[c_] > 64 * 1024)                                                     \
+                (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_),                  \
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, kAdjLdsMax); \
+            k_<<<A.box_grid[c_], BS_, A.box_lds[c_], s>>>(                                     \
                 P, n, A.n_box_work[c_], P.inst, A.box_work + A.box_work_off[c_],               \
-                A.box_tiles + A.box_work_off[c_], A.box_nodes, P.trig, P.coords,               \
-                (const T *)packed, (const T *)lam, (T *)mu, grad);
-        FK_ABOX(0, 4) FK_ABOX(1, 6)
-#undef FK_ABOX
-    } else if constexpr (D == 3) {
-#define FK_ABOX(c_, L_)                                                                        \
-        if (A.n_box_work[c_] > 0)                                                              \
-            k_adjoint_box<T, D, QS, L_, true><<<A.box_grid[c_], kBlock, lds, s>>>(             \
-                P, n, A.n_box_work[c_], P.inst, A.box_work + A.box_work_off[c_],               \
-                A.box_tiles + A.box_work_off[c_], A.box_nodes, P.trig, P.coords,               \
-                (const T *)packed, (const T *)lam, (T *)mu, grad);
-        FK_ABOX(0, 3) FK_ABOX(1, 4) FK_ABOX(2, 5) FK_ABOX(3, 6) FK_ABOX(4, 8)
-#undef FK_ABOX
+                A.box_tiles + A.box_work_off[c_], A.box_nodes, P.trig, (const T *)packed,      \
+                (const T *)lam, (T *)mu, grad);                                                \
+        }
+        if constexpr (D == 2) {
+            FK_ASEP(0, 6) FK_ASEP(1, 9) FK_ASEP(2, 12) FK_ASEP(3, 15)
+        } else {
+            FK_ASEP(0, 3) FK_ASEP(1, 4) FK_ASEP(2, 6) FK_ASEP(3, 9) FK_ASEP(4, 12)
+        }
+#undef FK_ASEP
     }
 }
 
