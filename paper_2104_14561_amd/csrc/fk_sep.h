@@ -110,7 +110,12 @@ __device__ inline void sep_vectors(const DevInst &I, int a, int idx, double bdt,
 //
 // Bound: the L1 record reads, 16 cycles of a CU per 16-byte record of a wave
 // (FP64 32), L0 L1 of them per node against 4 Q*^2 in the per-point form, and
-// about as much VALU issue.  @SEP2@
+// about as much VALU issue.  64-instance batch, per step: 0.91 million
+// separable nodes in FP32 73 us and 0.51 million in FP64 107 us over the
+// classes; a thread per node over the landing points took 182 us for the FP32
+// part with the 0.24 million other nodes (which now take 57 us, see
+// k_step_pt2), 223 us for the FP64 part (30 us now for its others).  From 16
+// nodes per axis on a footprint holds more records than the points read.
 template <typename T, int QS, int L, int BS, bool TW>
 __global__ void __launch_bounds__(BS) k_step_sep2(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
@@ -214,7 +219,8 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
 // with no weight (a branch per point would hold back the next point's reads).
 //
 // A lane holds one column's data instead of Q* (a thread per node takes 108 to
-// 156 VGPRs, three to four waves per SIMD, too few to cover the reads).  @PT2@
+// 156 VGPRs, three to four waves per SIMD).  The batch's non-separable nodes:
+// FP64 52 us a thread per node, 30 us now; FP32 54 and 57 us.
 template <typename T, int QS, bool TW>
 __global__ void __launch_bounds__(kBlock) k_step_pt2(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
@@ -332,7 +338,10 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
 // records against the axis-2 vectors.  Footprints up to 4 nodes (UN) unroll
 // the rows, wider ones loop over the instance's own L0 x L1.  TW: the R2
 // interpolant, the nodes' twist records beside the others.
-// @SEP3@
+// 129^3 ABC flow (3-node footprints, Q* = 6) in FP32: 64 us, 116 us with the
+// vectors selected by cell in registers and the coordinate form of the landing
+// points; 65^3 with the R2 interpolant 18 us against 457 us over the landing
+// points; 65^3 in FP64 with 6 x 6 x 9 footprints 116 against 597 us.
 template <typename T, int QS, int L, int BS, bool TW>
 __global__ void __launch_bounds__(BS) k_step_sep3(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
