@@ -288,6 +288,15 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
 // conflict-free ds_add per lane, out[blocks] written.
 hipError_t launch_lds_atomic_probe(bool f32, int blocks, int iters, double *out, hipStream_t s);
 
+// 1D plans, steps n_hi - 1 .. n_lo in one launch (fk_line.hip): from u_in;
+// u^{n_lo} to u_out and u^m to store + (m / every - shift) fields for every m
+// divisible by `every` (each may be null).  Affine axes of at most nmax nodes,
+// no landing point more than one period away, exit-1 faces, a compiled Q*.
+hipError_t launch_line_steps(const PlanDev &P, bool f32, int nmax, int n_hi, int n_lo, const void *u_in,
+                             void *u_out, void *store, int every, int shift, hipStream_t s);
+constexpr int kLineNodes = 4096;   // its longest axis: two record buffers and the masks in LDS
+inline size_t line_lds(int nmax, bool f32) { return (size_t)nmax * (2 * 2 * (f32 ? 4 : 8) + 5); }
+
 // Device address of the static scratch array on the current device (taken
 // with hipGetSymbolAddress on the first call per device).
 hipError_t static_scratch(void **out);

@@ -1,0 +1,83 @@
+"""One-dimensional plans, whose steps run several to a launch, against the
+oracle: a thread per node and quarter of the rule (up to 256 nodes), the loop
+over nodes (up to 4096) and the two-launch step past that, with exits at both
+faces, a ball, a periodic axis, landing points that hit a node exactly,
+snapshots on the way and checkpoints.
+
+Bars: FP64 1e-12, FP32 1e-5 (the stated bars of the forward pass), the stored
+checkpoints through the adjoint's gradient at 1e-10 relative."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2104_14561_amd import Plan  # noqa: E402
+
+
+def _problem(n, q=8, steps=7, kind="box", drift=0.3):
+    axis = W.uniform_axis(-1.0, 1.0, n, periodic=kind == "periodic")
+    p = W.Problem(axes=[axis], coef_kind="const", coef=(drift,), D=0.02, gh_q=q, dt=0.01, n_steps=steps)
+    if kind == "ball":
+        p = p.replace(region_kind="ball", center=(0.1, 0.0, 0.0), radius=0.7)
+    return p
+
+
+@pytest.mark.parametrize("prec,bar", [("f64", 1e-12), ("f32", 1e-5)])
+@pytest.mark.parametrize("n,q,kind", [(4, 2, "box"), (7, 3, "box"), (64, 5, "ball"), (255, 16, "box"), (256, 8, "ball"),
+                                      (257, 12, "box"), (300, 6, "periodic"), (129, 7, "periodic"), (1023, 16, "box"),
+                                      (4096, 4, "ball"), (4097, 8, "box")])
+def test_pass_and_snapshots(n, q, kind, prec, bar):
+    p = _problem(n, q, kind=kind)
+    snaps = [0, 3, 7, 6]
+    plan = Plan(p, precision=prec, use_graph=True)
+    for _ in range(2):   # the second call replays the graph
+        got = plan.split(plan.forward(snaps))[0].double().cpu().numpy()
+        if kind == "periodic":   # no exit: the zero field; a state of its own below
+            u = np.random.default_rng(3).uniform(size=n)
+            u[-1] = u[0]
+            got = plan.split(plan.forward_from(torch.from_numpy(u), 5, [0]))[0].double().cpu().numpy()
+            ref = u
+            for m in range(4, -1, -1):
+                ref = oracle.step(p, m, ref)
+            assert np.abs(got[0] - ref).max() <= bar
+        else:
+            assert np.abs(got - oracle.solve(p, snaps=snaps)).max() <= bar
+    assert plan.check_flags() == 0
+    plan.close()
+
+
+def test_translation_onto_nodes():
+    """No diffusion and a drift of whole cells: every landing point is a node,
+    the first ones the exit face itself."""
+    n, h = 65, 2.0 / 64
+    p = W.Problem(axes=[W.uniform_axis(-1.0, 1.0, n)], coef_kind="const", coef=(-3 * h / 0.01,), D=0.0, gh_q=4,
+                  dt=0.01, n_steps=3)
+    plan = Plan(p, precision="f64")
+    got = plan.split(plan.forward([0]))[0].cpu().numpy()[0]
+    plan.close()
+    assert np.abs(got - oracle.solve(p, snaps=[0])[0]).max() <= 1e-12
+
+
+@pytest.mark.parametrize("n,K", [(101, 1), (101, 3), (400, 4)])
+def test_checkpoints_and_recomputed_segments(n, K):
+    p = _problem(n, 8, steps=11)
+    lam = W.region_mean_weights(p)
+    g_ref, _ = oracle.adjoint(p, lam)
+    plan = Plan([p, _problem(n + 30, 8, steps=11)], precision="f64", ckpt_every=K)
+    u0 = plan.forward([0])
+    w = torch.zeros(plan.n_nodes, dtype=torch.float64)
+    w[:n] = torch.from_numpy(lam)
+    g, _ = plan.adjoint(w)
+    g = g.cpu().numpy()[0]
+    assert np.abs(plan.split(u0)[0][0].cpu().numpy() - oracle.solve(p, snaps=[0])[0]).max() <= 1e-12
+    assert np.abs(g - g_ref).max() <= 1e-10 * np.abs(g_ref).max()
+    plan.close()
