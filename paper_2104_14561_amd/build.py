@@ -1,7 +1,8 @@
 """Build libfkexit.so (HIP, gfx950) in-tree with hipcc.
 
 The kernels are split over several translation units: fk_slopes.hip (slope
-pass), fk_line.hip (several steps of 1D plans in one launch), fk_launch.hip (lane-group kernels, ELL form, exports) and one instance of
+pass), fk_line.hip (several steps of 1D plans in one launch),
+fk_small.hip (the one-launch step of small 2D plans), fk_launch.hip (lane-group kernels, ELL form, exports) and one instance of
 fk_node_inst.hip per (precision, dimension, forward|adjoint), each holding the
 thread-per-node and separable-box specialisations over Q*.  They compile in
 parallel."""
@@ -24,7 +25,8 @@ ARCH = os.environ.get("FKEXIT_ARCH", "gfx950")
 def units():
     """(source, object name, extra defines) of every translation unit."""
     out = [("fk_host.cpp", "fk_host", []), ("fk_launch.hip", "fk_launch", []),
-           ("fk_slopes.hip", "fk_slopes", []), ("fk_line.hip", "fk_line", [])]
+           ("fk_slopes.hip", "fk_slopes", []), ("fk_line.hip", "fk_line", []),
+           ("fk_small.hip", "fk_small", [])]
     for adj in (0, 1):
         for f32 in (1, 0):
             for d in (2, 3, 1):

@@ -285,6 +285,28 @@ __device__ inline double trig_arg(const DevInst &I, const double *tf, int a, dou
     return x;
 }
 
+// Drift of the 2D flows from the (sin, cos) of their two arguments.
+__device__ inline void drift_2d(const DevInst &I, const double *tf, double2 t0, double2 t1, double *b)
+{
+#pragma clang fp contract(off)
+    double b0, b1;
+    if (I.coef_kind == 1) {
+        const double sa = t0.x, ca = t0.y, sy = t1.x, cy = t1.y;
+        const double Api = I.coef[0] * M_PI;
+        b0 = -(Api * sa * cy);
+        b1 = Api * ca * sy;
+    } else {
+        // rolls: Pe v with v_1 = -pi cos(pi y) (sin(n x) + e cos(n x)),
+        // v_2 = n sin(pi y) (cos(n x) - e sin(n x)), e = eps cos(omega t)
+        const double s1 = t0.x, c1 = t0.y, s2 = t1.x, c2 = t1.y;
+        const double e = tf[0];
+        b0 = -(I.coef[0] * M_PI * c2 * (s1 + e * c1));
+        b1 = I.coef[0] * I.coef[3] * s2 * (c1 - e * s1);
+    }
+    b[0] = b0;
+    b[1] = b1;
+}
+
 // The kinds of one dimension only: branches that end in stores to different
 // entries are merged into one store through a selected address, which keeps
 // the array out of registers.
@@ -298,26 +320,8 @@ __device__ inline void drift(const DevInst &I, const double *tf, const double2 *
         for (int a = 0; a < D; ++a) b[a] = I.coef[a];
         return;
     }
-    if constexpr (D == 2) {
-        const double2 t0 = trig[I.coord_off[0] + idx[0]];
-        const double2 t1 = trig[I.coord_off[1] + idx[1]];
-        double b0, b1;
-        if (I.coef_kind == 1) {
-            const double sa = t0.x, ca = t0.y, sy = t1.x, cy = t1.y;
-            const double Api = I.coef[0] * M_PI;
-            b0 = -(Api * sa * cy);
-            b1 = Api * ca * sy;
-        } else {
-            // rolls: Pe v with v_1 = -pi cos(pi y) (sin(n x) + e cos(n x)),
-            // v_2 = n sin(pi y) (cos(n x) - e sin(n x)), e = eps cos(omega t)
-            const double s1 = t0.x, c1 = t0.y, s2 = t1.x, c2 = t1.y;
-            const double e = tf[0];
-            b0 = -(I.coef[0] * M_PI * c2 * (s1 + e * c1));
-            b1 = I.coef[0] * I.coef[3] * s2 * (c1 - e * s1);
-        }
-        b[0] = b0;
-        b[1] = b1;
-    }
+    if constexpr (D == 2)
+        drift_2d(I, tf, trig[I.coord_off[0] + idx[0]], trig[I.coord_off[1] + idx[1]], b);
     if constexpr (D == 3) {
         const double2 tx = trig[I.coord_off[0] + idx[0]];
         const double2 ty = trig[I.coord_off[1] + idx[1]];

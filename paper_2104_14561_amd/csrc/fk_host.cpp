@@ -185,6 +185,11 @@ struct fk_plan {
     // forward step lists
     std::vector<int> fw_nodes, box_nodes;
     std::vector<fk::WorkItem> fw_work, fw_split_work, box_work;
+    // one-launch step of small 2D plans
+    std::vector<int> small_nodes;
+    std::vector<fk::WorkItem> small_work;
+    std::vector<fk::TileBox> small_tiles;
+    int small_lds = 0;
     int box_work_off[fk::kBoxClasses] = {0}, n_box_work[fk::kBoxClasses] = {0};
     bool use_box = false;
     bool wraps = false;   // some landing point can lie more than one period away
@@ -965,6 +970,62 @@ fk_status build_plan(fk_plan *p)
             p->n_box_work[c2] = (int)bw[c2].size();
             p->box_work.insert(p->box_work.end(), bw[c2].begin(), bw[c2].end());
         }
+        // small 2D plans: a step in one launch, when the records of a patch and
+        // its reach (at most 1024) are few enough to be computed by every
+        // workgroup that reads them (513 x 257: 140 records for 32 nodes; one launch
+        // of 7.4 us against 15.6 us in two)
+        if (p->d == 2 && p->step_kind == 2 && node_ok && affine && !p->wraps && !p->faces &&
+            p->opt.form == FK_FORM_FUSED && p->n_active > 0) {
+            int pd[3] = {1, 1, 1};
+            fk::small_patch(p->qs, &pd[0], &pd[1]);
+            int cells_max = 0;
+            for (int i = 0; i < p->n_inst && cells_max <= fk::kSmallCells; ++i) {
+                const fk_problem &pr = p->probs[i];
+                std::vector<int> list = inst_rest[i];
+                list.insert(list.end(), inst_sep[i].begin(), inst_sep[i].end());
+                patch_sort(list, pr, keys, pd);
+                const int f0 = (int)p->small_nodes.size(), n1 = pr.ax[1].n;
+                const size_t w0 = p->small_work.size();
+                p->small_nodes.insert(p->small_nodes.end(), list.begin(), list.end());
+                patch_work(p->small_work, i, keys, f0, pd[0] * pd[1]);
+                for (size_t t = w0; t < p->small_work.size(); ++t) {
+                    fk::WorkItem &it = p->small_work[t];
+                    int mn[2] = {1 << 30, 1 << 30}, mx[2] = {-1, -1};
+                    bool all = true;
+                    for (int u = 0; u < it.count; ++u) {
+                        const int j = p->small_nodes[it.first + u], ia[2] = {j / n1, j % n1};
+                        for (int a = 0; a < 2; ++a) {
+                            mn[a] = std::min(mn[a], ia[a]);
+                            mx[a] = std::max(mx[a], ia[a]);
+                        }
+                        all = all && inst_inner[i][j] != 0;
+                    }
+                    it.kind = all ? 1 : 0;
+                    fk::TileBox tb;
+                    std::memset(&tb, 0, sizeof(tb));
+                    for (int a = 0; a < 2; ++a) {
+                        int lo = mn[a] - inst_halo[i][a], hi = mx[a] + inst_halo[i][a];
+                        if (!pr.ax[a].periodic) {
+                            lo = std::max(lo, 0);
+                            hi = std::min(hi, pr.ax[a].n - 1);
+                        }
+                        tb.lo[a] = lo;
+                        tb.ext[a] = hi - lo + 1;
+                    }
+                    tb.ext[2] = 1;
+                    tb.pad = mn[0] / pd[0] * pd[0];
+                    tb.soff = mn[1] / pd[1] * pd[1];
+                    cells_max = (int)std::min<long long>(std::max<long long>(cells_max, (long long)tb.ext[0] * tb.ext[1]), 1 << 20);
+                    p->small_tiles.push_back(tb);
+                }
+            }
+            if (cells_max > fk::kSmallCells) {
+                p->small_work.clear();
+                p->small_tiles.clear();
+                p->small_nodes.clear();
+            }
+            p->small_lds = cells_max * 4 * (p->f32 ? 4 : 8);
+        }
         // adjoint LDS tiles: node box of each work item widened by the reach,
         // d + 1 field planes, innermost axis padded to a pitch that puts the
         // rows of a wave's patch (16 nodes in 2D, 8 in 3D) on distinct banks
@@ -1321,6 +1382,9 @@ fk_status build_plan(fk_plan *p)
     add_region(p, "abox_nodes", sizeof(int) * std::max<size_t>(p->adj.box_nodes.size(), 1));
     add_region(p, "abox_work", sizeof(fk::WorkItem) * std::max<size_t>(p->adj.box_work.size(), 1));
     add_region(p, "abox_tiles", sizeof(fk::TileBox) * std::max<size_t>(p->adj.box_tiles.size(), 1));
+    add_region(p, "small_nodes", sizeof(int) * std::max<size_t>(p->small_nodes.size(), 1));
+    add_region(p, "small_work", sizeof(fk::WorkItem) * std::max<size_t>(p->small_work.size(), 1));
+    add_region(p, "small_tiles", sizeof(fk::TileBox) * std::max<size_t>(p->small_tiles.size(), 1));
     add_region(p, "fw_nodes", sizeof(int) * std::max<size_t>(p->fw_nodes.size(), 1));
     add_region(p, "fw_work", sizeof(fk::WorkItem) * std::max<size_t>(p->fw_work.size(), 1));
     add_region(p, "fw_split_work", sizeof(fk::WorkItem) * std::max<size_t>(p->fw_split_work.size(), 1));
@@ -1430,6 +1494,11 @@ void fill_dev(fk_plan *p)
         D.adj.box_grid[c2] = grid_for(p->adj.n_box_work[c2]);
         D.adj.box_lds[c2] = p->adj.box_lds[c2];
     }
+    D.small_nodes = (const int *)p->at("small_nodes");
+    D.small_work = (const fk::WorkItem *)p->at("small_work");
+    D.small_tiles = (const fk::TileBox *)p->at("small_tiles");
+    D.n_small_work = (int)p->small_work.size();
+    D.small_lds = p->small_lds;
     D.fw_nodes = (const int *)p->at("fw_nodes");
     D.fw_work = (const fk::WorkItem *)p->at("fw_work");
     D.n_fw_work = (int)p->fw_work.size();
@@ -1501,9 +1570,13 @@ fk_status need_ws(const fk_plan *p)
             return fail(FK_ERR_HIP, "launch failed: %s", hipGetErrorString(e_));     \
     } while (0)
 
-// One step u_next -> u_out (u_out must hold 1 on exit nodes already).
+// One step u_next -> u_out, two fields (u_out must hold 1 on exit nodes already).
 fk_status enqueue_step(fk_plan *p, int n, const void *u_next, void *u_out, hipStream_t s)
 {
+    if (p->dev.n_small_work > 0) {
+        FK_LAUNCH(fk::launch_step_small2(p->dev, p->f32, n, u_next, u_out, s));
+        return FK_OK;
+    }
     void *packed = p->at("packed");
     FK_LAUNCH(fk::launch_slopes(p->dev, p->f32, n, u_next, packed, s));
     if (p->opt.form == FK_FORM_ELL) {
@@ -1995,6 +2068,9 @@ fk_status upload_tables(fk_plan *p, hipStream_t s)
         FK_TRY(up("cov_ptr", p->adj.cov_ptr.data(), sizeof(int) * p->adj.cov_ptr.size()));
         FK_TRY(up("cov_base", p->adj.cov_base.data(), sizeof(int) * p->adj.cov_base.size()));
     }
+    FK_TRY(up("small_nodes", p->small_nodes.data(), sizeof(int) * p->small_nodes.size()));
+    FK_TRY(up("small_work", p->small_work.data(), sizeof(fk::WorkItem) * p->small_work.size()));
+    FK_TRY(up("small_tiles", p->small_tiles.data(), sizeof(fk::TileBox) * p->small_tiles.size()));
     FK_TRY(up("fw_nodes", p->fw_nodes.data(), sizeof(int) * p->fw_nodes.size()));
     FK_TRY(up("fw_work", p->fw_work.data(), sizeof(fk::WorkItem) * p->fw_work.size()));
     FK_TRY(up("fw_split_work", p->fw_split_work.data(), sizeof(fk::WorkItem) * p->fw_split_work.size()));

@@ -16,6 +16,18 @@ constexpr int kBoxClasses = 5;    // separable-form footprint classes
 constexpr int kTileClasses = 3;   // classes of the per-point transposed step's tiles
 constexpr int kAdjLdsMax = 159 * 1024;   // dynamic LDS of a transposed step, of a CU's 160 KB
 
+// The one-launch step of small 2D plans: lanes per node, and the patch of 256 /
+// lanes nodes that a workgroup takes (rows x columns, at most kSmallPatch each).
+constexpr int small_lanes(int qs) { return qs <= 2 ? 2 : (qs <= 4 ? 4 : 8); }
+constexpr int kSmallPatch = 16;
+inline void small_patch(int qs, int *rows, int *cols)
+{
+    const int n = 256 / small_lanes(qs);   // 32, 64 or 128 nodes
+    *rows = n == 32 ? 4 : 8;
+    *cols = n == 128 ? 16 : 8;
+}
+constexpr int kSmallCells = 1024;   // records of a patch and its reach at most
+
 // Longest footprint (nodes per axis) of a class of the separable form, and the
 // threads of a workgroup that takes its 256-node work items.  Forward: 128 for
 // the wide classes in FP64 (3D: from 9 nodes on in FP32 too), so that their LDS
@@ -159,6 +171,13 @@ struct PlanDev {
     int block;                  // threads per workgroup
     int group;                  // lanes per active node in the step passes
     int step_kind;              // 0: thread per node, 1: lane group, 2: split node
+    // one-launch step of small 2D plans (n_small_work > 0), a tile of records
+    // per work item (its pad and soff hold the patch's first row and column)
+    const WorkItem *small_work;
+    const TileBox *small_tiles;
+    const int *small_nodes;
+    int n_small_work;
+    int small_lds;              // bytes of the largest tile
     int all_affine;             // every axis of every instance is affine
     int rel_ok;                 // all_affine, and no landing point more than one period away
     int hermite2;               // R2 interpolant: 2D twist field in the records' fourth entry,
@@ -221,6 +240,9 @@ hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void 
 hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s);
 hipError_t launch_step_fused(const PlanDev &P, bool f32, int n, const void *packed,
                              void *u_out, hipStream_t s);
+// The whole step u_in -> u_out of a small 2D plan (P.n_small_work > 0).
+hipError_t launch_step_small2(const PlanDev &P, bool f32, int n, const void *u_in, void *u_out,
+                              hipStream_t s);
 bool step_node_compiled(int d, int qs);
 // LDS bytes of a separable-assembly launch: the axis vectors of 64 rows
 // (d x 2 x lm columns) and a zero column, then the class's block table

@@ -333,6 +333,164 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
     }
 }
 
+// A whole backward step of a small 2D plan in one launch: a workgroup takes a
+// patch of 256 / GL nodes, builds the records (u, slopes) of the patch and its
+// reach in LDS from u, the (sin, cos) of its coordinates beside them, and then
+// works as k_step_pt2 (GL lanes per node, lane l the axis-1 GH node l), every
+// record read from LDS.  Slopes of a patch's reach are computed by each
+// workgroup that needs them, which costs less than the launch that would share
+// them as long as the reach is a few patches.
+// Bound: the chain of one workgroup (one item each) and the launch (4 us).
+// 513 x 257 with a disc (28 thousand active nodes, Q* = 8) in FP32: 7.4 us against
+// 5.1 + 10.5 us in two launches; 129 x 33 periodic in FP64 6.1 against 4.1 + 7.9 us.
+template <typename T, int QS, bool TW>
+__global__ void __launch_bounds__(kBlock) k_step_small2(
+    const PlanDev P, int n, const DevInst *__restrict__ insts, const WorkItem *__restrict__ work,
+    const TileBox *__restrict__ tiles, const int *__restrict__ nodes, const T *__restrict__ u_in,
+    T *__restrict__ u_out)
+{
+#pragma clang fp contract(off)
+    using R = typename RecT<T, 4>::type;
+    constexpr int GL = small_lanes(QS), NPB = kBlock / GL;
+    struct Row { T x0, x1, d0, d1; };
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    R *rec = reinterpret_cast<R *>(smem_raw);
+    __shared__ Row rows[NPB][GL];
+    __shared__ double rd2[NPB][GL];
+    __shared__ int roff[NPB][GL];
+    __shared__ double2 trig[2][kSmallPatch];
+    const WorkItem it = work[blockIdx.x];
+    const TileBox tb = tiles[blockIdx.x];
+    const DevInst &I = insts[it.inst];
+    const double *tf = time_factors(P, n, it.inst);
+    const T *ui = u_in + I.node_off;
+    const int e1 = tb.ext[1], cells = tb.ext[0] * e1, s0 = (int)I.stride[0];
+    const unsigned long long re = fast_recip(e1);
+    // the patch's coordinates on the last wave, the records on all
+    const int c0 = tb.pad, c1 = tb.soff;   // first row and column of the patch
+    const int tl = (int)threadIdx.x - (kBlock - 64);
+    if (tl >= 0 && I.coef_kind != 0) {
+        const int a = tl >= kSmallPatch ? 1 : 0, i = tl - a * kSmallPatch;
+        const int k = (a ? c1 : c0) + i;
+        if (a < 2 && i < kSmallPatch && tl < 2 * kSmallPatch && k < I.n[a]) {
+            const double arg = trig_arg(I, tf, a, P.coords[I.coord_off[a] + k]);
+            trig[a][i] = make_double2(sin(arg), cos(arg));
+        }
+    }
+    for (int e = threadIdx.x; e < cells; e += kBlock) {
+        const int r = fast_div(e, re), c = e - r * e1;
+        int idx[3] = {wrap_index(tb.lo[0] + r, I.n[0], I.periodic[0]),
+                      wrap_index(tb.lo[1] + c, I.n[1], I.periodic[1]), 0};
+        R o;
+        o.x = ui[idx[0] * s0 + idx[1]];
+        T g[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            int il, ic, ir;
+            T rl, rr;
+            slope_stencil<T>(I, P.coords, a, idx[a], il, ic, ir, rl, rr);
+            const int b = a == 0 ? idx[1] : idx[0] * s0, st = a == 0 ? s0 : 1;
+            g[a] = pchip<T>(ui[b + il * st], ui[b + ic * st], ui[b + ir * st], rl, rr);
+        }
+        o.y = g[0];
+        o.z = g[1];
+        o.w = T(0);
+        if constexpr (TW) o.w = twist_2d<T>(I, P.coords, ui, idx);
+        rec[e] = o;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x % GL, slot = threadIdx.x / GL;
+    const int q = lane < QS ? lane : QS - 1;   // idle lanes repeat the last one, unweighted
+    const double gq = P.gh_a[q];
+    const T wq = lane < QS ? weights1<T>(P)[q] : T(0);
+    const bool valid = slot < it.count;
+    const int node = nodes[it.first + (valid ? slot : 0)];
+    int idx[3];
+    split_node<2>(I, node, idx);
+    const int own = (idx[0] - tb.lo[0]) * e1 + (idx[1] - tb.lo[1]);
+    const T uref = rec[own].x;
+    double b[2];
+    if (I.coef_kind == 0) {
+        b[0] = I.coef[0];
+        b[1] = I.coef[1];
+    } else {
+        drift_2d(I, tf, trig[0][idx[0] - c0], trig[1][idx[1] - c1], b);
+    }
+    const bool interior = it.kind == 1;
+    const bool ball = I.region_kind == 1;
+    const double r2 = ball ? I.r2 : HUGE_VAL;
+    // one landing coordinate: cell (unwrapped, inside the tile), position,
+    // squared distance (infinite: exit)
+    auto axis = [&](int a, int &k, T &s, double &d2) {
+        const double t = fma_t(gq, I.S * I.inv_h[a], b[a] * P.dt * I.inv_h[a]);
+        int kk = idx[a] + (int)floor(t);
+        if (!I.periodic[a]) kk = min(max(kk, 0), I.n[a] - 2);
+        kk = min(max(kk, tb.lo[a]), tb.lo[a] + tb.ext[a] - 2);
+        s = (T)(t - (double)(kk - idx[a]));
+        k = kk - tb.lo[a];
+        d2 = 0.0;
+        if (!interior) {
+            const double x = (idx[a] == I.n[a] - 1) ? I.hi[a] : (double)idx[a] * I.step[a] + I.lo[a];
+            const double c = x + b[a] * P.dt;
+            const double z = c + I.S * gq;
+            const double dz = z - I.center[a];
+            d2 = ball ? dz * dz : 0.0;
+            if (!I.periodic[a] && (z <= I.lo[a] || z >= I.hi[a])) d2 = HUGE_VAL;
+        }
+    };
+    int k0, k1;
+    T s, v0, v1, f0, f1;
+    double d2;
+    axis(0, k0, s, d2);
+    unit_basis<T>(s, v0, v1, f0, f1);
+    const T wh = wq * (T)I.step[0];
+    rows[slot][lane] = {wq * v0, wq * v1, wh * f0, wh * f1};
+    rd2[slot][lane] = d2;
+    roff[slot][lane] = k0 * e1;
+    axis(1, k1, s, d2);
+    unit_basis<T>(s, v0, v1, f0, f1);
+    // lanes of a node belong to one wave: its LDS writes precede its reads
+    __builtin_amdgcn_wave_barrier();
+    T a0 = T(0), a1 = T(0), g0 = T(0), g1 = T(0), pex = T(0);
+#pragma unroll 4
+    for (int q0 = 0; q0 < QS; ++q0) {
+        Row rw = rows[slot][q0];
+        const int off = roff[slot][q0] + k1;
+        if (!interior && rd2[slot][q0] + d2 >= r2) {
+            pex += rw.x0 + rw.x1;
+            rw = {T(0), T(0), T(0), T(0)};
+        }
+        const R *p = rec + off;
+        const R p00 = p[0], p01 = p[1], p10 = p[e1], p11 = p[e1 + 1];
+        a0 = fma_t(rw.x0, p00.x - uref, a0);
+        a1 = fma_t(rw.x0, p01.x - uref, a1);
+        a0 = fma_t(rw.x1, p10.x - uref, a0);
+        a1 = fma_t(rw.x1, p11.x - uref, a1);
+        a0 = fma_t(rw.d0, p00.y, a0);
+        a1 = fma_t(rw.d0, p01.y, a1);
+        a0 = fma_t(rw.d1, p10.y, a0);
+        a1 = fma_t(rw.d1, p11.y, a1);
+        g0 = fma_t(rw.x0, p00.z, g0);
+        g1 = fma_t(rw.x0, p01.z, g1);
+        g0 = fma_t(rw.x1, p10.z, g0);
+        g1 = fma_t(rw.x1, p11.z, g1);
+        if constexpr (TW) {
+            g0 = fma_t(rw.d0, p00.w, g0);
+            g1 = fma_t(rw.d0, p01.w, g1);
+            g0 = fma_t(rw.d1, p10.w, g0);
+            g1 = fma_t(rw.d1, p11.w, g1);
+        }
+    }
+    T acc = wq * (v0 * a0 + v1 * a1 + (T)I.step[1] * (f0 * g0 + f1 * g1));
+    T emass = wq * pex;
+    acc = group_sum<GL>(acc);
+    emass = group_sum<GL>(emass);
+    if (!valid || lane != 0) return;
+    const T v = uref + acc + emass * (T(1) - uref);
+    flag_nonfinite(P.flags, v);
+    store_node<2, T>(I, idx, node, v, u_out);
+}
+
 // The separable step in three dimensions.  The axis-2 vectors are in registers, those of
 // axes 0 and 1 in two LDS columns; an (i, j) row of the footprint is L2
 // records against the axis-2 vectors.  Footprints up to 4 nodes (UN) unroll
