@@ -41,6 +41,7 @@ namespace fk {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kWave = 64;
 
 // ---------------------------------------------------------------------------
 // Packed node record (u, slopes): 2 entries for d = 1, 4 for d = 2, 3.

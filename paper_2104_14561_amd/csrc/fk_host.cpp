@@ -190,6 +190,11 @@ struct fk_plan {
     std::vector<fk::WorkItem> small_work;
     std::vector<fk::TileBox> small_tiles;
     int small_lds = 0;
+    bool pt_groups = false;   // 2D landing points by lane groups (k_step_pt2)
+    // 3D plans in entry form (faces, axes that are not affine; box region)
+    std::vector<int> ent_nodes;
+    std::vector<fk::WorkItem> ent_work;
+    bool retab = false, retab_step = false;   // runaway tables, refilled each step
     int box_work_off[fk::kBoxClasses] = {0}, n_box_work[fk::kBoxClasses] = {0};
     bool use_box = false;
     bool wraps = false;   // some landing point can lie more than one period away
@@ -951,8 +956,17 @@ fk_status build_plan(fk_plan *p)
             const int f1 = (int)p->fw_nodes.size();
             p->fw_nodes.insert(p->fw_nodes.end(), fw.begin(), fw.end());
             const size_t w0 = p->fw_work.size(), ws0 = p->fw_split_work.size();
-            build_work(p->fw_work, i, (int)fw.size(), kBlock, f1);
-            build_work(p->fw_split_work, i, (int)fw.size(), kBlock / gs, f1);
+            // the lane groups of the 2D point form take full workgroups across
+            // patches; the thread-per-node form gathers 2^d corners per point
+            // and stays within one (65^3, Q* = 4, FP64: 155 us a step against
+            // 190 across)
+            if (p->pt_groups) {
+                build_work(p->fw_work, i, (int)fw.size(), kBlock, f1);
+                build_work(p->fw_split_work, i, (int)fw.size(), kBlock / gs, f1);
+            } else {
+                patch_work(p->fw_work, i, keys, f1, kBlock);
+                patch_work(p->fw_split_work, i, keys, f1, kBlock / gs);
+            }
             // kind 1: no landing point of any node of the item can exit
             auto mark = [&](std::vector<fk::WorkItem> &v, size_t from) {
                 for (size_t t = from; t < v.size(); ++t) {
@@ -997,6 +1011,20 @@ fk_status build_plan(fk_plan *p)
                         for (int a = 0; a < 2; ++a) {
                             mn[a] = std::min(mn[a], ia[a]);
                             mx[a] = std::max(mx[a], ia[a]);
+        // 2D landing points: lane groups relative to the node, a thread per node
+        // from as many nodes on as keep the chip in threads by themselves.
+        // Measured per step at footprints of 18 and more nodes, groups against
+        // threads: Q* = 8 FP64 501^2 89 against 110 us, 705^2 164 against 155;
+        // FP32 705^2 79 against 82, 1025^2 162 against 158; Q* = 4 301^2 12 against
+        // 21 (FP32), 501^2 23 against 21 and 34 against 32 (FP64).
+        {
+            long long points = 0;
+            for (int i = 0; i < p->n_inst; ++i)
+                points += (long long)inst_rest[i].size() +
+                          (!p->use_box || inst_cls[i] < 0 ? (long long)inst_sep[i].size() : 0);
+            const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
+            p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && (p->step_kind != 0 || points < most);
+        }
                         }
                         all = all && inst_inner[i][j] != 0;
                     }
@@ -1654,6 +1682,7 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
     // alternate between the two work fields
     auto slot_of = [&](int n) -> void * {
         if (!store_ckpt || n == p->N || n % p->opt.ckpt_every != 0) return nullptr;
+    D.pt_groups = p->pt_groups ? 1 : 0;
         return (unsigned char *)p->at("ckpt") + (size_t)(n / p->opt.ckpt_every) * fb;
     };
     void *cur = ua;

@@ -185,6 +185,7 @@ struct PlanDev {
     void *packed2;              // 3D R2: (t01, t02, t12, t012) per node, or null
     int faces;                  // face kinds other than exit-1, or node-dependent diffusion
     // forward step work: nodes handled per landing point (fw) and separable
+    int pt_groups;              // 2D landing points by lane groups, a thread per node if not
     // nodes handled in box form, by box class
     const int *fw_nodes;
     const WorkItem *fw_work;

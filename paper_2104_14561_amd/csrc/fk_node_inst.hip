@@ -53,7 +53,7 @@ void step_node_launch(const PlanDev &P, int n, const void *packed, void *u_out, 
         if constexpr (D == 2) {
             // affine axes, no landing point further than one period away: the
             // per-point form relative to the node
-            if (P.rel_ok && !P.faces) {
+            if (P.pt_groups) {
                 if (P.hermite2)
                     k_step_pt2<T, QS, true><<<P.fw_split_grid, kBlock, 0, s>>>(
                         P, n, P.n_fw_split_work, P.inst, P.fw_split_work, P.fw_nodes, P.trig, (const T *)packed, (T *)u_out);
@@ -61,9 +61,11 @@ void step_node_launch(const PlanDev &P, int n, const void *packed, void *u_out, 
                     k_step_pt2<T, QS, false><<<P.fw_split_grid, kBlock, 0, s>>>(
                         P, n, P.n_fw_split_work, P.inst, P.fw_split_work, P.fw_nodes, P.trig, (const T *)packed, (T *)u_out);
             } else if (P.step_kind == 2) {
-                FK_NODE(GS, false, P.fw_split_grid, P.n_fw_split_work, P.fw_split_work);
+                if (P.all_affine) FK_NODE(GS, true, P.fw_split_grid, P.n_fw_split_work, P.fw_split_work);
+                else FK_NODE(GS, false, P.fw_split_grid, P.n_fw_split_work, P.fw_split_work);
             } else {
-                FK_NODE(1, false, P.fw_grid, P.n_fw_work, P.fw_work);
+                if (P.all_affine) FK_NODE(1, true, P.fw_grid, P.n_fw_work, P.fw_work);
+                else FK_NODE(1, false, P.fw_grid, P.n_fw_work, P.fw_work);
             }
         } else if (P.step_kind == 2) {
             if (P.all_affine) FK_NODE(GS, true, P.fw_split_grid, P.n_fw_split_work, P.fw_split_work);

@@ -113,7 +113,7 @@ __device__ inline void sep_vectors(const DevInst &I, int a, int idx, double bdt,
 // about as much VALU issue.  64-instance batch, per step: 0.91 million
 // separable nodes in FP32 73 us and 0.51 million in FP64 107 us over the
 // classes; a thread per node over the landing points took 182 us for the FP32
-// part with the 0.24 million other nodes (which now take 57 us, see
+// part with the 0.24 million other nodes (which now take 48 us, see
 // k_step_pt2), 223 us for the FP64 part (30 us now for its others).  From 16
 // nodes per axis on a footprint holds more records than the points read.
 template <typename T, int QS, int L, int BS, bool TW>
@@ -219,8 +219,11 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
 // with no weight (a branch per point would hold back the next point's reads).
 //
 // A lane holds one column's data instead of Q* (a thread per node takes 108 to
-// 156 VGPRs, three to four waves per SIMD).  The batch's non-separable nodes:
-// FP64 52 us a thread per node, 30 us now; FP32 54 and 57 us.
+// 156 VGPRs, three to four waves per SIMD).  Lanes next to each other take
+// nodes next to each other, the same GH node, so that their records share
+// lines (57 us with a node's lanes side by side in FP32, 48 so; 301^2, points
+// spread over 45 cells: 25 and 20 us).  The batch's non-separable nodes: FP64 52
+// us a thread per node, 30 us now; FP32 54 and 48 us.
 template <typename T, int QS, bool TW>
 __global__ void __launch_bounds__(kBlock) k_step_pt2(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
@@ -232,10 +235,12 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
     constexpr int GL = QS <= 2 ? 2 : (QS <= 4 ? 4 : 8);
     constexpr int NPB = kBlock / GL;
     struct Row { T x0, x1, d0, d1; };
-    __shared__ Row rows[NPB][GL];
-    __shared__ double rd2[NPB][GL];
-    __shared__ int roff[NPB][GL];
-    const int lane = threadIdx.x % GL, slot = threadIdx.x / GL;
+    constexpr int NW = kWave / GL;
+    __shared__ Row rows[GL][NPB];
+    __shared__ double rd2[GL][NPB];
+    __shared__ int roff[GL][NPB];
+    const int wl = threadIdx.x % kWave;
+    const int lane = wl / NW, slot = threadIdx.x / kWave * NW + wl % NW;
     const int q = lane < QS ? lane : QS - 1;   // idle lanes repeat the last one, unweighted
     const double gq = P.gh_a[q];
     const T wq = lane < QS ? weights1<T>(P)[q] : T(0);
@@ -279,9 +284,9 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
         axis(0, k0, s, d2);
         unit_basis<T>(s, v0, v1, e0, e1);
         const T wh = wq * (T)I.step[0];
-        rows[slot][lane] = {wq * v0, wq * v1, wh * e0, wh * e1};
-        rd2[slot][lane] = d2;
-        roff[slot][lane] = k0 * s0;
+        rows[lane][slot] = {wq * v0, wq * v1, wh * e0, wh * e1};
+        rd2[lane][slot] = d2;
+        roff[lane][slot] = k0 * s0;
         axis(1, k1, s, d2);
         unit_basis<T>(s, v0, v1, e0, e1);
         // lanes of a node belong to one wave: its LDS writes precede its reads
@@ -290,10 +295,10 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
         T c0 = T(0), c1 = T(0), g0 = T(0), g1 = T(0), pex = T(0);
 #pragma unroll 4
         for (int q0 = 0; q0 < QS; ++q0) {
-            Row rw = rows[slot][q0];
-            int off = roff[slot][q0] + k1;
+            Row rw = rows[q0][slot];
+            int off = roff[q0][slot] + k1;
             if (!interior) {
-                const bool ex = rd2[slot][q0] + d2 >= r2;
+                const bool ex = rd2[q0][slot] + d2 >= r2;
                 if (ex) {
                     pex += rw.x0 + rw.x1;
                     rw = {T(0), T(0), T(0), T(0)};
@@ -324,8 +329,11 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
         __builtin_amdgcn_wave_barrier();
         T acc = wq * (v0 * c0 + v1 * c1 + (T)I.step[1] * (e0 * g0 + e1 * g1));
         T emass = wq * pex;
-        acc = group_sum<GL>(acc);
-        emass = group_sum<GL>(emass);
+#pragma unroll
+        for (int off = kWave / 2; off >= NW; off >>= 1) {
+            acc += __shfl_xor(acc, off, kWave);
+            emass += __shfl_xor(emass, off, kWave);
+        }
         if (!valid || lane != 0) continue;
         const T v = uref + acc + emass * (T(1) - uref);
         flag_nonfinite(P.flags, v);
