@@ -2,7 +2,8 @@
 
 The kernels are split over several translation units: fk_slopes.hip (slope
 pass), fk_line.hip (several steps of 1D plans in one launch),
-fk_small.hip (the one-launch step of small 2D plans), fk_launch.hip (lane-group kernels, ELL form, exports) and one instance of
+fk_small.hip (the one-launch step of small 2D plans), fk_ent.hip (3D plans
+with faces or axes of any kind), fk_launch.hip (lane-group kernels, ELL form, exports) and one instance of
 fk_node_inst.hip per (precision, dimension, forward|adjoint), each holding the
 thread-per-node and separable-box specialisations over Q*.  They compile in
 parallel."""
@@ -26,7 +27,7 @@ def units():
     """(source, object name, extra defines) of every translation unit."""
     out = [("fk_host.cpp", "fk_host", []), ("fk_launch.hip", "fk_launch", []),
            ("fk_slopes.hip", "fk_slopes", []), ("fk_line.hip", "fk_line", []),
-           ("fk_small.hip", "fk_small", [])]
+           ("fk_small.hip", "fk_small", []), ("fk_ent.hip", "fk_ent", [])]
     for adj in (0, 1):
         for f32 in (1, 0):
             for d in (2, 3, 1):

@@ -108,8 +108,8 @@ __device__ inline double coord(const DevInst &I, const double *coords, int a, in
 // Cell of z: max{k : x_k <= z}, clamped to [0, n-2].  On a uniform axis the
 // arithmetic guess floor((z - lo) / h) is within one cell of the answer (the
 // spacing deviates from h by far less than a cell), so one conditional step up
-// and one down against the node coordinates give it exactly; other axes use
-// binary search over the stored coordinates.
+// and one down against the node coordinates give it exactly; other axes look
+// the cell up by bucket, or bisect the stored coordinates.
 __device__ inline int locate(const DevInst &I, const double *coords, int a, double z)
 {
     const int n = I.n[a];
@@ -121,6 +121,16 @@ __device__ inline int locate(const DevInst &I, const double *coords, int a, doub
         if (k > 0 && coord(I, coords, a, k) > z) --k;
     } else {
         const double *x = coords + I.coord_off[a];
+        if (I.lut_n[a] > 0) {
+            // the largest node at or below the bucket's start, then at most a
+            // node or two on (buckets as wide as the smallest spacing)
+            const double f = floor((z - x[0]) * I.lut_inv[a]);
+            const int b = (f >= 0.0) ? ((f <= (double)(I.lut_n[a] - 1)) ? (int)f : I.lut_n[a] - 1) : 0;
+            k = (int)coords[I.lut_off[a] + b];
+            while (k < n - 2 && x[k + 1] <= z) ++k;
+            while (k > 0 && x[k] > z) --k;
+            return k;
+        }
         int l = 0, h = n - 1;
         if (z >= x[n - 1]) {
             l = n - 2;
@@ -466,6 +476,29 @@ __device__ inline void runaway_centre(const DevInst &I, const double *coords, co
     S[0] = sqrt(2.0 * CA) * sq;
     S[1] = sqrt(2.0 * CB) / pm * sqrt(om > 0.0 ? om : 0.0) * sq;
     S[2] = sqrt(2.0 * Dr) * sq;
+}
+
+// The same from per-coordinate tables (k_runaway_tables): every function of
+// the model is a product or sum of functions of one coordinate.
+__device__ inline void runaway_centre_tab(const DevInst &I, const double *coords, const double *tab,
+                                          const int *idx, double dt, double *c, double *S)
+{
+    const double *tp = tab + (I.coord_off[0] + idx[0]) * kReTab;
+    const double *tx = tab + (I.coord_off[1] + idx[1]) * kReTab;
+    const double *tr = tab + (I.coord_off[2] + idx[2]) * kReTab;
+    const double pm = coord(I, coords, 0, idx[0]);
+    const double xi = coord(I, coords, 1, idx[1]);
+    const double r = coord(I, coords, 2, idx[2]);
+    const double om = tx[0];
+    const double b0 = tx[2] - tp[0] * om + tp[1];
+    const double b1 = om * (tp[2] - xi * tp[3]) - xi * tp[4];
+    const double b2 = tr[0] + tr[1] * tp[7];
+    c[0] = pm + b0 * dt;
+    c[1] = xi + b1 * dt;
+    c[2] = r + b2 * dt;
+    S[0] = tp[5];
+    S[1] = tp[6] * tx[1];
+    S[2] = tr[2] * sqrt(tp[7]);
 }
 
 // Centre and per-axis scales of any model (S_a = the instance's S unless the

@@ -448,6 +448,57 @@ int footprint(double reach, double hmin)
     return (int)std::floor(std::min(2.0 * reach / hmin, 1e6)) + 3;
 }
 
+// Records per node of the 3D entry form as a share of the corners of the points
+// that stay inside (8 Q*^3 without exits): the mean over up to 500 of an instance's nodes of the product of the
+// distinct nodes per axis that its landing cells touch (runs of equal or
+// adjacent cells, as the kernel joins them), at the first step.  Models of
+// constant diffusion are taken at a shift of 0.37 cells.
+double ent_share(const fk_problem &pr, const std::vector<double> &gh, const std::vector<int> &nodes)
+{
+    if (nodes.empty()) return 0.0;
+    double tf[4], sum = 0.0, corners = 0.0;
+    runaway_time_factors(pr, pr.t0, tf);
+    const size_t step = (nodes.size() + 499) / 500;
+    for (size_t e = 0; e < nodes.size(); e += step) {
+        int r = nodes[e], idx[3];
+        double x[3], b[3], sg[3], prod = 1.0, pts = 8.0;
+        for (int a = 2; a >= 0; --a) {
+            idx[a] = r % pr.ax[a].n;
+            r /= pr.ax[a].n;
+            x[a] = pr.ax[a].nodes[idx[a]];
+            const int k = std::min(idx[a], pr.ax[a].n - 2);
+            b[a] = 0.37 * (pr.ax[a].nodes[k + 1] - pr.ax[a].nodes[k]) / pr.dt;
+            sg[a] = std::sqrt(2.0 * pr.D);
+        }
+        if (pr.coef_kind == FK_COEF_RUNAWAY3D) runaway_coefficients(pr, tf, x, b, sg);
+        for (int a = 0; a < 3; ++a) {
+            const double *xs = pr.ax[a].nodes;
+            const int na = pr.ax[a].n;
+            int last = -2, cnt = 0, in = 0;
+            for (double g : gh) {
+                double z = x[a] + b[a] * pr.dt + sg[a] * std::sqrt(2.0 * pr.dt) * g;
+                if (pr.ax[a].periodic) {
+                    const double per = xs[na - 1] - xs[0];
+                    z = z >= xs[na - 1] ? z - per : (z < xs[0] ? z + per : z);
+                } else {
+                    if (pr.face[a][0] == FK_FACE_REFLECT && z < xs[0]) z = 2.0 * xs[0] - z;
+                    if (pr.face[a][1] == FK_FACE_REFLECT && z > xs[na - 1]) z = 2.0 * xs[na - 1] - z;
+                    if (!(z > xs[0] && z < xs[na - 1])) continue;
+                }
+                const int k = (int)(std::upper_bound(xs + 1, xs + na - 1, z) - xs) - 1;
+                cnt += k == last ? 0 : (k == last + 1 ? 1 : 2);
+                last = k;
+                ++in;
+            }
+            prod *= cnt;
+            pts *= in;
+        }
+        sum += prod;
+        corners += pts;
+    }
+    return corners > 0.0 ? sum / corners : 0.0;
+}
+
 void add_region(fk_plan *p, const char *name, size_t bytes)
 {
     Region r;
@@ -857,6 +908,26 @@ fk_status build_plan(fk_plan *p)
         }
     }
     p->node_off[p->n_inst] = p->n_nodes;
+    // bucket tables of the axes that are not uniform, behind the coordinates:
+    // per bucket of the smallest spacing the largest node at or below its start
+    for (int i = 0; i < p->n_inst; ++i)
+        for (int a = 0; a < p->d; ++a) {
+            fk::DevInst &I = p->inst[i];
+            if (I.uniform[a]) continue;
+            const fk_axis &ax = p->probs[i].ax[a];
+            double hmin = 1e300;
+            for (int k = 1; k < ax.n; ++k) hmin = std::min(hmin, ax.nodes[k] - ax.nodes[k - 1]);
+            const double nb = std::ceil((ax.nodes[ax.n - 1] - ax.nodes[0]) / hmin) + 1.0;
+            if (!(nb <= 65536.0)) continue;
+            I.lut_n[a] = (int)nb;
+            I.lut_inv[a] = 1.0 / hmin;
+            I.lut_off[a] = (long long)p->coords.size();
+            int k = 0;
+            for (int b = 0; b < I.lut_n[a]; ++b) {
+                while (k < ax.n - 2 && ax.nodes[k + 1] <= ax.nodes[0] + b * hmin) ++k;
+                p->coords.push_back((double)k);
+            }
+        }
     // forward step layout: thread per node for large plans (with the box form
     // for separable nodes), Q* lanes per node for small ones
     {
@@ -931,6 +1002,20 @@ fk_status build_plan(fk_plan *p)
             }
         };
         std::vector<long long> keys;
+        // 2D landing points: lane groups relative to the node, a thread per node
+        // from as many nodes on as keep the chip in threads by themselves.
+        // Measured per step at footprints of 18 and more nodes, groups against
+        // threads: Q* = 8 FP64 501^2 89 against 110 us, 705^2 164 against 155;
+        // FP32 705^2 79 against 82, 1025^2 162 against 158; Q* = 4 301^2 12 against
+        // 21 (FP32), 501^2 23 against 21 and 34 against 32 (FP64).
+        {
+            long long points = 0;
+            for (int i = 0; i < p->n_inst; ++i)
+                points += (long long)inst_rest[i].size() +
+                          (!p->use_box || inst_cls[i] < 0 ? (long long)inst_sep[i].size() : 0);
+            const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
+            p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && (p->step_kind != 0 || points < most);
+        }
         for (int i = 0; i < p->n_inst; ++i) {
             const fk_problem &pr = p->probs[i];
             std::vector<int> fw = inst_rest[i];
@@ -984,6 +1069,45 @@ fk_status build_plan(fk_plan *p)
             p->n_box_work[c2] = (int)bw[c2].size();
             p->box_work.insert(p->box_work.end(), bw[c2].begin(), bw[c2].end());
         }
+        // 3D plans with faces or axes that are not affine, box region: the
+        // separable step in entry form, a thread per node, where its records
+        // are few against the points' own corners.  Measured per step against
+        // the point form: 49 x 41 x 128, Q* = 4, FP32 43 us against 126 (Q* = 6:
+        // 94 against 359); 65^3 with nothing shared 85 against 120 in FP32,
+        // 203 against 204 or 168 in FP64 (0.5: 211 against 179 past it); 33^3, shares 0.2 and 1: 30 against 45
+        // and 54 against 44; 17^3: 20 against 21 and 46 against 25, too few
+        // nodes to hide the reads of one thread.
+        bool short_axes = true;   // entries hold 16-bit node indices
+        for (const fk::DevInst &I : p->inst)
+            for (int a = 0; a < p->d; ++a) short_axes = short_axes && I.n[a] <= 65536;
+        bool ent = p->d == 3 && p->step_kind != 1 && node_ok && (p->faces || !affine) && !p->wraps &&
+                   p->opt.form == FK_FORM_FUSED && p->opt.hermite == FK_HERMITE_R1 &&
+                   p->probs[0].region_kind == FK_REGION_BOX && short_axes;
+        if (ent) {
+            double share = 0.0;   // weighted by nodes
+            for (int i = 0; i < p->n_inst; ++i) {
+                std::vector<int> list = inst_rest[i];
+                list.insert(list.end(), inst_sep[i].begin(), inst_sep[i].end());
+                share += ent_share(p->probs[i], p->gh_a, list) * (double)list.size();
+            }
+            share /= (double)std::max<long long>(p->n_active, 1);
+            ent = share <= (large ? (p->f32 ? 1.0 : 0.5) : (p->n_active >= 16384 ? 0.5 : 0.2));
+        }
+        if (ent) {
+            for (int i = 0; i < p->n_inst; ++i) {
+                std::vector<int> list = inst_rest[i];
+                list.insert(list.end(), inst_sep[i].begin(), inst_sep[i].end());
+                std::sort(list.begin(), list.end());   // along the last axis
+                const int f0 = (int)p->ent_nodes.size();
+                p->ent_nodes.insert(p->ent_nodes.end(), list.begin(), list.end());
+                build_work(p->ent_work, i, (int)list.size(), kBlock, f0);
+            }
+            for (const fk_problem &pr : p->probs)
+                if (pr.coef_kind == FK_COEF_RUNAWAY3D) {
+                    p->retab = true;
+                    p->retab_step = p->retab_step || pr.coef[11] > 0.0;
+                }
+        }
         // small 2D plans: a step in one launch, when the records of a patch and
         // its reach (at most 1024) are few enough to be computed by every
         // workgroup that reads them (513 x 257: 140 records for 32 nodes; one launch
@@ -1011,20 +1135,6 @@ fk_status build_plan(fk_plan *p)
                         for (int a = 0; a < 2; ++a) {
                             mn[a] = std::min(mn[a], ia[a]);
                             mx[a] = std::max(mx[a], ia[a]);
-        // 2D landing points: lane groups relative to the node, a thread per node
-        // from as many nodes on as keep the chip in threads by themselves.
-        // Measured per step at footprints of 18 and more nodes, groups against
-        // threads: Q* = 8 FP64 501^2 89 against 110 us, 705^2 164 against 155;
-        // FP32 705^2 79 against 82, 1025^2 162 against 158; Q* = 4 301^2 12 against
-        // 21 (FP32), 501^2 23 against 21 and 34 against 32 (FP64).
-        {
-            long long points = 0;
-            for (int i = 0; i < p->n_inst; ++i)
-                points += (long long)inst_rest[i].size() +
-                          (!p->use_box || inst_cls[i] < 0 ? (long long)inst_sep[i].size() : 0);
-            const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
-            p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && (p->step_kind != 0 || points < most);
-        }
                         }
                         all = all && inst_inner[i][j] != 0;
                     }
@@ -1410,6 +1520,9 @@ fk_status build_plan(fk_plan *p)
     add_region(p, "abox_nodes", sizeof(int) * std::max<size_t>(p->adj.box_nodes.size(), 1));
     add_region(p, "abox_work", sizeof(fk::WorkItem) * std::max<size_t>(p->adj.box_work.size(), 1));
     add_region(p, "abox_tiles", sizeof(fk::TileBox) * std::max<size_t>(p->adj.box_tiles.size(), 1));
+    add_region(p, "ent_nodes", sizeof(int) * std::max<size_t>(p->ent_nodes.size(), 1));
+    add_region(p, "ent_work", sizeof(fk::WorkItem) * std::max<size_t>(p->ent_work.size(), 1));
+    add_region(p, "retab", p->retab ? sizeof(double) * fk::kReTab * p->coords.size() : 0);
     add_region(p, "small_nodes", sizeof(int) * std::max<size_t>(p->small_nodes.size(), 1));
     add_region(p, "small_work", sizeof(fk::WorkItem) * std::max<size_t>(p->small_work.size(), 1));
     add_region(p, "small_tiles", sizeof(fk::TileBox) * std::max<size_t>(p->small_tiles.size(), 1));
@@ -1522,6 +1635,12 @@ void fill_dev(fk_plan *p)
         D.adj.box_grid[c2] = grid_for(p->adj.n_box_work[c2]);
         D.adj.box_lds[c2] = p->adj.box_lds[c2];
     }
+    D.ent_nodes = (const int *)p->at("ent_nodes");
+    D.ent_work = (const fk::WorkItem *)p->at("ent_work");
+    D.n_ent_work = (int)p->ent_work.size();
+    D.ent_grid = grid_for(p->ent_work.size());
+    D.retab = p->retab ? (double *)p->at("retab") : nullptr;
+    D.retab_step = p->retab_step ? 1 : 0;
     D.small_nodes = (const int *)p->at("small_nodes");
     D.small_work = (const fk::WorkItem *)p->at("small_work");
     D.small_tiles = (const fk::TileBox *)p->at("small_tiles");
@@ -1563,6 +1682,7 @@ void fill_dev(fk_plan *p)
     for (const fk::DevInst &I : p->inst)
         for (int a = 0; a < p->d; ++a)
             if (!I.affine[a]) D.all_affine = 0;
+    D.pt_groups = p->pt_groups ? 1 : 0;
     D.rel_ok = D.all_affine && !p->wraps ? 1 : 0;
     D.step_kind = p->step_kind;
     D.slope_grid = grid_for(p->slope_work.size());
@@ -1682,7 +1802,6 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
     // alternate between the two work fields
     auto slot_of = [&](int n) -> void * {
         if (!store_ckpt || n == p->N || n % p->opt.ckpt_every != 0) return nullptr;
-    D.pt_groups = p->pt_groups ? 1 : 0;
         return (unsigned char *)p->at("ckpt") + (size_t)(n / p->opt.ckpt_every) * fb;
     };
     void *cur = ua;
@@ -2097,6 +2216,8 @@ fk_status upload_tables(fk_plan *p, hipStream_t s)
         FK_TRY(up("cov_ptr", p->adj.cov_ptr.data(), sizeof(int) * p->adj.cov_ptr.size()));
         FK_TRY(up("cov_base", p->adj.cov_base.data(), sizeof(int) * p->adj.cov_base.size()));
     }
+    FK_TRY(up("ent_nodes", p->ent_nodes.data(), sizeof(int) * p->ent_nodes.size()));
+    FK_TRY(up("ent_work", p->ent_work.data(), sizeof(fk::WorkItem) * p->ent_work.size()));
     FK_TRY(up("small_nodes", p->small_nodes.data(), sizeof(int) * p->small_nodes.size()));
     FK_TRY(up("small_work", p->small_work.data(), sizeof(fk::WorkItem) * p->small_work.size()));
     FK_TRY(up("small_tiles", p->small_tiles.data(), sizeof(fk::TileBox) * p->small_tiles.size()));
@@ -2105,6 +2226,8 @@ fk_status upload_tables(fk_plan *p, hipStream_t s)
     FK_TRY(up("fw_split_work", p->fw_split_work.data(), sizeof(fk::WorkItem) * p->fw_split_work.size()));
     FK_TRY(up("box_nodes", p->box_nodes.data(), sizeof(int) * p->box_nodes.size()));
     FK_TRY(up("box_work", p->box_work.data(), sizeof(fk::WorkItem) * p->box_work.size()));
+    // tables that do not depend on the step are filled here, once
+    if (p->retab && !p->retab_step) FK_LAUNCH(fk::launch_runaway_tables(p->dev, 0, s));
     FK_LAUNCH(fk::launch_clear_flags(p->dev, s));
     return FK_OK;
 }

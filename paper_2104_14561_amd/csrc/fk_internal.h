@@ -86,6 +86,12 @@ struct DevInst {
     int blo[kMaxDim];              // reachable box (the nodes a step's gathers can touch):
     int blen[kMaxDim];             // first node and length per axis (0 without active nodes)
     int sep_l[kMaxDim];            // footprint nodes per axis of one node's landing cells
+    // axes that are not uniform: cell lookup by buckets of the smallest spacing,
+    // lut_n entries of the coordinate array from lut_off (0 entries: bisection)
+    long long lut_off[kMaxDim];
+    double lut_inv[kMaxDim];
+    int lut_n[kMaxDim];
+    int pad1;
 };
 
 // A contiguous chunk of one instance's nodes (slope pass) or active nodes
@@ -179,13 +185,20 @@ struct PlanDev {
     int n_small_work;
     int small_lds;              // bytes of the largest tile
     int all_affine;             // every axis of every instance is affine
+    int pt_groups;              // 2D landing points by lane groups, a thread per node if not
     int rel_ok;                 // all_affine, and no landing point more than one period away
     int hermite2;               // R2 interpolant: 2D twist field in the records' fourth entry,
                                 // 3D twist fields in a second record per node (packed2)
     void *packed2;              // 3D R2: (t01, t02, t12, t012) per node, or null
     int faces;                  // face kinds other than exit-1, or node-dependent diffusion
+    double *retab;              // runaway model: kReTab values per coordinate, or null
+    int retab_step;             // its time factors depend on the step
+    // 3D plans with faces or axes of any kind (box region): nodes in entry form
+    const int *ent_nodes;
+    const WorkItem *ent_work;
+    int n_ent_work;
+    int ent_grid;
     // forward step work: nodes handled per landing point (fw) and separable
-    int pt_groups;              // 2D landing points by lane groups, a thread per node if not
     // nodes handled in box form, by box class
     const int *fw_nodes;
     const WorkItem *fw_work;
@@ -239,8 +252,14 @@ hipError_t launch_init_field(const PlanDev &P, bool f32, void *u, hipStream_t s)
 hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void *packed,
                          hipStream_t s);
 hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s);
+constexpr int kReTab = 8;   // runaway model: tabulated values per coordinate
+// the runaway model's per-coordinate tables at step n (P.retab)
+hipError_t launch_runaway_tables(const PlanDev &P, int n, hipStream_t s);
 hipError_t launch_step_fused(const PlanDev &P, bool f32, int n, const void *packed,
                              void *u_out, hipStream_t s);
+// The step of 3D plans in entry form (P.n_ent_work > 0).
+hipError_t launch_step_ent3(const PlanDev &P, bool f32, int n, const void *packed, void *u_out,
+                            hipStream_t s);
 // The whole step u_in -> u_out of a small 2D plan (P.n_small_work > 0).
 hipError_t launch_step_small2(const PlanDev &P, bool f32, int n, const void *u_in, void *u_out,
                               hipStream_t s);

@@ -97,6 +97,7 @@ bool box_compiled(int d, int qs)
 hipError_t launch_step_fused(const PlanDev &P, bool f32, int n, const void *packed, void *u_out,
                              hipStream_t s)
 {
+    if (P.n_ent_work > 0) return launch_step_ent3(P, f32, n, packed, u_out, s);
     if (P.step_kind != 1) {
         bool ok = false;
         switch (P.d) {

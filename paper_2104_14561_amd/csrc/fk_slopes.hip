@@ -117,6 +117,10 @@ hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void 
                          hipStream_t s)
 {
     if (P.n_slope_work == 0) return hipSuccess;
+    if (P.retab && P.retab_step) {
+        const hipError_t e = launch_runaway_tables(P, n, s);
+        if (e != hipSuccess) return e;
+    }
 #define FK_SLOPES(TW_)                                                                          \
     FK_DISPATCH_D(P.d,                                                                          \
         if (f32) k_slopes<float, D, TW_><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const float *)u, (float *)packed); \
@@ -132,6 +136,10 @@ hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void 
 
 hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s)
 {
+    if (P.retab && P.retab_step) {
+        const hipError_t e = launch_runaway_tables(P, n, s);
+        if (e != hipSuccess) return e;
+    }
     if (P.n_table_work == 0) return hipSuccess;
     const int g = P.n_table_work >= 8 ? (P.n_table_work + 7) / 8 * 8 : P.n_table_work;
     FK_DISPATCH_D(P.d,
