@@ -2118,7 +2118,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_tiles(int n_cov, const int *_
                                                          const int *__restrict__ cov_ptr,
                                                          const int *__restrict__ cov_base,
                                                          const T *__restrict__ stage,
-                                                         T *__restrict__ mu)
+                                                         int fresh, T *__restrict__ mu)
 {
     constexpr int NF = D + 1, PS = RecStride<D>::value;
     const int stride = gridDim.x * blockDim.x;
@@ -2132,6 +2132,19 @@ __global__ void __launch_bounds__(kBlock) k_gather_tiles(int n_cov, const int *_
             const T *sp = stage + cov_base[k];
 #pragma unroll
             for (int f = 0; f < NF; ++f) acc[f] += sp[f];
+        }
+        if (fresh) {
+            // every tile is here: the sums are mu
+            using R = typename RecT<T, PS>::type;
+            R r;
+            r.x = acc[0];
+            r.y = acc[1];
+            if constexpr (PS == 4) {
+                r.z = acc[2];
+                r.w = NF > 3 ? acc[NF - 1] : T(0);
+            }
+            reinterpret_cast<R *>(mu)[j] = r;
+            continue;
         }
 #pragma unroll
         for (int f = 0; f < NF; ++f)
@@ -2344,96 +2357,6 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
         tile.template flush<PS>(I, mu, (T *)P.adj.stage);
         reduce_theta(red, gth, grad, it.inst);
         __syncthreads();
-    }
-}
-
-// lam^{n+1} += J_F(u)^T mu_g (scatter over each node's slope stencil);
-// lam_next must hold mu_u on entry.
-template <typename T, int D>
-__global__ void __launch_bounds__(kBlock) k_adjoint_slopes_T(PlanDev P, const T *__restrict__ u,
-                                                             T *__restrict__ mu,
-                                                             T *__restrict__ lam_next,
-                                                             const WorkItem *__restrict__ items,
-                                                             int first, int n_items)
-{
-    constexpr int PS = RecStride<D>::value;
-    const WorkRange wr = work_range(first, n_items);
-    for (int w = wr.begin; w < wr.end; w += wr.step) {
-        const WorkItem it = items[w];
-        if ((int)threadIdx.x >= it.count || it.kind != 0) continue;
-        const DevInst &I = P.inst[it.inst];
-        const int node = it.first + threadIdx.x;
-        int idx[3];
-        split_node<D>(I, node, idx);
-        const T *ui = u + I.node_off;
-        T *li = lam_next + I.node_off;
-        for (int a = 0; a < D; ++a) {
-            T *mp = &mu[(I.node_off + node) * PS + 1 + a];
-            const T m = *mp;
-            if (m == T(0)) continue;
-            *mp = T(0);   // mu is clear again for the next step
-            const int na = I.n[a];
-            const double *x = P.coords + I.coord_off[a];
-            const int i = idx[a];
-            int il, ic, ir;
-            double hl, hr;
-            if (I.periodic[a]) {
-                ic = (i == na - 1) ? 0 : i;
-                il = (ic == 0) ? na - 2 : ic - 1;
-                ir = ic + 1;
-                hl = (ic == 0) ? x[na - 1] - x[na - 2] : x[ic] - x[ic - 1];
-                hr = x[ic + 1] - x[ic];
-            } else if (i == 0) {
-                il = 0; ic = 1; ir = 2;
-                hl = x[1] - x[0]; hr = x[2] - x[1];
-            } else if (i == na - 1) {
-                il = na - 3; ic = na - 2; ir = na - 1;
-                hl = x[na - 2] - x[na - 3]; hr = x[na - 1] - x[na - 2];
-            } else {
-                il = i - 1; ic = i; ir = i + 1;
-                hl = x[i] - x[i - 1]; hr = x[i + 1] - x[i];
-            }
-            const long long base = node - (long long)i * I.stride[a];
-            const long long nl = base + (long long)il * I.stride[a];
-            const long long nc = base + (long long)ic * I.stride[a];
-            const long long nr = base + (long long)ir * I.stride[a];
-            // derivative 0 where a divided difference vanishes, including
-            // differences that are rounding noise of a flat stretch (below
-            // 2^-30 of the values; in FP32 that is exact equality)
-            const T tau = T(0x1p-30);
-            const T vl = ui[nl], vc = ui[nc], vr = ui[nr];
-            if (fabs(vc - vl) <= tau * (fabs(vc) + fabs(vl)) ||
-                fabs(vr - vc) <= tau * (fabs(vr) + fabs(vc)))
-                continue;
-            const T dl = (vc - vl) / (T)hl;
-            const T dr = (vr - vc) / (T)hr;
-            if (!(dl * dr > T(0))) continue;
-            const T den = (dl + dr) * (dl + dr);
-            const T gdl = T(2) * dr * dr / den;
-            const T gdr = T(2) * dl * dl / den;
-            atomicAdd(&li[nl], m * (-gdl / (T)hl));
-            atomicAdd(&li[nc], m * (gdl / (T)hl - gdr / (T)hr));
-            atomicAdd(&li[nr], m * (gdr / (T)hr));
-        }
-    }
-}
-
-// lam <- mu_u (field 0 of the records) over the nodes of a work list (node
-// runs), clearing mu_u for the next step.
-template <typename T, int D>
-__global__ void __launch_bounds__(kBlock) k_mu_value(PlanDev P, T *__restrict__ mu,
-                                                     T *__restrict__ lam,
-                                                     const WorkItem *__restrict__ items,
-                                                     int first, int n_items)
-{
-    constexpr int PS = RecStride<D>::value;
-    const WorkRange wr = work_range(first, n_items);
-    for (int w = wr.begin; w < wr.end; w += wr.step) {
-        const WorkItem it = items[w];
-        if ((int)threadIdx.x >= it.count || it.kind != 0) continue;
-        const long long g = P.inst[it.inst].node_off + it.first + threadIdx.x;
-        lam[g] = mu[g * PS];
-        mu[g * PS] = T(0);
     }
 }
 

@@ -159,7 +159,7 @@ struct fk_plan {
     std::vector<double> gh_a, gh_w, gh_w1;
     std::vector<float> gh_wf, gh_w1f;
     std::vector<double> tfac;
-    std::vector<fk::WorkItem> slope_work, run_work, node_work, act_work, row_work, split_work;
+    std::vector<fk::WorkItem> slope_work, node_work, act_work, row_work, split_work;
     std::vector<fk::WorkItem> ell_work;   // non-separable ELL rows by width class
     std::vector<fk::WorkItem> ell_sep_work;   // separable ELL rows, runs of up to 64, by class
     int ell_lmax = 1;                     // longest row box axis
@@ -180,6 +180,7 @@ struct fk_plan {
         int fw_lds[fk::kTileClasses] = {0};
         // tile staging (see stage_tiles)
         long long stage_entries = 0;
+        bool all_staged = false;   // no tile flushes with atomics
         std::vector<int> cov_node, cov_ptr, cov_base;
     } adj;
     // forward step lists
@@ -520,6 +521,7 @@ void stage_tiles(fk_plan *p)
     const int d = p->d, NF = d + 1;
     auto &A = p->adj;
     A.stage_entries = 0;
+    A.all_staged = false;
     A.cov_node.clear();
     A.cov_ptr.clear();
     A.cov_base.clear();
@@ -542,6 +544,9 @@ void stage_tiles(fk_plan *p)
         return;
     }
     A.stage_entries = off;
+    A.all_staged = true;
+    for (const fk::TileBox &tb : A.fw_tiles) A.all_staged = A.all_staged && tb.soff >= 0;
+    for (const fk::TileBox &tb : A.box_tiles) A.all_staged = A.all_staged && tb.soff >= 0;
     // each tile entry's packed node (periodic tiles may run past the seam)
     auto visit = [&](const std::vector<fk::TileBox> &tiles, const std::vector<fk::WorkItem> &work,
                      auto &&fn) {
@@ -656,7 +661,7 @@ fk_status build_plan(fk_plan *p)
     for (double a : p->gh_a) amax = std::max(amax, std::fabs(a));
 
     const int npb = kBlock / p->G;
-    std::vector<fk::WorkItem> tables, runs;
+    std::vector<fk::WorkItem> tables;
     long long ell_total = 0, ell_wmax = 0, ell_rows_w = 0;
     std::vector<std::vector<int>> inst_sep, inst_rest;
     std::vector<int> inst_cls, inst_lneed, inst_wraps;
@@ -785,21 +790,6 @@ fk_status build_plan(fk_plan *p)
         for (int a = 0; a < pr.d && na > 0; ++a) {
             I.blo[a] = blo[a];
             I.blen[a] = bhi[a] - blo[a] + 1;
-        }
-        if (na > 0) {
-            const int dl = pr.d - 1;
-            long long rows = 1;
-            for (int a = 0; a < dl; ++a) rows *= (bhi[a] - blo[a] + 1);
-            for (long long r = 0; r < rows; ++r) {
-                long long rr = r, base = 0;
-                for (int a = dl - 1; a >= 0; --a) {
-                    const int len = bhi[a] - blo[a] + 1;
-                    const int ia = blo[a] + (int)(rr % len);
-                    rr /= len;
-                    base += (long long)ia * I.stride[a];
-                }
-                build_work(runs, i, bhi[dl] - blo[dl] + 1, kBlock, (int)(base + blo[dl]), 0);
-            }
         }
         p->cls.insert(p->cls.end(), c.begin(), c.end());
         I.n_act = na;
@@ -1337,8 +1327,11 @@ fk_status build_plan(fk_plan *p)
             stage_tiles(p);
         }
     }
-    // slope pass: pieces of the reachable boxes, 1024 nodes each (four per
-    // thread) when that still gives every CU its eight workgroups, else 256
+    // slope pass and its transpose: pieces of the reachable boxes, 512 nodes each
+    // (two per thread) when those fill the chip more than twice, else 256; a
+    // workgroup each (129^3, FP32: 1024 nodes in 2048 workgroups, whose second
+    // round is nearly empty, 24.4 and 48 us, pieces of 512 24.6 and 38, of 256 31
+    // and 42)
     {
         long long box_nodes_all = 0;
         std::vector<long long> box_n(p->n_inst, 0);
@@ -1348,10 +1341,9 @@ fk_status build_plan(fk_plan *p)
             for (int a = 0; a < p->d; ++a) box_n[i] *= p->inst[i].blen[a];
             box_nodes_all += box_n[i];
         }
-        const int piece = box_nodes_all >= 1024LL * 256 * 8 ? 4 * kBlock : kBlock;
+        const int piece = box_nodes_all >= 1024LL * 256 * 8 ? 2 * kBlock : kBlock;
         p->slope_work = tables;
         for (int i = 0; i < p->n_inst; ++i) build_work(p->slope_work, i, (int)box_n[i], piece);
-        p->run_work = runs;
     }
     p->n_table_work = (int)tables.size();
 
@@ -1507,7 +1499,6 @@ fk_status build_plan(fk_plan *p)
     add_region(p, "tfac", sizeof(double) * p->tfac.size());
     add_region(p, "trig", sizeof(double) * 2 * std::max<size_t>(p->coords.size(), 1));
     add_region(p, "slope_work", sizeof(fk::WorkItem) * std::max<size_t>(p->slope_work.size(), 1));
-    add_region(p, "run_work", sizeof(fk::WorkItem) * std::max<size_t>(p->run_work.size(), 1));
     add_region(p, "node_work", sizeof(fk::WorkItem) * std::max<size_t>(p->node_work.size(), 1));
     add_region(p, "act_work", sizeof(fk::WorkItem) * std::max<size_t>(p->act_work.size(), 1));
     add_region(p, "ell_work", sizeof(fk::WorkItem) * std::max<size_t>(p->ell_work.size(), 1));
@@ -1578,9 +1569,6 @@ void fill_dev(fk_plan *p)
     D.tfac = (const double *)p->at("tfac");
     D.trig = (double2 *)p->at("trig");
     D.slope_work = (const fk::WorkItem *)p->at("slope_work");
-    D.run_work = (const fk::WorkItem *)p->at("run_work");
-    D.n_run_work = (int)p->run_work.size();
-    D.run_grid = grid_for(p->run_work.size());
     D.node_work = (const fk::WorkItem *)p->at("node_work");
     D.act_work = (const fk::WorkItem *)p->at("act_work");
     D.ell_work = (const fk::WorkItem *)p->at("ell_work");
@@ -1625,6 +1613,7 @@ void fill_dev(fk_plan *p)
     D.adj.box_tiles = (const fk::TileBox *)p->at("abox_tiles");
     const bool staged = p->opt.ckpt_every > 0 && p->adj.stage_entries > 0;
     D.adj.stage = staged ? p->at("stage") : nullptr;
+    D.adj.fresh = staged && p->adj.all_staged && p->step_kind != 1 ? 1 : 0;
     D.adj.n_cov = staged ? (int)p->adj.cov_node.size() : 0;
     D.adj.cov_node = staged ? (const int *)p->at("cov_node") : nullptr;
     D.adj.cov_ptr = staged ? (const int *)p->at("cov_ptr") : nullptr;
@@ -1685,7 +1674,7 @@ void fill_dev(fk_plan *p)
     D.pt_groups = p->pt_groups ? 1 : 0;
     D.rel_ok = D.all_affine && !p->wraps ? 1 : 0;
     D.step_kind = p->step_kind;
-    D.slope_grid = grid_for(p->slope_work.size());
+    D.slope_grid = grid_for(p->slope_work.size(), 64);
     D.node_grid = grid_for(p->node_work.size());
     D.act_grid = grid_for(p->act_work.size());
     D.row_grid = grid_for(p->row_work.size());
@@ -2198,7 +2187,6 @@ fk_status upload_tables(fk_plan *p, hipStream_t s)
     FK_TRY(up("gh_w1f", p->gh_w1f.data(), sizeof(float) * p->gh_w1f.size()));
     FK_TRY(up("tfac", p->tfac.data(), sizeof(double) * p->tfac.size()));
     FK_TRY(up("slope_work", p->slope_work.data(), sizeof(fk::WorkItem) * p->slope_work.size()));
-    FK_TRY(up("run_work", p->run_work.data(), sizeof(fk::WorkItem) * p->run_work.size()));
     FK_TRY(up("node_work", p->node_work.data(), sizeof(fk::WorkItem) * p->node_work.size()));
     FK_TRY(up("act_work", p->act_work.data(), sizeof(fk::WorkItem) * p->act_work.size()));
     FK_TRY(up("ell_work", p->ell_work.data(), sizeof(fk::WorkItem) * p->ell_work.size()));

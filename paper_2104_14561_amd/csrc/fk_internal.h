@@ -129,6 +129,7 @@ struct AdjLists {
     // tile staging: each tile's entries (fields interleaved) at its soff; per
     // node the staging entries (field 0) of the tiles that cover it
     void *stage;                // T, or null when the tiles flush with atomics
+    int fresh;                  // every tile is staged: the gather stores mu, which need not be cleared
     int n_cov;                  // nodes covered by a staged tile
     const int *cov_node;        // [n_cov] packed node index
     const int *cov_ptr;         // [n_cov + 1] into cov_base
@@ -158,7 +159,6 @@ struct PlanDev {
     const double *tfac;         // [n_steps][n_inst][kTimeFactors]
     double2 *trig;              // per-axis (sin, cos) of the drift arguments at t_n
     const WorkItem *slope_work; // trig table items, then pieces of the reachable boxes
-    const WorkItem *run_work;   // the reachable boxes as node runs along the last axis (adjoint)
     const WorkItem *node_work;  // all nodes (adjoint passes)
     const WorkItem *act_work;   // step pass work list (block / G active nodes each)
     const WorkItem *row_work;   // row-per-thread work list (block active nodes each)
@@ -166,7 +166,6 @@ struct PlanDev {
     int n_inst;
     int n_slope_work;
     int n_table_work;
-    int n_run_work;
     int n_node_work;
     int n_act_work;
     int n_row_work;
@@ -217,7 +216,6 @@ struct PlanDev {
     int n_split_work;
     int split_grid;
     int slope_grid;             // workgroups of the slope pass
-    int run_grid;               // workgroups of passes over run_work
     int node_grid;              // workgroups of all-node passes
     int act_grid;               // workgroups of the step pass
     int row_grid;               // workgroups of row-per-thread passes

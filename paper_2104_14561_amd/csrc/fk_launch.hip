@@ -237,8 +237,8 @@ hipError_t launch_adjoint_step(const PlanDev &P0, bool f32, int n, const void *p
             // the staged tiles into mu, once both lists have run
             if (part != 1 && P.adj.stage) {
                 FK_DISPATCH_D(P.d,
-                    if (f32) k_gather_tiles<float, D><<<flat_grid(P.adj.n_cov), kBlock, 0, s>>>(P.adj.n_cov, P.adj.cov_node, P.adj.cov_ptr, P.adj.cov_base, (const float *)P.adj.stage, (float *)mu);
-                    else k_gather_tiles<double, D><<<flat_grid(P.adj.n_cov), kBlock, 0, s>>>(P.adj.n_cov, P.adj.cov_node, P.adj.cov_ptr, P.adj.cov_base, (const double *)P.adj.stage, (double *)mu));
+                    if (f32) k_gather_tiles<float, D><<<flat_grid(P.adj.n_cov), kBlock, 0, s>>>(P.adj.n_cov, P.adj.cov_node, P.adj.cov_ptr, P.adj.cov_base, (const float *)P.adj.stage, P.adj.fresh, (float *)mu);
+                    else k_gather_tiles<double, D><<<flat_grid(P.adj.n_cov), kBlock, 0, s>>>(P.adj.n_cov, P.adj.cov_node, P.adj.cov_ptr, P.adj.cov_base, (const double *)P.adj.stage, P.adj.fresh, (double *)mu));
             }
             return hipGetLastError();
         }
@@ -248,28 +248,6 @@ hipError_t launch_adjoint_step(const PlanDev &P0, bool f32, int n, const void *p
     FK_DISPATCH_D(P.d, FK_DISPATCH_G(P.group,
         if (f32) k_adjoint_step<float, D, G><<<P.act_grid, kBlock, 0, s>>>(P, n, (const float *)packed, (const float *)lam, (float *)mu, grad);
         else k_adjoint_step<double, D, G><<<P.act_grid, kBlock, 0, s>>>(P, n, (const double *)packed, (const double *)lam, (double *)mu, grad)));
-    return hipGetLastError();
-}
-
-hipError_t launch_adjoint_slopes_T(const PlanDev &P, bool f32, const void *u, void *mu,
-                                   void *lam_next, hipStream_t s)
-{
-    // every node an adjoint step can touch lies in the slope pass' node runs
-    // (the active region widened by the reach and the slope stencil)
-    const WorkItem *runs = P.run_work;
-    const int r0 = 0, nr = P.n_run_work;
-    if (nr <= 0) return hipSuccess;
-    const int g = P.run_grid;
-    FK_DISPATCH_D(P.d,
-        if (f32) {
-            k_mu_value<float, D><<<g, kBlock, 0, s>>>(P, (float *)mu, (float *)lam_next, runs, r0, nr);
-            k_adjoint_slopes_T<float, D><<<g, kBlock, 0, s>>>(P, (const float *)u, (float *)mu, (float *)lam_next, runs, r0, nr);
-            k_fold_images<float, D><<<g, kBlock, 0, s>>>(P, (float *)lam_next, runs, r0, nr);
-        } else {
-            k_mu_value<double, D><<<g, kBlock, 0, s>>>(P, (double *)mu, (double *)lam_next, runs, r0, nr);
-            k_adjoint_slopes_T<double, D><<<g, kBlock, 0, s>>>(P, (const double *)u, (double *)mu, (double *)lam_next, runs, r0, nr);
-            k_fold_images<double, D><<<g, kBlock, 0, s>>>(P, (double *)lam_next, runs, r0, nr);
-        });
     return hipGetLastError();
 }
 

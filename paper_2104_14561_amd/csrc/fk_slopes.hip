@@ -1,8 +1,48 @@
-// fk_slopes.hip -- the slope pass (F^n of Eq. (e36)) and its launchers.
+// fk_slopes.hip -- the slope pass (F^n of Eq. (e36)), its transpose, and their
+// launchers.
 #include "fk_device.h"
 
 namespace fk {
 namespace {
+
+// Decoding of a region item: nodes of the instance's reachable box numbered
+// along the box from the item's start.  The start is uniform (scalar unit), a
+// lane's offset takes reciprocal multiplications.
+template <int D> struct BoxItem {
+    int ll, lm, row0, in0, pl0, mid0;
+    bool small;
+    unsigned long long rl, rm;
+    __device__ BoxItem(const DevInst &I, int first)
+    {
+        ll = I.blen[D - 1];
+        lm = D == 3 ? I.blen[1] : 1;
+        row0 = D == 1 ? 0 : first / ll;
+        in0 = D == 1 ? first : first - row0 * ll;
+        pl0 = D == 3 ? row0 / lm : 0;
+        mid0 = D == 3 ? row0 - pl0 * lm : 0;
+        small = ll < (1 << 14) && lm < (1 << 14);   // fast_div's range
+        rl = fast_recip(ll);
+        rm = fast_recip(lm);
+    }
+    __device__ void index(const DevInst &I, int o, int *idx) const
+    {
+        const int e = in0 + o;
+        if constexpr (D == 1) {
+            idx[0] = I.blo[0] + e;
+        } else {
+            const int dr = small ? fast_div(e, rl) : e / ll;
+            idx[D - 1] = I.blo[D - 1] + e - dr * ll;
+            if constexpr (D == 2) {
+                idx[0] = I.blo[0] + row0 + dr;
+            } else {
+                const int m = mid0 + dr;
+                const int dp = small ? fast_div(m, rm) : m / lm;
+                idx[1] = I.blo[1] + m - dp * lm;
+                idx[0] = I.blo[0] + pl0 + dp;
+            }
+        }
+    }
+};
 
 // Slope pass for step n over work items [first, first + count): table items
 // (kind 1 + a) fill the (sin, cos) table of axis a; region items (kind 0)
@@ -40,31 +80,10 @@ __global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, 
         }
         const T *ui = u + I.node_off;
         R *rec = reinterpret_cast<R *>(packed) + I.node_off;
-        // start of the item inside the box (uniform), then lane offsets
-        const int ll = I.blen[D - 1], lm = D == 3 ? I.blen[1] : 1;
-        const int row0 = D == 1 ? 0 : it.first / ll;
-        const int in0 = D == 1 ? it.first : it.first - row0 * ll;
-        const int pl0 = D == 3 ? row0 / lm : 0;
-        const int mid0 = D == 3 ? row0 - pl0 * lm : 0;
-        const bool small = ll < (1 << 14) && lm < (1 << 14);   // fast_div's range
-        const unsigned long long rl = fast_recip(ll), rm = fast_recip(lm);
+        const BoxItem<D> box(I, it.first);
         auto at = [&](int o) {
             int idx[3] = {0, 0, 0};
-            int e = in0 + o;
-            if constexpr (D == 1) {
-                idx[0] = I.blo[0] + e;
-            } else {
-                const int dr = small ? fast_div(e, rl) : e / ll;
-                idx[D - 1] = I.blo[D - 1] + e - dr * ll;
-                if constexpr (D == 2) {
-                    idx[0] = I.blo[0] + row0 + dr;
-                } else {
-                    const int m = mid0 + dr;
-                    const int dp = small ? fast_div(m, rm) : m / lm;
-                    idx[1] = I.blo[1] + m - dp * lm;
-                    idx[0] = I.blo[0] + pl0 + dp;
-                }
-            }
+            box.index(I, o, idx);
             int st[3];
             int node = 0;
 #pragma unroll
@@ -101,17 +120,212 @@ __global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, 
             }
             rec[node] = r;
         };
-        if (it.count == 4 * kBlock) {
-            // the four nodes of a thread side by side, for the loads in flight
+        if (it.count == 2 * kBlock) {
+            // the two nodes of a thread side by side, for the loads in flight
 #pragma unroll
-            for (int k = 0; k < 4; ++k) at(k * kBlock + (int)threadIdx.x);
+            for (int k = 0; k < 2; ++k) at(k * kBlock + (int)threadIdx.x);
         } else {
             for (int o = threadIdx.x; o < it.count; o += kBlock) at(o);
         }
     }
 }
 
+// The step's last pass of the transpose over the region items: from mu (per
+// node the cotangents of u and of the slopes) the cotangent of u,
+//   lam[m] = mu_u[m] + sum_a (J_a(u)^T mu_a)[m],
+// gathered: node m along axis a belongs to the slope stencils centred at m - 1,
+// m and m + 1 (an end node's slope to its inner neighbour's stencil).  Exit
+// nodes and images get 0, a node with images their cotangents too.
+//
+// Bound: one read of mu and u and one write of lam (24 bytes per node in FP32,
+// 3D) and the nine slope derivatives of a node.  It was three launches (value,
+// scatter with nine atomic adds per node, fold) which also cleared mu for the
+// next step; the gather of the tiles now stores instead of adding.  129^3 in
+// FP32: 75 us in three launches, 38 now, the gather 41 and 33 us; the FP32 part
+// of the 64-instance batch 49 and 18.5 us.
+template <typename T, int D>
+__global__ void __launch_bounds__(kBlock) k_slopes_T(PlanDev P, int first, int count,
+                                                     const T *__restrict__ u,
+                                                     const T *__restrict__ mu,
+                                                     T *__restrict__ lam)
+{
+    constexpr int PS = RecStride<D>::value;
+    using R = typename RecT<T, PS>::type;
+    const WorkRange wr = work_range(first, count);
+    for (int w = wr.begin; w < wr.end; w += wr.step) {
+        const WorkItem it = P.slope_work[w];
+        const DevInst &I = P.inst[it.inst];
+        const T *ui = u + I.node_off;
+        const T *mi = mu + I.node_off * PS;
+        const BoxItem<D> box(I, it.first);
+        for (int o = threadIdx.x; o < it.count; o += kBlock) {
+            int idx[3] = {0, 0, 0}, st[3];
+            box.index(I, o, idx);
+            int node = 0, img = 0;
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+                st[a] = a == D - 1 ? 1 : (int)I.stride[a];
+                node += idx[a] * st[a];
+                if (I.periodic[a] && idx[a] == 0) img |= 1 << a;
+            }
+            if (P.chi[I.node_off + node] != 0) {
+                lam[I.node_off + node] = T(0);
+                continue;
+            }
+            // field f of node j's images along the axes of mask
+            auto images = [&](int j, int mask, int f) {
+                T s = T(0);
+                for (int k = 1; k < (1 << D); ++k) {
+                    if ((k & ~mask) != 0) continue;
+                    int jj = j;
+                    for (int a = 0; a < D; ++a)
+                        if (k & (1 << a)) jj += (I.n[a] - 1) * st[a];
+                    s += mi[(long long)jj * PS + f];
+                }
+                return s;
+            };
+            const R rc = reinterpret_cast<const R *>(mi)[node];
+            T acc = rc.x;
+            if (img != 0) acc += images(node, img, 0);
+            const T uc = ui[node];
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+                const int na = I.n[a], i = idx[a], base = node - i * st[a];
+                const bool per = I.periodic[a] != 0;
+                const int mask = img & ~(1 << a);
+                // node at distance k along the axis (clamped: without weight there)
+                auto pos = [&](int k) {
+                    int p = i + k;
+                    if (per) p = p < 0 ? p + na - 1 : (p >= na - 1 ? p - (na - 1) : p);
+                    else p = min(max(p, 0), na - 1);
+                    return p;
+                };
+                const int p0 = pos(-1), p2 = pos(1);
+                const T um2 = ui[base + pos(-2) * st[a]], um1 = ui[base + p0 * st[a]];
+                const T up1 = ui[base + p2 * st[a]], up2 = ui[base + pos(2) * st[a]];
+                const bool in0 = per || i >= 2, in1 = per || (i >= 1 && i <= na - 2), in2 = per || i <= na - 3;
+                T own = rc.y;
+                if constexpr (PS == 4) own = a == 0 ? rc.y : (a == 1 ? rc.z : rc.w);
+                const T *ma = mi + 1 + a;
+                T m0 = ma[(long long)(base + p0 * st[a]) * PS], m1 = own;
+                T m2 = ma[(long long)(base + p2 * st[a]) * PS];
+                // near an end the stencils centred here also serve the end node (or
+                // the image of node 0), and images along other axes count
+                if (mask != 0 || (per ? i <= 1 || i >= na - 2 : i <= 2 || i >= na - 3)) {
+                    auto more = [&](int p, int own_node) {
+                        T m = T(0);
+                        if (mask != 0) m += images(own_node, mask, 1 + a);
+                        auto end = [&](int q) {
+                            const int j = base + q * st[a];
+                            m += ma[(long long)j * PS];
+                            if (mask != 0) m += images(j, mask, 1 + a);
+                        };
+                        if (per) {
+                            if (p == 0) end(na - 1);
+                        } else {
+                            if (p == 1) end(0);
+                            if (p == na - 2) end(na - 1);
+                        }
+                        return m;
+                    };
+                    m0 += more(p0, base + p0 * st[a]);
+                    m1 += more(i, node);
+                    m2 += more(p2, base + p2 * st[a]);
+                }
+                m0 = in0 ? m0 : T(0);
+                m1 = in1 ? m1 : T(0);
+                m2 = in2 ? m2 : T(0);
+                // inverse spacings of the cells m - 2 .. m + 1
+                T r0, r1, r2, r3;
+                if (I.affine[a]) {
+                    r0 = r1 = r2 = r3 = (T)I.inv_h[a];
+                } else {
+                    const double *x = P.coords + I.coord_off[a];
+                    auto inv = [&](int p) { return T(1) / (T)(x[p + 1] - x[p]); };
+                    auto cell = [&](int k) {
+                        int p = i + k;
+                        if (per) p = p < 0 ? p + na - 1 : (p >= na - 1 ? p - (na - 1) : p);
+                        return min(max(p, 0), na - 2);
+                    };
+                    r0 = inv(cell(-2));
+                    r1 = inv(cell(-1));
+                    r2 = inv(cell(0));
+                    r3 = inv(cell(1));
+                }
+                // m dF/d(left difference) / h_l and m dF/d(right difference) / h_r;
+                // 0 where a divided difference vanishes, including differences that
+                // are rounding noise of a flat stretch (below 2^-30 of the values; in
+                // FP32 that is exact equality)
+                auto part = [&](T vl, T vc, T vr, T rl, T rr, T m, T &cl, T &cr) {
+                    constexpr T tau = T(0x1p-30);
+                    const T el = vc - vl, er = vr - vc;
+                    const T dl = el * rl, dr = er * rr;
+                    bool ok = m != T(0) && dl * dr > T(0);
+                    if constexpr (sizeof(T) == 8)
+                        ok = ok && fabs(el) > tau * (fabs(vc) + fabs(vl)) && fabs(er) > tau * (fabs(vr) + fabs(vc));
+                    const T inv = T(1) / (dl + dr);
+                    const T x = dr * inv, y = dl * inv;
+                    cl = ok ? T(2) * x * x * m * rl : T(0);
+                    cr = ok ? T(2) * y * y * m * rr : T(0);
+                };
+                T cl, cr;
+                part(um2, um1, uc, r0, r1, m0, cl, cr);
+                acc += cr;
+                part(um1, uc, up1, r1, r2, m1, cl, cr);
+                acc += cl - cr;
+                part(uc, up1, up2, r2, r3, m2, cl, cr);
+                acc -= cl;
+            }
+            lam[I.node_off + node] = acc;
+        }
+    }
+}
+
+// mu <- 0 over the region items (plans whose tiles do not all pass the gather).
+template <typename T, int D>
+__global__ void __launch_bounds__(kBlock) k_mu_clear(PlanDev P, int first, int count, T *__restrict__ mu)
+{
+    constexpr int PS = RecStride<D>::value;
+    using R = typename RecT<T, PS>::type;
+    const WorkRange wr = work_range(first, count);
+    for (int w = wr.begin; w < wr.end; w += wr.step) {
+        const WorkItem it = P.slope_work[w];
+        const DevInst &I = P.inst[it.inst];
+        R *mr = reinterpret_cast<R *>(mu) + I.node_off;
+        const BoxItem<D> box(I, it.first);
+        for (int o = threadIdx.x; o < it.count; o += kBlock) {
+            int idx[3] = {0, 0, 0};
+            box.index(I, o, idx);
+            int node = 0;
+#pragma unroll
+            for (int a = 0; a < D; ++a) node += idx[a] * (a == D - 1 ? 1 : (int)I.stride[a]);
+            R z;
+            z.x = z.y = T(0);
+            if constexpr (PS == 4) z.z = z.w = T(0);
+            mr[node] = z;
+        }
+    }
+}
+
 }  // namespace
+
+hipError_t launch_adjoint_slopes_T(const PlanDev &P, bool f32, const void *u, void *mu,
+                                   void *lam_next, hipStream_t s)
+{
+    // every node that an adjoint step can touch lies in the reachable boxes
+    // (the active region widened by the reach and the slope stencil)
+    const int first = P.n_table_work, count = P.n_slope_work - P.n_table_work;
+    if (count <= 0) return hipSuccess;
+    FK_DISPATCH_D(P.d,
+        if (f32) {
+            k_slopes_T<float, D><<<P.slope_grid, kBlock, 0, s>>>(P, first, count, (const float *)u, (const float *)mu, (float *)lam_next);
+            if (!P.adj.fresh) k_mu_clear<float, D><<<P.slope_grid, kBlock, 0, s>>>(P, first, count, (float *)mu);
+        } else {
+            k_slopes_T<double, D><<<P.slope_grid, kBlock, 0, s>>>(P, first, count, (const double *)u, (const double *)mu, (double *)lam_next);
+            if (!P.adj.fresh) k_mu_clear<double, D><<<P.slope_grid, kBlock, 0, s>>>(P, first, count, (double *)mu);
+        });
+    return hipGetLastError();
+}
 
 hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void *packed,
                          hipStream_t s)
