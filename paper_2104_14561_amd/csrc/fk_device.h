@@ -1711,6 +1711,97 @@ __global__ void __launch_bounds__(kBlock) k_ell_apply(PlanDev P, const int *__re
     }
 }
 
+// The same product for small plans, four lanes per row (each a quarter of its
+// value blocks, 16 neighbouring rows side by side in a wave) and a column of
+// Algorithm 1 per blockIdx.y: column c's records at packed + c * plane, its
+// field at u_out + c * fstride.  Below a quarter of a million rows a lane per row
+// leaves most of the chip's wavefront slots empty and the time is one row's
+// chain of dependent block loads and gathers; the values that the columns read
+// again come from the L2.  257^2 nodes with a disc, four columns in FP32: 20.8 us
+// a lane per row, 8.4 so.
+template <typename T, int D>
+__global__ void __launch_bounds__(kBlock) k_ell_apply_split(PlanDev P, const int *__restrict__ org,
+                                                            const T *__restrict__ vals,
+                                                            const T *__restrict__ exit_mass,
+                                                            const T *__restrict__ packed,
+                                                            long long plane, T *__restrict__ u_out,
+                                                            long long fstride)
+{
+    constexpr int PS = RecStride<D>::value, G = 4, NW = kWave / G, NS = G;
+    using R = typename RecT<T, PS>::type;
+    const R *rec = reinterpret_cast<const R *>(packed + blockIdx.y * plane);
+    u_out += blockIdx.y * fstride;
+    const int wl = threadIdx.x % kWave, part = wl / NW;
+    const int slot = threadIdx.x / kWave * NW + wl % NW;
+    const WorkRange wr = work_range(0, P.n_row_work * NS);
+    for (int w = wr.begin; w < wr.end; w += wr.step) {
+        const WorkItem it = P.row_work[w / NS];
+        const int sub = (w % NS) * (kBlock / G);
+        if (sub >= it.count) continue;
+        const bool valid = sub + slot < it.count;
+        const DevInst &I = P.inst[it.inst];
+        const long long rows = I.n_act;
+        const long long r = it.first + min(sub + slot, it.count - 1);
+        const long long row = I.act_off + r;
+        const int node = P.active[row];
+        const T uref = rec[I.node_off + node].x;
+        int o[3] = {0, 0, 0};
+        for (int a = 0; a < D; ++a) o[a] = org[row * 3 + a];
+        constexpr int K = EllBlock<T>::K;
+        using B = EllBlock<T>;
+        const int bpf = I.ell_nbp / K;
+        const B *v0 = reinterpret_cast<const B *>(vals + I.ell_off) + r;
+        const long long fs = (long long)bpf * rows;   // stride between field planes, in blocks
+        const int lb0 = bpf * part / G, lb1 = bpf * (part + 1) / G;
+        int bi[3] = {0, 0, 0};
+        {
+            int e = lb0 * K;
+#pragma unroll
+            for (int a = D - 1; a > 0; --a) {
+                const int q = e / I.ell_box[a];
+                bi[a] = e - q * I.ell_box[a];
+                e = q;
+            }
+            bi[0] = e < I.ell_box[0] ? e : 0;
+        }
+        T acc = T(0);
+#pragma unroll 2
+        for (int lb = lb0; lb < lb1; ++lb) {
+            const B *vp = v0 + (long long)lb * rows;
+            B vf[D + 1];
+#pragma unroll
+            for (int f = 0; f <= D; ++f) vf[f] = vp[f * fs];
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                long long nd = I.node_off;
+#pragma unroll
+                for (int a = 0; a < D; ++a) {
+                    int ia = o[a] + bi[a];
+                    if (ia > I.n[a] - 1) ia = I.n[a] - 1;   // zero-valued box nodes stay in range
+                    nd += (long long)ia * I.stride[a];
+                }
+                const R rc = rec[nd];
+                acc += vf[0].v[j] * (rc.x - uref) + vf[1].v[j] * rc.y;
+                if constexpr (D >= 2) acc += vf[2].v[j] * rc.z;
+                if constexpr (D == 3) acc += vf[3].v[j] * rc.w;
+#pragma unroll
+                for (int a = D - 1; a >= 0; --a) {
+                    if (++bi[a] < I.ell_box[a]) break;
+                    bi[a] = 0;
+                }
+            }
+        }
+#pragma unroll
+        for (int off = NW; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+        if (!valid || part != 0) continue;
+        int idx[3];
+        split_node<D>(I, node, idx);
+        const T v = uref + (acc + exit_mass[row] * (T(1) - uref));
+        flag_nonfinite(P.flags, v);
+        store_node<D, T>(I, idx, node, v, u_out);
+    }
+}
+
 // Multi-column product (Algorithm 1): the assembled A_n applied to nc <= NC
 // columns at once, a sparse matrix times a dense block.  Each row's value
 // blocks are read once and contracted with the records of every column

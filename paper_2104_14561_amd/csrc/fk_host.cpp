@@ -1899,7 +1899,6 @@ fk_status enqueue_horizons(fk_plan *p, const int *hz, int n_h, void *u_out, hipS
         int *org = (int *)p->at("ell_org");
         void *vals = p->at("ell_vals"), *em = p->at("ell_em");
         unsigned char *planes = (unsigned char *)p->at("packed_mc");
-        const size_t plane_b = fb * rec_stride(p->d);
         FK_LAUNCH(fk::launch_tables(p->dev, step, s));
         FK_LAUNCH(fk::launch_assemble_ell(p->dev, p->f32, step, org, vals, em, s));
         for (size_t k0 = first; k0 < order.size();) {
@@ -1907,9 +1906,8 @@ fk_status enqueue_horizons(fk_plan *p, const int *hz, int n_h, void *u_out, hipS
             // entries whose fields are adjacent in u_out
             int nc = 1;
             while (nc < chunk && k0 + nc < order.size() && order[k0 + nc] == order[k0] + nc) ++nc;
-            for (int c = 0; c < nc; ++c)
-                FK_LAUNCH(fk::launch_slopes(p->dev, p->f32, step, col(order[k0 + c]),
-                                            planes + (size_t)c * plane_b, s));
+            FK_LAUNCH(fk::launch_slopes_mc(p->dev, p->f32, step, col(order[k0]), (long long)fe, planes,
+                                           (long long)(fe * rec_stride(p->d)), nc, s));
             FK_LAUNCH(fk::launch_ell_apply_mc(p->dev, p->f32, org, vals, em, planes,
                                               (long long)(fe * rec_stride(p->d)), col(order[k0]),
                                               (long long)fe, nc, s));

@@ -249,6 +249,10 @@ struct PlanDev {
 hipError_t launch_init_field(const PlanDev &P, bool f32, void *u, hipStream_t s);
 hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void *packed,
                          hipStream_t s);
+// the slope pass of nc columns (fields ustride, records pstride elements apart),
+// the tables of step n in place
+hipError_t launch_slopes_mc(const PlanDev &P, bool f32, int n, const void *u, long long ustride,
+                            void *packed, long long pstride, int nc, hipStream_t s);
 hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s);
 constexpr int kReTab = 8;   // runaway model: tabulated values per coordinate
 // the runaway model's per-coordinate tables at step n (P.retab)

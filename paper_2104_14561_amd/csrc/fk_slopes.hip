@@ -58,10 +58,14 @@ template <int D> struct BoxItem {
 // 256-thread workgroup idle.  129^3 FP32: 57 us with a workgroup per row and
 // three divisions per axis, 24 us now; the FP32 part of the 64-instance batch
 // 31 us, now 22 us.
+//
+// Several columns (Algorithm 1) in one launch: column c = blockIdx.y, its field
+// at u + c * ustride, its records at packed + c * pstride.
 template <typename T, int D, bool TW>
 __global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, int count,
                                                    const T *__restrict__ u,
-                                                   T *__restrict__ packed)
+                                                   T *__restrict__ packed,
+                                                   long long ustride, long long pstride)
 {
     constexpr int PS = RecStride<D>::value;
     using R = typename RecT<T, PS>::type;
@@ -78,8 +82,8 @@ __global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, 
             P.trig[I.coord_off[a] + i] = make_double2(sin(arg), cos(arg));
             continue;
         }
-        const T *ui = u + I.node_off;
-        R *rec = reinterpret_cast<R *>(packed) + I.node_off;
+        const T *ui = u + blockIdx.y * ustride + I.node_off;
+        R *rec = reinterpret_cast<R *>(packed + blockIdx.y * pstride) + I.node_off;
         const BoxItem<D> box(I, it.first);
         auto at = [&](int o) {
             int idx[3] = {0, 0, 0};
@@ -337,8 +341,8 @@ hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void 
     }
 #define FK_SLOPES(TW_)                                                                          \
     FK_DISPATCH_D(P.d,                                                                          \
-        if (f32) k_slopes<float, D, TW_><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const float *)u, (float *)packed); \
-        else k_slopes<double, D, TW_><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const double *)u, (double *)packed))
+        if (f32) k_slopes<float, D, TW_><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const float *)u, (float *)packed, 0, 0); \
+        else k_slopes<double, D, TW_><<<P.slope_grid, kBlock, 0, s>>>(P, n, 0, P.n_slope_work, (const double *)u, (double *)packed, 0, 0))
     if (P.hermite2) {
         FK_SLOPES(true);
     } else {
@@ -357,7 +361,19 @@ hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s)
     if (P.n_table_work == 0) return hipSuccess;
     const int g = P.n_table_work >= 8 ? (P.n_table_work + 7) / 8 * 8 : P.n_table_work;
     FK_DISPATCH_D(P.d,
-        k_slopes<double, D, false><<<g, kBlock, 0, s>>>(P, n, 0, P.n_table_work, nullptr, nullptr));
+        k_slopes<double, D, false><<<g, kBlock, 0, s>>>(P, n, 0, P.n_table_work, nullptr, nullptr, 0, 0));
+    return hipGetLastError();
+}
+
+hipError_t launch_slopes_mc(const PlanDev &P, bool f32, int n, const void *u, long long ustride,
+                            void *packed, long long pstride, int nc, hipStream_t s)
+{
+    const int first = P.n_table_work, count = P.n_slope_work - P.n_table_work;
+    if (count <= 0) return hipSuccess;
+    const dim3 g(P.slope_grid, nc);
+    FK_DISPATCH_D(P.d,
+        if (f32) k_slopes<float, D, false><<<g, kBlock, 0, s>>>(P, n, first, count, (const float *)u, (float *)packed, ustride, pstride);
+        else k_slopes<double, D, false><<<g, kBlock, 0, s>>>(P, n, first, count, (const double *)u, (double *)packed, ustride, pstride));
     return hipGetLastError();
 }
 
