@@ -69,8 +69,9 @@ __device__ inline void sep_gradient(const DevInst &I, int a, int idx, double bdt
 // past the node's footprint carry no weight: along the row they may fall on
 // any later entry of the tile (the host leaves L entries behind it), outside
 // the tile's rows or before its first column they are clamped.  Bound: the LDS
-// adds, 17 to 24 cycles of a CU per wave instruction (left out, the FP32
-// classes of the batch take 10 to 16 us instead of 40 to 53).
+// adds, 8.4 cycles of a CU per wave instruction at best, about 11 here (lanes
+// whose footprints start differently meet; left out, the FP32 classes of the
+// batch take 10 to 16 us instead of 39 to 46).
 template <typename T, int QS, int L, int BS>
 __global__ void __launch_bounds__(BS) k_adjoint_sep2(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
@@ -136,11 +137,13 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep2(
             const int pitch = tile.pitch, plane = tile.plane;
             auto rows = [&](auto lr) {
                 constexpr int LR = decltype(lr)::value;
-                auto row = [&](int i, const R *rr, auto &&at, auto &&tat) {
+                // t_first + tat(j): entry of column j in the tile's row
+                auto row = [&](int i, const R *rr, auto &&at, int t_first, auto &&tat) {
                     const V2 e = col[i * BS];
                     const T v0 = e.x, q0 = e.y * h0;
                     const T lv = Lm * v0, ls = Lm * q0;
-                    double *tp = tmem + min(max(tr0 + i, 0), tile.ext[0] - 1) * pitch;
+                    double *t0 = tmem + (min(max(tr0 + i, 0), tile.ext[0] - 1) * pitch + t_first);
+                    double *t1 = t0 + plane, *t2 = t1 + plane;
                     T tA = T(0), tB = T(0);
 #pragma unroll
                     for (int j = 0; j < LR; ++j) {
@@ -150,10 +153,10 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep2(
                         tB = fma_t(V1[j], r.y, tB);
                         A1[j] = fma_t(v0, u, fma_t(q0, r.y, A1[j]));
                         B1[j] = fma_t(v0, r.z, B1[j]);
-                        double *e1 = tp + tat(j);
-                        lds_add(e1, (double)(lv * V1[j]));
-                        lds_add(e1 + plane, (double)(ls * V1[j]));
-                        lds_add(e1 + 2 * plane, (double)(lv * S1[j]));
+                        const int e = tat(j);
+                        lds_add(t0 + e, (double)(lv * V1[j]));
+                        lds_add(t1 + e, (double)(ls * V1[j]));
+                        lds_add(t2 + e, (double)(lv * S1[j]));
                     }
                     V2 ab;
                     ab.x = tA;
@@ -164,12 +167,12 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep2(
                     const R *rc = ri + o1;
                     for (int i = 0; i < L0; ++i)
                         row(i, rc + wrap_index(o0 + i, n0, per0) * s0, [](int j) { return j; },
-                            [&](int j) { return tc0 + j; });
+                            tc0, [](int j) { return j; });
                 } else {
                     for (int i = 0; i < L0; ++i)
                         row(i, ri + wrap_index(o0 + i, n0, per0) * s0,
                             [&](int j) { return wrap_index(o1 + j, n1, per1); },
-                            [&](int j) { return max(tc0 + j, 0); });
+                            0, [&](int j) { return max(tc0 + j, 0); });
                 }
             };
             if (L > 6 || L1 > 3) rows(std::integral_constant<int, L>{});
@@ -383,12 +386,17 @@ __global__ void __launch_bounds__(64 * QS, sizeof(T) == 4 ? 6 : 2) k_adjoint_pt2
 // 3D.  LDS: per thread a column of (V0, S0) pairs, replaced by (A0, B0) row by
 // row, one of (V1, S1) and one of the sums (A1, B1); the axis-2 vectors and
 // sums are registers.  Footprints up to 4 nodes (UN) unroll the rows and keep
-// (A1, B1) in registers too.  129^3 ABC flow (3-node footprints) in FP32:
-// 209 us, 369 us with derivative vectors per axis (224 VGPRs); 65^3 in FP64 with
-// 6 x 6 x 9 footprints 386 us against 47.7 ms per landing point (a tile of that
-// reach did not fit LDS, and every add went to global memory).
+// (A1, B1) in registers too; in FP32 with 3-node footprints four workgroups fit
+// a CU (126 VGPRs, 40 KB).  Bound: vector issue (1970 instructions per node's
+// wave, 100 us of the 162 below at 129^3), then the adds: a wave takes 4 rows
+// of 16 nodes (8 rows of 8 met two by two on the LDS banks, 16.4 cycles per add).
+// 129^3 ABC flow (3-node footprints) in FP32: 369 us with derivative vectors per
+// axis (224 VGPRs), 208 with sums, 182 in rows of 16 and a cell's fields flushed
+// together, 162 with the fourth workgroup; 65^3 in FP64 with 6 x 6 x 9 footprints
+// 386 us against 47.7 ms per landing point (a tile of that reach did not fit LDS,
+// and every add went to global memory).
 template <typename T, int QS, int L, int BS>
-__global__ void __launch_bounds__(BS) k_adjoint_sep3(
+__global__ void __launch_bounds__(BS, (sizeof(T) == 4 && L == 3) ? 4 : 1) k_adjoint_sep3(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
     const WorkItem *__restrict__ work, const TileBox *__restrict__ tiles,
     const int *__restrict__ nodes, const double2 *__restrict__ trig,
@@ -410,9 +418,10 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep3(
         const int L0 = UN ? L : min(I.sep_l[0], L), L1 = UN ? L : min(I.sep_l[1], L);
         const int L2 = UN ? L : min(I.sep_l[2], L);
         // columns (guards at both ends): axis 0, axis 1, axis-1 sums; the axis-2
-        // vectors and sums pass through the first and second together
+        // vectors and sums pass through the first and second together; unrolled,
+        // the first's upper and the second's lower guard are one
         V2 *cA = reinterpret_cast<V2 *>(smem_raw) + BS + threadIdx.x;
-        const int nA = max(L0, L2) + 2, nB = L1 + 2;
+        const int nA = max(L0, L2) + (UN ? 1 : 2), nB = L1 + 2;
         V2 *cB = cA + nA * BS, *cC = cB + nB * BS;
         double *const tmem = reinterpret_cast<double *>(smem_raw) +
                              (nA + (UN ? 1 : 2) * nB) * BS * (sizeof(V2) / 8);
@@ -477,7 +486,7 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep3(
             const int per0 = I.periodic[0], per1 = I.periodic[1], per2 = I.periodic[2];
             const int t0 = o0 - tile.lo[0], t1 = o1 - tile.lo[1], t2 = o2 - tile.lo[2];
             const int pitch = tile.pitch, plane = tile.plane;
-            auto box = [&](int o2b, auto &&at, auto &&tat) {
+            auto box = [&](int o2b, auto &&at, int t_first, auto &&tat) {
                 auto slab = [&](int i) {
                     const V2 e0 = cA[i * BS];
                     const T v0 = e0.x, q0 = e0.y * h0;
@@ -488,7 +497,8 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep3(
                         const V2 e1 = cB[j * BS];
                         const T v1 = e1.x, q1 = e1.y * h1;
                         const R *rr = ri + (r0 + wrap_index(o1 + j, n1, per1) * s1);
-                        double *tp = tmem + (p0 + min(max(t1 + j, 0), tile.ext[1] - 1)) * pitch;
+                        double *d0 = tmem + ((p0 + min(max(t1 + j, 0), tile.ext[1] - 1)) * pitch + t_first);
+                        double *d1 = d0 + plane, *d2 = d1 + plane, *d3 = d2 + plane;
                         const T vv = v0 * v1, sv = q0 * v1, vs = v0 * q1;
                         const T fa = Lm * vv, fb = Lm * sv, fc = Lm * vs;
                         T su = T(0), s_0 = T(0), s_1 = T(0);
@@ -501,11 +511,11 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep3(
                             s_1 = fma_t(V2_[k], r.z, s_1);
                             A2[k] = fma_t(vv, u, fma_t(sv, r.y, fma_t(vs, r.z, A2[k])));
                             B2[k] = fma_t(vv, r.w, B2[k]);
-                            double *e2 = tp + tat(k);
-                            lds_add(e2, (double)(fa * V2_[k]));
-                            lds_add(e2 + plane, (double)(fb * V2_[k]));
-                            lds_add(e2 + 2 * plane, (double)(fc * V2_[k]));
-                            lds_add(e2 + 3 * plane, (double)(fa * S2_[k]));
+                            const int e = tat(k);
+                            lds_add(d0 + e, (double)(fa * V2_[k]));
+                            lds_add(d1 + e, (double)(fb * V2_[k]));
+                            lds_add(d2 + e, (double)(fc * V2_[k]));
+                            lds_add(d3 + e, (double)(fa * S2_[k]));
                         }
                         A0 = fma_t(v1, su, fma_t(q1, s_1, A0));
                         B0 = fma_t(v1, s_0, B0);
@@ -534,9 +544,9 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep3(
                 for (int i = 0; i < L0; ++i) slab(i);
             };
             if (__all(o2 >= 0 && o2 + L <= n2))
-                box(o2, [](int k) { return k; }, [&](int k) { return t2 + k; });
+                box(o2, [](int k) { return k; }, t2, [](int k) { return k; });
             else
-                box(0, [&](int k) { return wrap_index(o2 + k, n2, per2); },
+                box(0, [&](int k) { return wrap_index(o2 + k, n2, per2); }, 0,
                     [&](int k) { return max(t2 + k, 0); });
             T Gz[3], Hz[3];
             gradient(0, cA, Gz[0], Hz[0]);

@@ -87,7 +87,7 @@ __device__ inline WorkRange work_range(int first, int n_work)
 // makes (n m) >> 32 exact while n d < 2^32.
 __device__ inline unsigned long long fast_recip(int d)
 {
-    return (1ull << 32) / (unsigned long long)d + 1ull;
+    return (unsigned long long)(0xffffffffu / (unsigned)d) + 1ull;
 }
 __device__ inline int fast_div(int n, unsigned long long m)
 {
@@ -2066,16 +2066,15 @@ struct MuTile {
     double *lds;
     int lo[3], ext[3];
     int pitch, plane, total;
-    // reciprocals for the flush's index decoding: floor(n / d) = (n m) >> 32
-    // with m = floor(2^32 / d) + 1, exact while n d < 2^32 (tiles hold fewer
-    // than 2^13 entries)
-    unsigned long long rplane, rpitch, rext1, rlast;
     int soff, cells;
     bool use;
 
+    // reciprocals for the flush's index decoding: floor(n / d) = (n m) >> 32
+    // with m = floor((2^32 - 1) / d) + 1, exact while n d < 2^32 (tiles hold
+    // fewer than 2^15 entries)
     __device__ static unsigned long long recip(int d)
     {
-        return (1ull << 32) / (unsigned long long)d + 1ull;
+        return (unsigned long long)(0xffffffffu / (unsigned)d) + 1ull;
     }
     __device__ static int qdiv(int n, unsigned long long m)
     {
@@ -2095,10 +2094,6 @@ struct MuTile {
         for (int a = 0; a < D - 1; ++a) plane *= ext[a];
         plane *= pitch;
         total = NF * plane;
-        rplane = recip(plane);
-        rpitch = recip(pitch);
-        rext1 = recip(ext[1] > 0 ? ext[1] : 1);
-        rlast = recip(ext[D - 1]);
         soff = tb.soff;
         cells = plane / pitch * ext[D - 1];
     }
@@ -2148,15 +2143,23 @@ struct MuTile {
     {
         if (!use) return;
         if (stage != nullptr && soff >= 0) {
-            // slot order (cell, field): consecutive lanes store consecutive words
-            T *slot = stage + soff;
-            for (int k = threadIdx.x; k < cells * NF; k += blockDim.x) {
-                const int c = k / NF, f = k - c * NF;
-                const int row = qdiv(c, rlast), ll = c - row * ext[D - 1];
-                slot[k] = (T)lds[f * plane + row * pitch + ll];
+            // slot order (cell, field): a lane stores a cell's fields, consecutive
+            // lanes consecutive cells
+            struct Cell { T f[NF]; };
+            Cell *slot = reinterpret_cast<Cell *>(stage + soff);
+            const unsigned long long rlast = recip(ext[D - 1]);
+            for (int c = threadIdx.x; c < cells; c += blockDim.x) {
+                const int row = qdiv(c, rlast);
+                const double *e = lds + (row * pitch + c - row * ext[D - 1]);
+                Cell v;
+#pragma unroll
+                for (int f = 0; f < NF; ++f) v.f[f] = (T)e[f * plane];
+                slot[c] = v;
             }
             return;
         }
+        const unsigned long long rplane = recip(plane), rpitch = recip(pitch);
+        const unsigned long long rext1 = recip(ext[1] > 0 ? ext[1] : 1);
         for (int e = threadIdx.x; e < total; e += blockDim.x) {
             const T v = (T)lds[e];
             if (v == T(0)) continue;

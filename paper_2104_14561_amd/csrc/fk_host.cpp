@@ -799,14 +799,9 @@ fk_status build_plan(fk_plan *p)
         build_work(p->node_work, i, (int)J, kBlock);
         build_work(p->act_work, i, na, npb);
         // separable nodes: every active node of a box region; for a ball, nodes
-        // whose landing points stay strictly inside it (distance + reach < r)
+        // whose landing points stay strictly inside it (the box of half lengths
+        // reach_a around the node lies inside)
         {
-            double reach2 = 0.0;
-            for (int a = 0; a < pr.d; ++a) {
-                const double ra = drift_bound(pr, a) * pr.dt + I.S * amax;
-                reach2 += ra * ra;
-            }
-            const double reach = std::sqrt(reach2);
             int Lneed = 0;
             bool wraps = false;   // a landing cell more than one period away
             for (int a = 0; a < pr.d; ++a) {
@@ -833,13 +828,13 @@ fk_status build_plan(fk_plan *p)
                 // axis (with a relative margin for the rounding of z), nor the ball
                 bool interior = true;
                 long long r = j;
-                double dist2 = 0.0;
+                double far2 = 0.0;   // of the box's farthest corner from the centre
                 for (int a = pr.d - 1; a >= 0; --a) {
                     const int ia = (int)(r % pr.ax[a].n);
                     r /= pr.ax[a].n;
                     const double x = pr.ax[a].nodes[ia];
-                    const double dx = x - pr.center[a];
-                    dist2 += dx * dx;
+                    const double dx = std::fabs(x - pr.center[a]) + reach_a[a];
+                    far2 += dx * dx;
                     if (!pr.ax[a].periodic) {
                         const double lo = pr.ax[a].nodes[0], hi = pr.ax[a].nodes[pr.ax[a].n - 1];
                         const double m = reach_a[a] * (1.0 + 1e-6) + 1e-12 * (hi - lo);
@@ -847,7 +842,7 @@ fk_status build_plan(fk_plan *p)
                     }
                 }
                 if (pr.region_kind == FK_REGION_BALL) {
-                    separable = std::sqrt(dist2) + reach < pr.radius * (1.0 - 1e-9);
+                    separable = std::sqrt(far2) < pr.radius * (1.0 - 1e-9);
                     interior = interior && separable;
                 }
                 inner[j] = interior ? 1 : 0;
@@ -947,10 +942,10 @@ fk_status build_plan(fk_plan *p)
         }
         const int gs = std::max(2, group_of(p->qs));
         std::vector<std::vector<fk::WorkItem>> bw(fk::kBoxClasses);
-        // node lists in patch order (16x16 in 2D, 4x8x8 in 3D, 256 in 1D):
+        // node lists in patch order (16x16 in 2D, 4x4x16 in 3D, 256 in 1D):
         // a work item never straddles a patch, so its landing footprint (and
         // the adjoint's LDS tile of mu) stays compact
-        static const int kPatch[3][3] = {{256, 1, 1}, {16, 16, 1}, {4, 8, 8}};
+        static const int kPatch[3][3] = {{256, 1, 1}, {16, 16, 1}, {4, 4, 16}};
         auto patch_sort = [&](std::vector<int> &list, const fk_problem &pr,
                               std::vector<long long> &keys, const int *pd = nullptr) {
             if (!pd) pd = kPatch[pr.d - 1];
@@ -1207,22 +1202,14 @@ fk_status build_plan(fk_plan *p)
             *bytes = elems * elt_b;
             return tb;
         };
-        // the pitch, at most a quarter longer than the row, whose rows (16 nodes
-        // by 4 in 2D, 8 by 8 in 3D: a wave's part of a patch) fall on the 32
-        // double-wide LDS banks most evenly
+        // the pitch: a multiple of 16 where that is at most a quarter longer than
+        // the row.  An LDS add takes 16 lanes at a time (8.4 cycles of a CU per wave
+        // instruction, 16.4 where two of the 16 meet on one of 16 double-wide
+        // banks): a patch's full rows of 16 nodes meet on none at any pitch, those
+        // that start amid the 16 lanes on none at a multiple of 16
         auto pitch_wave = [&](int last) {
-            const int nc = p->d == 2 ? 16 : 8, nr = 64 / nc;
-            int best = last, bl = 1 << 30;
-            for (int c = last; c <= std::max(last + 3, last * 5 / 4); ++c) {
-                int load[32] = {0}, mx = 0;
-                for (int r = 0; r < nr; ++r)
-                    for (int k = 0; k < nc; ++k) mx = std::max(mx, ++load[(r * c + k) % 32]);
-                if (mx < bl) {
-                    bl = mx;
-                    best = c;
-                }
-            }
-            return best;
+            const int c = (last + 15) / 16 * 16;
+            return c <= std::max(last + 3, last * 5 / 4) ? c : last;
         };
         // adjoint lists: separable nodes by footprint class in the separable
         // form, up to 15 nodes per axis in 2D (wider footprints add more
@@ -1247,7 +1234,7 @@ fk_status build_plan(fk_plan *p)
                     const int l0 = un ? Lc : std::min(L[0], Lc), l1 = un ? Lc : std::min(L[1], Lc);
                     const int l2 = p->d < 3 ? 0 : (un ? Lc : std::min(L[2], Lc));
                     const int entries = p->d == 2 ? std::max(l0, l1) + 2
-                                                  : std::max(l0, l2) + 2 + (un ? 1 : 2) * (l1 + 2);
+                                                  : std::max(l0, l2) + (un ? 1 : 2) + (un ? 1 : 2) * (l1 + 2);
                     cols = (size_t)entries * fk::adj_threads(p->d, Lc, p->f32) * 2 * (p->f32 ? 4 : 8);
                 }
                 const size_t slack = 16 * elt_b;
@@ -1605,7 +1592,7 @@ void fill_dev(fk_plan *p)
     for (int c = 0; c < fk::kTileClasses; ++c) {
         D.adj.fw_work_off[c] = p->adj.fw_work_off[c];
         D.adj.n_fw_work[c] = p->adj.n_fw_work[c];
-        D.adj.fw_grid[c] = grid_for(p->adj.n_fw_work[c]);
+        D.adj.fw_grid[c] = grid_for(p->adj.n_fw_work[c], 64);
         D.adj.fw_lds[c] = p->adj.fw_lds[c];
     }
     D.adj.box_nodes = (const int *)p->at("abox_nodes");
@@ -1621,7 +1608,7 @@ void fill_dev(fk_plan *p)
     for (int c2 = 0; c2 < fk::kBoxClasses; ++c2) {
         D.adj.box_work_off[c2] = p->adj.box_work_off[c2];
         D.adj.n_box_work[c2] = p->adj.n_box_work[c2];
-        D.adj.box_grid[c2] = grid_for(p->adj.n_box_work[c2]);
+        D.adj.box_grid[c2] = grid_for(p->adj.n_box_work[c2], 64);
         D.adj.box_lds[c2] = p->adj.box_lds[c2];
     }
     D.ent_nodes = (const int *)p->at("ent_nodes");
