@@ -344,8 +344,9 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
 // A whole backward step of a small 2D plan in one launch: a workgroup takes a
 // patch of 256 / GL nodes, builds the records (u, slopes) of the patch and its
 // reach in LDS from u, the (sin, cos) of its coordinates beside them, and then
-// works as k_step_pt2 (GL lanes per node, lane l the axis-1 GH node l), every
-// record read from LDS.  Slopes of a patch's reach are computed by each
+// works as k_step_pt2 (GL lanes per node, lane l the axis-1 GH node l; a lane has
+// one landing position per axis, taken on the coordinates), every record read
+// from LDS.  Slopes of a patch's reach are computed by each
 // workgroup that needs them, which costs less than the launch that would share
 // them as long as the reach is a few patches.
 // Bound: the chain of one workgroup (one item each) and the launch (4 us).
@@ -430,21 +431,13 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     // one landing coordinate: cell (unwrapped, inside the tile), position,
     // squared distance (infinite: exit)
     auto axis = [&](int a, int &k, T &s, double &d2) {
-        const double t = fma_t(gq, I.S * I.inv_h[a], b[a] * P.dt * I.inv_h[a]);
-        int kk = idx[a] + (int)floor(t);
-        if (!I.periodic[a]) kk = min(max(kk, 0), I.n[a] - 2);
-        kk = min(max(kk, tb.lo[a]), tb.lo[a] + tb.ext[a] - 2);
-        s = (T)(t - (double)(kk - idx[a]));
-        k = kk - tb.lo[a];
-        d2 = 0.0;
-        if (!interior) {
-            const double x = (idx[a] == I.n[a] - 1) ? I.hi[a] : (double)idx[a] * I.step[a] + I.lo[a];
-            const double c = x + b[a] * P.dt;
-            const double z = c + I.S * gq;
-            const double dz = z - I.center[a];
-            d2 = ball ? dz * dz : 0.0;
-            if (!I.periodic[a] && (z <= I.lo[a] || z >= I.hi[a])) d2 = HUGE_VAL;
-        }
+        const double x = (idx[a] == I.n[a] - 1) ? I.hi[a] : (double)idx[a] * I.step[a] + I.lo[a];
+        const AxisEval e = eval_axis_affine(I, a, x + b[a] * P.dt, gq);
+        int kk = e.k;
+        if (I.periodic[a]) kk += kk < tb.lo[a] ? I.n[a] - 1 : (kk > tb.lo[a] + tb.ext[a] - 2 ? 1 - I.n[a] : 0);
+        k = min(max(kk, tb.lo[a]), tb.lo[a] + tb.ext[a] - 2) - tb.lo[a];
+        s = (T)e.s;
+        d2 = e.ex ? HUGE_VAL : (ball ? e.dz2 : 0.0);
     };
     int k0, k1;
     T s, v0, v1, f0, f1;

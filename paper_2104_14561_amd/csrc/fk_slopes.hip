@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, 
 // 3D) and the nine slope derivatives of a node.  It was three launches (value,
 // scatter with nine atomic adds per node, fold) which also cleared mu for the
 // next step; the gather of the tiles now stores instead of adding.  129^3 in
-// FP32: 75 us in three launches, 38 now, the gather 41 and 33 us; the FP32 part
+// FP32: 75 us in three launches, 41 now, the gather 41 and 31 us; the FP32 part
 // of the 64-instance batch 49 and 18.5 us.
 template <typename T, int D>
 __global__ void __launch_bounds__(kBlock) k_slopes_T(PlanDev P, int first, int count,
@@ -262,15 +262,23 @@ __global__ void __launch_bounds__(kBlock) k_slopes_T(PlanDev P, int first, int c
                 // FP32 that is exact equality)
                 auto part = [&](T vl, T vc, T vr, T rl, T rr, T m, T &cl, T &cr) {
                     constexpr T tau = T(0x1p-30);
+                    constexpr T tiny = sizeof(T) == 8 ? T(0x1p-1000) : T(0x1p-110f);
                     const T el = vc - vl, er = vr - vc;
                     const T dl = el * rl, dr = er * rr;
                     bool ok = m != T(0) && dl * dr > T(0);
                     if constexpr (sizeof(T) == 8)
                         ok = ok && fabs(el) > tau * (fabs(vc) + fabs(vl)) && fabs(er) > tau * (fabs(vr) + fabs(vc));
-                    const T inv = T(1) / (dl + dr);
-                    const T x = dr * inv, y = dl * inv;
-                    cl = ok ? T(2) * x * x * m * rl : T(0);
-                    cr = ok ? T(2) * y * y * m * rr : T(0);
+                    // as 2 dr^2 / (dl + dr)^2: squares that underflow (a front's far
+                    // tail) count as the quotient of what is left of them
+                    const T den = (dl + dr) * (dl + dr);
+                    const T inv = T(1) / den;
+                    T gl = T(2) * dr * dr * inv, gr = T(2) * dl * dl * inv;
+                    if (ok && den < tiny) {
+                        gl = T(2) * dr * dr / den;
+                        gr = T(2) * dl * dl / den;
+                    }
+                    cl = ok ? gl * (m * rl) : T(0);
+                    cr = ok ? gr * (m * rr) : T(0);
                 };
                 T cl, cr;
                 part(um2, um1, uc, r0, r1, m0, cl, cr);
