@@ -345,27 +345,33 @@ double drift_bound(const fk_problem &pr, int a)
     return (std::fabs(c[2]) + std::fabs(c[1])) * f;
 }
 
-// Exit value of a point (-1: none), the same comparisons as the kernels:
-// faces by the lowest axis, low face first, then the ball (value 1).
-int exit_value(const fk_problem &pr, const double *z)
+// One axis' part of a node's class: the exit value through its faces (-1: none),
+// its square distance from the ball's centre, image of node 0.
+struct NodeCode {
+    double t2;
+    int face, image;
+};
+
+// The codes of axis a, the same comparisons as the kernels: low face first.  A
+// node's value is that of the lowest axis with one, then the ball's (value 1;
+// the squares summed in axis order).
+std::vector<NodeCode> node_codes(const fk_problem &pr, int a)
 {
-    for (int a = 0; a < pr.d; ++a) {
-        if (pr.ax[a].periodic) continue;
+    const fk_axis &ax = pr.ax[a];
+    std::vector<NodeCode> v(ax.n);
+    for (int k = 0; k < ax.n; ++k) {
+        NodeCode &e = v[k];
+        e.image = ax.periodic && k == ax.n - 1 ? 1 : 0;
+        const double z = ax.nodes[e.image ? 0 : k];
+        const double t = z - pr.center[a];
+        e.t2 = t * t;
+        e.face = -1;
+        if (ax.periodic) continue;
         const int fl = pr.face[a][0], fh = pr.face[a][1];
-        if (fl != FK_FACE_REFLECT && z[a] <= pr.ax[a].nodes[0]) return fl == FK_FACE_EXIT0 ? 0 : 1;
-        if (fh != FK_FACE_REFLECT && z[a] >= pr.ax[a].nodes[pr.ax[a].n - 1])
-            return fh == FK_FACE_EXIT0 ? 0 : 1;
+        if (fl != FK_FACE_REFLECT && z <= ax.nodes[0]) e.face = fl == FK_FACE_EXIT0 ? 0 : 1;
+        else if (fh != FK_FACE_REFLECT && z >= ax.nodes[ax.n - 1]) e.face = fh == FK_FACE_EXIT0 ? 0 : 1;
     }
-    if (pr.region_kind == FK_REGION_BALL) {
-        double s = 0.0;
-        for (int a = 0; a < pr.d; ++a) {
-            const double t = z[a] - pr.center[a];
-            const double t2 = t * t;
-            s = s + t2;
-        }
-        if (s >= pr.radius * pr.radius) return 1;
-    }
-    return -1;
+    return v;
 }
 
 // Runaway-electron model (Section 4.3): the time factors (E, nu_ee, v_T,
@@ -556,24 +562,24 @@ void stage_tiles(fk_plan *p)
             const fk_problem &pr = p->probs[work[t].inst];
             long long stride[3] = {1, 1, 1};
             for (int a = d - 2; a >= 0; --a) stride[a] = stride[a + 1] * pr.ax[a + 1].n;
-            const int e0 = tb.ext[0], e1 = d > 1 ? tb.ext[1] : 1, e2 = d > 2 ? tb.ext[2] : 1;
-            int c = 0;
+            auto index = [&](int a, int l) {
+                const int n = pr.ax[a].n;
+                int i = tb.lo[a] + l;
+                if (pr.ax[a].periodic) {
+                    if (i < 0) i += n - 1;
+                    else if (i > n - 1) i -= n - 1;
+                }
+                return i;
+            };
+            const int e0 = d > 1 ? tb.ext[0] : 1, e1 = d > 2 ? tb.ext[1] : 1, el = tb.ext[d - 1];
+            int base = tb.soff;
             for (int l0 = 0; l0 < e0; ++l0)
-                for (int l1 = 0; l1 < e1; ++l1)
-                    for (int l2 = 0; l2 < e2; ++l2, ++c) {
-                        const int l[3] = {l0, l1, l2};
-                        long long node = p->node_off[work[t].inst];
-                        for (int a = 0; a < d; ++a) {
-                            const int n = pr.ax[a].n;
-                            int i = tb.lo[a] + l[a];
-                            if (pr.ax[a].periodic) {
-                                if (i < 0) i += n - 1;
-                                else if (i > n - 1) i -= n - 1;
-                            }
-                            node += (long long)i * stride[a];
-                        }
-                        fn(node, tb.soff + c * NF);
-                    }
+                for (int l1 = 0; l1 < e1; ++l1) {
+                    long long row = p->node_off[work[t].inst];
+                    if (d > 1) row += index(0, l0) * stride[0];
+                    if (d > 2) row += index(1, l1) * stride[1];
+                    for (int l = 0; l < el; ++l, base += NF) fn(row + index(d - 1, l), base);
+                }
         }
     };
     // counting sort by node, then the covered nodes only
@@ -729,33 +735,56 @@ fk_status build_plan(fk_plan *p)
         const bool skip_i = !p->skip.empty() && p->skip[i];
 
         // node classes: 0 active, 1 exit, 2 image of active, 3 image of exit
+        // (an image takes its original's value), row by row along the last axis
         std::vector<unsigned char> c(J);
-        int idx[3];
-        double x[3];
-        for (long long j = 0; j < J; ++j) {
-            long long r = j;
-            for (int a = pr.d - 1; a >= 0; --a) { idx[a] = (int)(r % pr.ax[a].n); r /= pr.ax[a].n; }
-            bool image = false;
-            for (int a = 0; a < pr.d; ++a)
-                if (pr.ax[a].periodic && idx[a] == pr.ax[a].n - 1) { image = true; idx[a] = 0; }
-            for (int a = 0; a < pr.d; ++a) x[a] = pr.ax[a].nodes[idx[a]];
-            const int ev = skip_i ? 1 : exit_value(pr, x);
-            c[j] = (unsigned char)((image ? 2 : 0) | (ev >= 0 ? 1 : 0) | (ev == 0 ? 4 : 0));
-        }
+        std::vector<NodeCode> code[3];
+        for (int a = 0; a < pr.d; ++a) code[a] = node_codes(pr, a);
         int na = 0;
         int amin[3] = {1 << 30, 1 << 30, 1 << 30}, amax_i[3] = {-1, -1, -1};
-        for (long long j = 0; j < J; ++j)
-            if (c[j] == 0) {
-                p->active.push_back((int)j);
-                na++;
-                long long r = j;
-                for (int a = pr.d - 1; a >= 0; --a) {
-                    const int ia = (int)(r % pr.ax[a].n);
-                    r /= pr.ax[a].n;
-                    amin[a] = std::min(amin[a], ia);
-                    amax_i[a] = std::max(amax_i[a], ia);
+        {
+            const int dl = pr.d - 1, nl = pr.ax[dl].n;
+            const bool ball = pr.region_kind == FK_REGION_BALL;
+            const double r2 = pr.radius * pr.radius;
+            int o[3] = {0, 0, 0};   // the row's indices along the other axes
+            for (long long j0 = 0; j0 < J; j0 += nl) {
+                int ev0 = -1, image0 = 0;
+                double s0 = 0.0;
+                for (int a = 0; a < dl; ++a) {
+                    const NodeCode &e = code[a][o[a]];
+                    if (ev0 < 0) ev0 = e.face;
+                    image0 |= e.image;
+                    s0 = s0 + e.t2;
+                }
+                int first = -1, last = -1;
+                for (int k = 0; k < nl; ++k) {
+                    const NodeCode &e = code[dl][k];
+                    int ev = ev0 >= 0 ? ev0 : e.face;
+                    if (ev < 0 && ball && s0 + e.t2 >= r2) ev = 1;
+                    if (skip_i) ev = 1;
+                    const unsigned char cj =
+                        (unsigned char)((image0 | e.image ? 2 : 0) | (ev >= 0 ? 1 : 0) | (ev == 0 ? 4 : 0));
+                    c[j0 + k] = cj;
+                    if (cj == 0) {
+                        p->active.push_back((int)(j0 + k));
+                        ++na;
+                        if (first < 0) first = k;
+                        last = k;
+                    }
+                }
+                if (first >= 0) {
+                    amin[dl] = std::min(amin[dl], first);
+                    amax_i[dl] = std::max(amax_i[dl], last);
+                    for (int a = 0; a < dl; ++a) {
+                        amin[a] = std::min(amin[a], o[a]);
+                        amax_i[a] = std::max(amax_i[a], o[a]);
+                    }
+                }
+                for (int a = dl - 1; a >= 0; --a) {
+                    if (++o[a] < pr.ax[a].n) break;
+                    o[a] = 0;
                 }
             }
+        }
         // trig tables of the drift arguments, one entry per axis coordinate
         if (pr.coef_kind != FK_COEF_CONST && pr.coef_kind != FK_COEF_RUNAWAY3D)
             for (int a = 0; a < pr.d; ++a)
@@ -949,27 +978,39 @@ fk_status build_plan(fk_plan *p)
         auto patch_sort = [&](std::vector<int> &list, const fk_problem &pr,
                               std::vector<long long> &keys, const int *pd = nullptr) {
             if (!pd) pd = kPatch[pr.d - 1];
-            std::vector<std::pair<long long, int>> kv;
-            kv.reserve(list.size());
-            for (int j : list) {
-                long long r = j, key = 0;
-                int ia[3];
-                for (int a = pr.d - 1; a >= 0; --a) {
-                    ia[a] = (int)(r % pr.ax[a].n);
-                    r /= pr.ax[a].n;
-                }
-                for (int a = 0; a < pr.d; ++a) {
-                    const int np = (pr.ax[a].n + pd[a] - 1) / pd[a];
-                    key = key * np + ia[a] / pd[a];
-                }
-                kv.push_back({key * (1LL << 31) + j, j});
+            // counting sort by patch of the ascending list (or of two, one behind
+            // the other)
+            const auto mid = std::is_sorted_until(list.begin(), list.end());
+            if (std::is_sorted(mid, list.end())) std::inplace_merge(list.begin(), mid, list.end());
+            else std::sort(list.begin(), list.end());
+            std::vector<int> part[3];   // an index' share of the patch number
+            int patches = 1;
+            for (int a = pr.d - 1; a >= 0; --a) {
+                part[a].resize(pr.ax[a].n);
+                for (int k = 0; k < pr.ax[a].n; ++k) part[a][k] = k / pd[a] * patches;
+                patches *= (pr.ax[a].n + pd[a] - 1) / pd[a];
             }
-            std::sort(kv.begin(), kv.end());
-            keys.clear();
-            for (size_t t = 0; t < kv.size(); ++t) {
-                list[t] = kv[t].second;
-                keys.push_back(kv[t].first >> 31);
+            std::vector<int> key(list.size()), at((size_t)patches + 1, 0);
+            for (size_t t = 0; t < list.size(); ++t) {
+                unsigned r = (unsigned)list[t];
+                int k = 0;
+                for (int a = pr.d - 1; a > 0; --a) {
+                    const unsigned n = (unsigned)pr.ax[a].n, q = r / n;
+                    k += part[a][r - q * n];
+                    r = q;
+                }
+                key[t] = k + part[0][r];
+                ++at[(size_t)key[t] + 1];
             }
+            for (int k = 0; k < patches; ++k) at[(size_t)k + 1] += at[k];
+            std::vector<int> out(list.size());
+            keys.resize(list.size());
+            for (size_t t = 0; t < list.size(); ++t) {
+                const int s = at[key[t]]++;
+                out[s] = list[t];
+                keys[s] = key[t];
+            }
+            list.swap(out);
         };
         auto patch_work = [&](std::vector<fk::WorkItem> &out, int inst, const std::vector<long long> &keys,
                               int first, int chunk) {
@@ -1164,10 +1205,11 @@ fk_status build_plan(fk_plan *p)
             const fk_problem &pr = p->probs[it.inst];
             int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-1, -1, -1};
             for (int t = 0; t < it.count; ++t) {
-                long long r = list[it.first + t];
+                unsigned r = (unsigned)list[it.first + t];
                 for (int a = pr.d - 1; a >= 0; --a) {
-                    const int ia = (int)(r % pr.ax[a].n);
-                    r /= pr.ax[a].n;
+                    const unsigned n = (unsigned)pr.ax[a].n, q = a > 0 ? r / n : 0u;
+                    const int ia = (int)(r - q * n);
+                    r = q;
                     mn[a] = std::min(mn[a], ia);
                     mx[a] = std::max(mx[a], ia);
                 }
