@@ -88,8 +88,9 @@ enum { FK_COEF_CONST = 0, FK_COEF_CELLULAR2D = 1, FK_COEF_ABC3D = 2, FK_COEF_ROL
  * decides (low face before high face), then the ball.  Plans with a face other
  * than FK_FACE_EXIT1 (and FK_COEF_RUNAWAY3D plans) run the fused form and the
  * forward calls only, in the thread-per-node step layouts (fk_options
- * .step_kernel 0, 1 or 3; 4 falls back to 1) or the lane-group one (2, and
- * with FK_HERMITE_R2). */
+ * .step_kernel 0, 1 or 3; 4 falls back to 1), in 3D box regions the separable
+ * step over shared entries where that reads fewer records, or the lane-group
+ * one (2, and with FK_HERMITE_R2). */
 enum { FK_FACE_EXIT1 = 0, FK_FACE_EXIT0 = 1, FK_FACE_REFLECT = 2 };
 
 /* Exit region (paper Section 2: D is an open box; a disc or ball target, such
@@ -115,9 +116,9 @@ enum { FK_PREC_F64 = 0, FK_PREC_F32 = 1 };
  * In 3D the four twist fields (axis sets {0,1}, {0,2}, {1,2}, {0,1,2}) sit in
  * a second record per node in the workspace.  R2 is built for d = 1 (the
  * same as R1), 2 and 3, the fused form and the forward pass (fk_forward,
- * fk_forward_from, fk_step, fk_forward_horizons); in 3D with the
- * thread-per-node step only (fk_options.step_kernel 0, 1 or 3; a gh_q with
- * such a kernel compiled) and exit-1 faces.  Other combinations are
+ * fk_forward_from, fk_step, fk_forward_horizons); in 3D with
+ * fk_options.step_kernel 0, 1 or 3 only (a gh_q with a thread-per-node
+ * kernel compiled) and exit-1 faces.  Other combinations are
  * FK_ERR_UNSUPPORTED. */
 enum { FK_HERMITE_R1 = 0, FK_HERMITE_R2 = 1 };
 
@@ -168,16 +169,19 @@ typedef struct {
                         2 = a lane group per node over the tensor points (any gh_q);
                         3 = Q* lanes per node over the outermost axis;
                         4 = separable box form for nodes whose landing points
-                        cannot reach a ball boundary (footprint up to 8 nodes
-                        per axis; d >= 2 on affine axes), one thread per node
-                        for the others.  1, 3 and 4 exist for d=1: gh_q
-                        2..8,10,12,16; d=2: 2..8; d=3: 2..6
-                        (FK_ERR_UNSUPPORTED otherwise).  auto picks 4 for 3D
-                        plans with many active nodes, 1 for other large plans,
-                        3 for small ones, 2 when the others are not compiled
-                        for gh_q; fk_tune measures them instead.  Plans with
-                        faces other than exit-1 (or the runaway model) take 4
-                        as 1, and with FK_HERMITE_R2 always run 2 */
+                        cannot reach a ball boundary (footprint up to 15 nodes
+                        per axis in 2D, 12 in 3D; d >= 2 on affine axes), per
+                        landing point for the others.  1, 3 and 4 exist for
+                        d=1: gh_q 2..8,10,12,16; d=2: 2..8; d=3: 2..6
+                        (FK_ERR_UNSUPPORTED otherwise).  auto picks 4 for 2D
+                        and 3D plans with many active nodes, 1 for other large
+                        plans, 3 for small ones (2D: the whole step in one
+                        launch where its records fit the LDS; 1D on an affine
+                        axis of up to 4096 nodes: many steps in one launch), 2
+                        when the others are not compiled for gh_q; fk_tune
+                        measures them instead.  Plans with faces other than
+                        exit-1 (or the runaway model) take 4 as 1, and with
+                        FK_HERMITE_R2 always run 2 */
     int columns;     /* fk_forward_horizons: most columns one launch of the
                         FK_FORM_ELL product takes (1..4; 0 = 1); the workspace
                         holds that many record planes */

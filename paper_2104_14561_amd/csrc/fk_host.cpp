@@ -191,6 +191,11 @@ struct fk_plan {
     std::vector<fk::WorkItem> small_work;
     std::vector<fk::TileBox> small_tiles;
     int small_lds = 0;
+    // periodic plans whose own passes take a separable or one-launch form: a
+    // field that a caller hands in may hold other values on the image nodes than
+    // on their originals, which those forms read interchangeably, so it takes
+    // the per-point form for its step (fw lists of every node beside the box ones)
+    bool periodic = false, dual = false;
     bool pt_groups = false;   // 2D landing points by lane groups (k_step_pt2)
     // 3D plans in entry form (faces, axes that are not affine; box region)
     std::vector<int> ent_nodes;
@@ -216,6 +221,8 @@ struct fk_plan {
     std::map<std::string, Region> reg;
     size_t ws_bytes = 0;
     size_t ws_fwd_bytes = 0;   // prefix of the workspace that a forward pass uses
+    size_t ws_opt_bytes = 0;   // of it, lists and tables of the specialised steps (beside the common ones)
+    size_t n_coords = 0;       // axis coordinates at the head of coords, bucket tables behind them
     unsigned char *ws = nullptr;
     fk::PlanDev dev{};
     // graph cache
@@ -922,6 +929,7 @@ fk_status build_plan(fk_plan *p)
         }
     }
     p->node_off[p->n_inst] = p->n_nodes;
+    p->n_coords = p->coords.size();
     // bucket tables of the axes that are not uniform, behind the coordinates:
     // per bucket of the smallest spacing the largest node at or below its start
     for (int i = 0; i < p->n_inst; ++i)
@@ -932,7 +940,7 @@ fk_status build_plan(fk_plan *p)
             double hmin = 1e300;
             for (int k = 1; k < ax.n; ++k) hmin = std::min(hmin, ax.nodes[k] - ax.nodes[k - 1]);
             const double nb = std::ceil((ax.nodes[ax.n - 1] - ax.nodes[0]) / hmin) + 1.0;
-            if (!(nb <= 65536.0)) continue;
+            if (!(nb <= std::min(16.0 * ax.n, 65536.0))) continue;   // bisection
             I.lut_n[a] = (int)nb;
             I.lut_inv[a] = 1.0 / hmin;
             I.lut_off[a] = (long long)p->coords.size();
@@ -957,9 +965,47 @@ fk_status build_plan(fk_plan *p)
         else if (sk == 3 || (sk == 0 && !large)) p->step_kind = 2;
         else p->step_kind = 0;
         // the separable form by default: a node's Q*^d points gather 2^d
-        // corners each, against the product of its footprint's lengths
+        // corners each, against the product of its footprint's lengths.  In 3D
+        // also for small plans, where Q* lanes per node took (per step, slopes
+        // included, FP32) 18.6 against 12.3 us at 9^3, Q* = 4, 57 against 13.4 at
+        // 33^3, Q* = 6, 149 against 15 at 49^3, and 19.3 against 19.4 at worst
+        // (17^3, Q* = 4, 9-node footprints).  In 2D a step in one launch is better
+        // until its points cost more than the second launch: per million points
+        // 1.6 us in FP32, 3.0 in FP64, per million footprint records 1.1 and 2.4
+        // (257 x 129, Q* = 8, FP64: 11.4 against 10.0 us with 3-node footprints, 12.5
+        // against 14.7 with 7; 361^2: 30.6 against 14.7 and 32 against 22; 361^2,
+        // Q* = 4: 14.1 against 11.4, where the rule still takes the one launch)
+        bool sep2d = false;
+        if (p->d == 2 && sk == 0 && !large) {
+            double gain = 0.0;
+            bool rest = false;
+            for (int i = 0; i < p->n_inst; ++i) {
+                rest = rest || !inst_rest[i].empty() || (inst_cls[i] < 0 && !inst_sep[i].empty());
+                if (inst_cls[i] < 0) continue;
+                const double points = (p->f32 ? 1.6 : 3.0) * p->qs * p->qs;
+                const double records = (p->f32 ? 1.1 : 2.4) * p->inst[i].sep_l[0] * p->inst[i].sep_l[1];
+                gain += 1e-6 * (double)inst_sep[i].size() * (points - records);
+            }
+            sep2d = gain > (rest ? 9.0 : 4.5);
+        }
         p->use_box = node_ok && affine && !p->faces && fk::box_compiled(p->d, p->qs) &&
-                     (sk == 4 || (sk == 0 && large));
+                     (sk == 4 || (sk == 0 && (large || sep2d || p->d == 3)));
+        bool all_sep = true;
+        for (int i = 0; i < p->n_inst; ++i) {
+            all_sep = all_sep && inst_rest[i].empty() && (inst_cls[i] >= 0 || inst_sep[i].empty());
+            for (int a = 0; a < p->d; ++a) p->periodic = p->periodic || p->probs[i].ax[a].periodic != 0;
+        }
+        int lmax = 0;
+        for (const fk::DevInst &I : p->inst)
+            for (int a = 0; a < p->d; ++a) lmax = std::max(lmax, I.sep_l[a]);
+        // (a caller who asks for the box form, and large 3D plans of narrow
+        // footprints, always read image nodes as their originals)
+        const bool reads_images = p->opt.hermite == FK_HERMITE_R1 &&
+                                  ((sk == 4 && lmax <= 8) || (sk == 0 && p->d == 3 && large && lmax <= 5));
+        if (p->use_box && p->periodic && !reads_images) {
+            if (all_sep) p->dual = true;
+            else p->use_box = false;
+        }
         // 1D: one workgroup takes an instance through many steps when its axis
         // fits the LDS (measured on 201 nodes, Q* = 16, FP64: 16 us per step in
         // two launches, 0.9 us inside one)
@@ -1038,16 +1084,16 @@ fk_status build_plan(fk_plan *p)
             long long points = 0;
             for (int i = 0; i < p->n_inst; ++i)
                 points += (long long)inst_rest[i].size() +
-                          (!p->use_box || inst_cls[i] < 0 ? (long long)inst_sep[i].size() : 0);
+                          (!p->use_box || inst_cls[i] < 0 || p->dual ? (long long)inst_sep[i].size() : 0);
             const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
             p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && (p->step_kind != 0 || points < most);
         }
         for (int i = 0; i < p->n_inst; ++i) {
             const fk_problem &pr = p->probs[i];
             std::vector<int> fw = inst_rest[i];
-            if (!p->use_box || inst_cls[i] < 0) {
+            if (!p->use_box || inst_cls[i] < 0 || p->dual)
                 fw.insert(fw.end(), inst_sep[i].begin(), inst_sep[i].end());
-            } else {
+            if (p->use_box && inst_cls[i] >= 0) {
                 std::vector<int> sep = inst_sep[i];
                 patch_sort(sep, pr, keys);
                 const int f0 = (int)p->box_nodes.size();
@@ -1128,6 +1174,10 @@ fk_status build_plan(fk_plan *p)
                 p->ent_nodes.insert(p->ent_nodes.end(), list.begin(), list.end());
                 build_work(p->ent_work, i, (int)list.size(), kBlock, f0);
             }
+            // nothing else walks the point lists then
+            p->fw_nodes.clear();
+            p->fw_work.clear();
+            p->fw_split_work.clear();
             for (const fk_problem &pr : p->probs)
                 if (pr.coef_kind == FK_COEF_RUNAWAY3D) {
                     p->retab = true;
@@ -1138,7 +1188,7 @@ fk_status build_plan(fk_plan *p)
         // its reach (at most 1024) are few enough to be computed by every
         // workgroup that reads them (513 x 257: 140 records for 32 nodes; one launch
         // of 7.4 us against 15.6 us in two)
-        if (p->d == 2 && p->step_kind == 2 && node_ok && affine && !p->wraps && !p->faces &&
+        if (p->d == 2 && p->step_kind == 2 && !p->use_box && node_ok && affine && !p->wraps && !p->faces &&
             p->opt.form == FK_FORM_FUSED && p->n_active > 0) {
             int pd[3] = {1, 1, 1};
             fk::small_patch(p->qs, &pd[0], &pd[1]);
@@ -1526,7 +1576,7 @@ fk_status build_plan(fk_plan *p)
     add_region(p, "gh_w1", sizeof(double) * p->gh_w1.size());
     add_region(p, "gh_w1f", sizeof(float) * p->gh_w1f.size());
     add_region(p, "tfac", sizeof(double) * p->tfac.size());
-    add_region(p, "trig", sizeof(double) * 2 * std::max<size_t>(p->coords.size(), 1));
+    add_region(p, "trig", sizeof(double) * 2 * std::max<size_t>(p->n_coords, 1));
     add_region(p, "slope_work", sizeof(fk::WorkItem) * std::max<size_t>(p->slope_work.size(), 1));
     add_region(p, "node_work", sizeof(fk::WorkItem) * std::max<size_t>(p->node_work.size(), 1));
     add_region(p, "act_work", sizeof(fk::WorkItem) * std::max<size_t>(p->act_work.size(), 1));
@@ -1540,17 +1590,25 @@ fk_status build_plan(fk_plan *p)
     add_region(p, "abox_nodes", sizeof(int) * std::max<size_t>(p->adj.box_nodes.size(), 1));
     add_region(p, "abox_work", sizeof(fk::WorkItem) * std::max<size_t>(p->adj.box_work.size(), 1));
     add_region(p, "abox_tiles", sizeof(fk::TileBox) * std::max<size_t>(p->adj.box_tiles.size(), 1));
+    const size_t opt0 = p->ws_bytes;
     add_region(p, "ent_nodes", sizeof(int) * std::max<size_t>(p->ent_nodes.size(), 1));
     add_region(p, "ent_work", sizeof(fk::WorkItem) * std::max<size_t>(p->ent_work.size(), 1));
-    add_region(p, "retab", p->retab ? sizeof(double) * fk::kReTab * p->coords.size() : 0);
+    add_region(p, "retab", p->retab ? sizeof(double) * fk::kReTab * p->n_coords : 0);
     add_region(p, "small_nodes", sizeof(int) * std::max<size_t>(p->small_nodes.size(), 1));
     add_region(p, "small_work", sizeof(fk::WorkItem) * std::max<size_t>(p->small_work.size(), 1));
     add_region(p, "small_tiles", sizeof(fk::TileBox) * std::max<size_t>(p->small_tiles.size(), 1));
+    if (p->dual) {
+        add_region(p, "box_nodes", sizeof(int) * std::max<size_t>(p->box_nodes.size(), 1));
+        add_region(p, "box_work", sizeof(fk::WorkItem) * std::max<size_t>(p->box_work.size(), 1));
+    }
+    p->ws_opt_bytes = p->ws_bytes - opt0 + sizeof(double) * (p->coords.size() - p->n_coords);
     add_region(p, "fw_nodes", sizeof(int) * std::max<size_t>(p->fw_nodes.size(), 1));
     add_region(p, "fw_work", sizeof(fk::WorkItem) * std::max<size_t>(p->fw_work.size(), 1));
     add_region(p, "fw_split_work", sizeof(fk::WorkItem) * std::max<size_t>(p->fw_split_work.size(), 1));
-    add_region(p, "box_nodes", sizeof(int) * std::max<size_t>(p->box_nodes.size(), 1));
-    add_region(p, "box_work", sizeof(fk::WorkItem) * std::max<size_t>(p->box_work.size(), 1));
+    if (!p->dual) {
+        add_region(p, "box_nodes", sizeof(int) * std::max<size_t>(p->box_nodes.size(), 1));
+        add_region(p, "box_work", sizeof(fk::WorkItem) * std::max<size_t>(p->box_work.size(), 1));
+    }
     add_region(p, "flags", 64);
     const size_t fb = elt(p) * (size_t)p->n_nodes;
     add_region(p, "uA", fb);
@@ -1737,9 +1795,20 @@ fk_status need_ws(const fk_plan *p)
     } while (0)
 
 // One step u_next -> u_out, two fields (u_out must hold 1 on exit nodes already).
-fk_status enqueue_step(fk_plan *p, int n, const void *u_next, void *u_out, hipStream_t s)
+// The step's lists for a field of the plan's own (image nodes hold their
+// originals' values) or for a caller's.
+fk::PlanDev step_dev(const fk_plan *p, bool own)
 {
-    if (p->dev.n_small_work > 0) {
+    fk::PlanDev D = p->dev;
+    if (p->dual && own) D.n_fw_work = D.n_fw_split_work = 0;
+    if (p->dual && !own)
+        for (int c = 0; c < fk::kBoxClasses; ++c) D.n_box_work[c] = 0;
+    return D;
+}
+
+fk_status enqueue_step(fk_plan *p, int n, const void *u_next, void *u_out, hipStream_t s, bool own)
+{
+    if (p->dev.n_small_work > 0 && (own || !p->periodic)) {
         FK_LAUNCH(fk::launch_step_small2(p->dev, p->f32, n, u_next, u_out, s));
         return FK_OK;
     }
@@ -1751,7 +1820,7 @@ fk_status enqueue_step(fk_plan *p, int n, const void *u_next, void *u_out, hipSt
         FK_LAUNCH(fk::launch_assemble_ell(p->dev, p->f32, n, cols, vals, em, s));
         FK_LAUNCH(fk::launch_ell_apply(p->dev, p->f32, cols, vals, em, packed, u_out, s));
     } else {
-        FK_LAUNCH(fk::launch_step_fused(p->dev, p->f32, n, packed, u_out, s));
+        FK_LAUNCH(fk::launch_step_fused(step_dev(p, own), p->f32, n, packed, u_out, s));
     }
     return FK_OK;
 }
@@ -1841,7 +1910,7 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
     for (int n = start - 1; n >= 0; --n) {
         void *dst = slot_of(n);
         if (!dst) dst = (cur == ua) ? ub : ua;
-        FK_TRY(enqueue_step(p, n, cur, dst, s));
+        FK_TRY(enqueue_step(p, n, cur, dst, s, !u_start || n < start - 1));
         cur = dst;
         FK_TRY(snap_copy(n, cur));
     }
@@ -1921,7 +1990,7 @@ fk_status enqueue_horizons(fk_plan *p, const int *hz, int n_h, void *u_out, hipS
         if (!ell) {
             for (size_t k = first; k < order.size(); ++k) {
                 FK_LAUNCH(fk::launch_slopes(p->dev, p->f32, step, col(order[k]), packed, s));
-                FK_LAUNCH(fk::launch_step_fused(p->dev, p->f32, step, packed, col(order[k]), s));
+                FK_LAUNCH(fk::launch_step_fused(step_dev(p, true), p->f32, step, packed, col(order[k]), s));
             }
             continue;
         }
@@ -2172,7 +2241,9 @@ fk_status fk_forward_static(fk_plan *p, const int *snap_steps, int n_snap, void 
     if (!p) return fail(FK_ERR_ARG, "null plan");
     FK_TRY(check_snaps(p, snap_steps, n_snap, p->N, u_out));
     if (p->sub) return fail(FK_ERR_UNSUPPORTED, "plans with instances forced to FP64");
-    if (p->ws_fwd_bytes > (size_t)FK_STATIC_SCRATCH_BYTES)
+    // the array holds the specialised steps' lists beside the documented size
+    if (p->ws_fwd_bytes - p->ws_opt_bytes > (size_t)FK_STATIC_SCRATCH_BYTES ||
+        p->ws_fwd_bytes > (size_t)FK_STATIC_SCRATCH_BYTES + fk::kScratchExtra)
         return fail(FK_ERR_WORKSPACE,
                     "plan needs %zu bytes of forward workspace, the static scratch holds %zu",
                     p->ws_fwd_bytes, (size_t)FK_STATIC_SCRATCH_BYTES);
@@ -2302,12 +2373,12 @@ fk_status fk_step(fk_plan *p, int n, const void *u_next, void *u_out, void *stre
     if (n < 0 || n >= p->N) return fail(FK_ERR_ARG, "step %d outside [0, N-1]", n);
     hipStream_t s = (hipStream_t)stream;
     FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, u_out, s));
-    FK_TRY(enqueue_step(p, n, u_next, u_out, s));
+    FK_TRY(enqueue_step(p, n, u_next, u_out, s, false));
     if (fk_plan *c = p->sub) {
         double *ua = (double *)c->at("uA"), *ub = (double *)c->at("uB");
         FK_LAUNCH(fk::launch_convert_in(c->dev, (const float *)u_next, ua, s));
         FK_LAUNCH(fk::launch_init_field(c->dev, false, ub, s));
-        FK_TRY(enqueue_step(c, n, ua, ub, s));
+        FK_TRY(enqueue_step(c, n, ua, ub, s, false));
         FK_LAUNCH(fk::launch_convert_out(c->dev, ub, (float *)u_out, s));
     }
     return FK_OK;
@@ -2334,7 +2405,7 @@ fk_status fk_apply_step(fk_plan *p, int n, int transpose, const void *x, void *y
             FK_LAUNCH(fk::launch_assemble_ell(p->dev, p->f32, n, cols, vals, em, s));
             FK_LAUNCH(fk::launch_ell_apply(p->dev, p->f32, cols, vals, em, packed, out, s));
         } else {
-            FK_LAUNCH(fk::launch_step_fused(p->dev, p->f32, n, packed, out, s));
+            FK_LAUNCH(fk::launch_step_fused(step_dev(p, false), p->f32, n, packed, out, s));
         }
         return FK_OK;
     };
@@ -2473,7 +2544,7 @@ fk_status fk_adjoint(fk_plan *p, const void *lam0, double *grad, void *lamN, voi
             void *dst = seg + (size_t)(m - n0 - 1) * fb;
             FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, dst, s));
             FK_TRY(prof_mark(p, -1, s));
-            FK_TRY(enqueue_step(p, m, field(m + 1), dst, s));
+            FK_TRY(enqueue_step(p, m, field(m + 1), dst, s, true));
             FK_TRY(prof_mark(p, 3, s));
         }
         for (int n = n0; n < n1; ++n) {
@@ -2542,7 +2613,7 @@ fk_status fk_profile_pass(fk_plan *p, double *ms, int *counts, void *stream)
             FK_LAUNCH(fk::launch_ell_apply(p->dev, p->f32, cols, vals, em, packed, nxt, s));
             FK_TRY(rec(3));
         } else {
-            FK_LAUNCH(fk::launch_step_fused(p->dev, p->f32, n, packed, nxt, s));
+            FK_LAUNCH(fk::launch_step_fused(step_dev(p, true), p->f32, n, packed, nxt, s));
             FK_TRY(rec(1));
         }
         std::swap(cur, nxt);

@@ -254,6 +254,9 @@ hipError_t launch_slopes(const PlanDev &P, bool f32, int n, const void *u, void 
 hipError_t launch_slopes_mc(const PlanDev &P, bool f32, int n, const void *u, long long ustride,
                             void *packed, long long pstride, int nc, hipStream_t s);
 hipError_t launch_tables(const PlanDev &P, int n, hipStream_t s);
+// room of the static scratch beside FK_STATIC_SCRATCH_BYTES (lists of small and
+// 3D entry-form plans: at most 64 bytes per node of up to 131 thousand)
+constexpr size_t kScratchExtra = 8u << 20;
 constexpr int kReTab = 8;   // runaway model: tabulated values per coordinate
 // the runaway model's per-coordinate tables at step n (P.retab)
 hipError_t launch_runaway_tables(const PlanDev &P, int n, hipStream_t s);

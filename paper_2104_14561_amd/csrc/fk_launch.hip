@@ -16,7 +16,7 @@ namespace fk {
 // array's name as an address: the device address comes from
 // hipGetSymbolAddress, taken once per device with that device current.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[FK_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[FK_STATIC_SCRATCH_BYTES + kScratchExtra];
 
 hipError_t static_scratch(void **out)
 {

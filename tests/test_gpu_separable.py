@@ -71,9 +71,13 @@ def _check_step(p, prec, kernel, hermite="r1"):
     ref = oracle.step(p.replace(hermite=hermite), 1, u)
     plan = Plan(p, precision=prec, step_kernel=kernel, hermite=hermite)
     got = plan.split(plan.step(1, torch.from_numpy(u.reshape(-1))))[0].double().cpu().numpy()
+    own = plan.split(plan.forward([0]))[0].double().cpu().numpy()[0]
     assert plan.check_flags() == 0
     plan.close()
     err = np.abs(got - ref).max()
+    assert err <= BAR[prec], err
+    # periodic plans take a caller's field per point and their own as the class says
+    err = np.abs(own - oracle.solve(p.replace(hermite=hermite), snaps=[0])[0]).max()
     assert err <= BAR[prec], err
 
 
@@ -104,6 +108,22 @@ def test_one_launch_step_2d(region, L, q, prec):
     takes, the two-launch step runs."""
     p = _rolls(L, q) if region == "periodic" else _flow2d(L, region, q)
     _check_step(p, prec, "auto")
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("hermite", ["r1", "r2"])
+@pytest.mark.parametrize("name", ["rolls", "abc", "abc_wide"])
+def test_caller_fields_with_other_values_on_image_nodes(name, hermite, prec):
+    """A caller's field is read node by node: its image nodes need not hold
+    their originals' values."""
+    p = {"rolls": _rolls(6), "abc": _abc(4, n=19), "abc_wide": _abc(7, n=23)}[name]
+    u = W.random_field(p.shape, 9)
+    ref = oracle.step(p.replace(hermite=hermite), 1, u)
+    plan = Plan(p, precision=prec, hermite=hermite)
+    got = plan.split(plan.step(1, torch.from_numpy(u.reshape(-1))))[0].double().cpu().numpy()
+    frm = plan.split(plan.forward_from(torch.from_numpy(u.reshape(-1)), 2, [1]))[0].double().cpu().numpy()[0]
+    plan.close()
+    assert np.abs(got - ref).max() <= BAR[prec] and np.abs(frm - ref).max() <= BAR[prec]
 
 
 @pytest.mark.parametrize("q", [4, 7])
