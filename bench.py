@@ -109,7 +109,8 @@ def ell_roofline(plan, ms_apply: float):
 def kernel_sources_hash() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("fk_device.h", "fk_node_inst.hip", "fk_launch.hip", "fk_internal.h", "fk_host.cpp"):
+    for f in ("fk_device.h", "fk_sep.h", "fk_adj_sep.h", "fk_slopes.hip", "fk_line.hip", "fk_small.hip",
+              "fk_ent.hip", "fk_node_inst.hip", "fk_launch.hip", "fk_internal.h", "fk_host.cpp"):
         with open(os.path.join(ROOT, "paper_2104_14561_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -493,7 +494,7 @@ def main():
     if t_adj_kernel >= t_step_kernel:
         ms_k = prof_a["adjoint_step"][0]
         roof = scope_roofline(d, Q, n_point, ms_k, ADJOINT_FACTOR, plan.precision,
-                              "k_adjoint_node (transposed step, nodes handled per landing point)")
+                              "k_adjoint_pt2 (transposed step, nodes handled per landing point)")
         bf = builder_adjoint_flops(d, qs)
         roof["builder_count"] = {
             "flops_per_active_node": bf,
@@ -511,14 +512,16 @@ def main():
             "frac": round(rate / peak, 4),
             "note": "lane-level ds_add_f64; peak from fk_probe_lds_atomics (2048 x 256 lanes, "
                     "conflict-free) on this device, this run"}
-        # interior work items (no exit tests) and the rest: one launch each
-        kname = ["void k_adjoint_node<float, 2, 8, true, true>",
-                 "void k_adjoint_node<float, 2, 8, true, false>"]
+        # one launch per class of tile bytes
+        kname = "void k_adjoint_pt2<float, 8>"
         share = t_adj_kernel / ms_step
     else:
         ms_k = prof_f["step_fused"][0]
-        roof = scope_roofline(d, Q, Ja, ms_k, 1, plan.precision, "k_step_node (fused step)")
-        kname = "void k_step_node<float, 2, 8, 1, true, false, false>"
+        roof = scope_roofline(d, Q, Ja, ms_k, 1, plan.precision,
+                              "k_step_sep2 and k_step_pt2 (fused step: separable nodes by footprint class, "
+                              "the others per landing point)")
+        kname = [f"void k_step_sep2<float, 8, {n}, 256, false>" for n in (6, 9, 12, 15)] + [
+            "void k_step_pt2<float, 8, false>"]
         share = t_step_kernel / ms_step
     roof["traffic"] = measured_traffic(kname)
     roof["share_of_step"] = round(share, 4)
