@@ -1241,8 +1241,7 @@ fk_status build_plan(fk_plan *p)
             p->small_lds = cells_max * 4 * (p->f32 ? 4 : 8);
         }
         // adjoint LDS tiles: node box of each work item widened by the reach,
-        // d + 1 field planes, innermost axis padded to a pitch that puts the
-        // rows of a wave's patch (16 nodes in 2D, 8 in 3D) on distinct banks
+        // d + 1 field planes, innermost axis padded to pitch_wave's pitch
         const int NF = p->d + 1;
         const size_t elt_b = 8;   // tiles accumulate in FP64 in both precisions
         const size_t budget = 60 * 1024;   // plus static LDS, within 64 KB per workgroup
