@@ -115,10 +115,10 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep2(
             drift<D>(I, tf, trig, idx, b);
             const double b0 = b[0] * P.dt, b1 = b[1] * P.dt;
             int o0, o1;
-            T m;
+            T m, mx;
             T V1[L], S1[L], A1[L], B1[L];
-            if (interior) sep_vectors<T, QS, BS, false>(I, 1, idx[1], b1, L1, ga, w1, col, o1, m);
-            else sep_vectors<T, QS, BS, true>(I, 1, idx[1], b1, L1, ga, w1, col, o1, m);
+            if (interior) sep_vectors<T, QS, BS, false>(I, 1, idx[1], b1, L1, ga, w1, col, o1, m, mx);
+            else sep_vectors<T, QS, BS, true>(I, 1, idx[1], b1, L1, ga, w1, col, o1, m, mx);
             const T h0 = (T)I.step[0], h1 = (T)I.step[1];
 #pragma unroll
             for (int j = 0; j < L; ++j) {
@@ -129,8 +129,8 @@ __global__ void __launch_bounds__(BS) k_adjoint_sep2(
                     S1[j] = e.y * h1;
                 }
             }
-            if (interior) sep_vectors<T, QS, BS, false>(I, 0, idx[0], b0, L0, ga, w1, col, o0, m);
-            else sep_vectors<T, QS, BS, true>(I, 0, idx[0], b0, L0, ga, w1, col, o0, m);
+            if (interior) sep_vectors<T, QS, BS, false>(I, 0, idx[0], b0, L0, ga, w1, col, o0, m, mx);
+            else sep_vectors<T, QS, BS, true>(I, 0, idx[0], b0, L0, ga, w1, col, o0, m, mx);
             const int s0 = (int)I.stride[0], n0 = I.n[0], n1 = I.n[1];
             const int per0 = I.periodic[0], per1 = I.periodic[1];
             const int tr0 = o0 - tile.lo[0], tc0 = o1 - tile.lo[1];
@@ -445,14 +445,14 @@ __global__ void __launch_bounds__(BS, (sizeof(T) == 4 && L == 3) ? 4 : 1) k_adjo
             drift<D>(I, tf, trig, idx, b);
             const double bd[3] = {b[0] * P.dt, b[1] * P.dt, b[2] * P.dt};
             int o0, o1, o2;
-            T m;
+            T m, mx;
             T V2_[L], S2_[L], A2[L], B2[L];
             T A1[UN ? L : 1], B1[UN ? L : 1];
             auto vectors = [&](int a, int La, V2 *col, int &o) {
                 if (interior || I.periodic[a])
-                    sep_vectors<T, QS, BS, false>(I, a, idx[a], bd[a], La, ga, w1, col, o, m);
+                    sep_vectors<T, QS, BS, false>(I, a, idx[a], bd[a], La, ga, w1, col, o, m, mx);
                 else
-                    sep_vectors<T, QS, BS, true>(I, a, idx[a], bd[a], La, ga, w1, col, o, m);
+                    sep_vectors<T, QS, BS, true>(I, a, idx[a], bd[a], La, ga, w1, col, o, m, mx);
             };
             auto gradient = [&](int a, const V2 *col, T &G, T &H) {
                 if (interior || I.periodic[a])

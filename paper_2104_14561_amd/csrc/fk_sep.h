@@ -48,11 +48,13 @@ __device__ inline void unit_basis(T s, T &v0, T &v1, T &d0, T &d1)
 // nodes and the subtraction from the cell's node take some twenty, and its
 // rounding is relative to the few cells of the displacement instead of the
 // axis' length.  Exits on a non-periodic axis are decided on the coordinate
-// z = c + S a_q itself (every product rounded, as everywhere).
+// z = c + S a_q itself (every product rounded, as everywhere); m and x are the
+// weights inside and outside (EX), summed apart: the exit mass as a difference
+// from the sum of all weights would carry that sum's rounding.
 template <typename T, int QS, int BS, bool EX>
 __device__ inline void sep_vectors(const DevInst &I, int a, int idx, double bdt, int L,
                                    const double *__restrict__ ga, const T *__restrict__ w1,
-                                   typename Vec2T<T>::type *col, int &o, T &m)
+                                   typename Vec2T<T>::type *col, int &o, T &m, T &x)
 {
 #pragma clang fp contract(off)
     using V2 = typename Vec2T<T>::type;
@@ -72,7 +74,7 @@ __device__ inline void sep_vectors(const DevInst &I, int a, int idx, double bdt,
     z.x = T(0);
     z.y = T(0);
     for (int j = -1; j <= L; ++j) col[j * BS] = z;
-    m = T(0);
+    m = x = T(0);
 #pragma unroll
     for (int q = 0; q < QS; ++q) {
         const double t = fma_t(ga[q], sh, br);
@@ -82,7 +84,10 @@ __device__ inline void sep_vectors(const DevInst &I, int a, int idx, double bdt,
         T w = w1[q];
         if constexpr (EX) {
             const double zq = c + I.S * ga[q];
-            if (!per && (zq <= lo || zq >= hi)) w = T(0);
+            if (!per && (zq <= lo || zq >= hi)) {
+                x += w;
+                w = T(0);
+            }
             m += w;
         }
         T v0, v1, d0, d1;
@@ -150,10 +155,10 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
         const bool interior = it.kind == 1;   // host: no landing point can exit
         const int L0 = min(I.sep_l[0], L), L1 = min(I.sep_l[1], L);
         int o0, o1;
-        T m0, m1, emass = T(0);
+        T m0, m1, x0, x1, emass = T(0);
         T V1[L], S1[L];
-        if (interior) sep_vectors<T, QS, BS, false>(I, 1, idx[1], b[1] * P.dt, L1, ga, w1, col, o1, m1);
-        else sep_vectors<T, QS, BS, true>(I, 1, idx[1], b[1] * P.dt, L1, ga, w1, col, o1, m1);
+        if (interior) sep_vectors<T, QS, BS, false>(I, 1, idx[1], b[1] * P.dt, L1, ga, w1, col, o1, m1, x1);
+        else sep_vectors<T, QS, BS, true>(I, 1, idx[1], b[1] * P.dt, L1, ga, w1, col, o1, m1, x1);
         const T h0 = (T)I.step[0], h1 = (T)I.step[1];
 #pragma unroll
         for (int j = 0; j < L; ++j) {
@@ -166,10 +171,10 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
             }
         }
         if (interior) {
-            sep_vectors<T, QS, BS, false>(I, 0, idx[0], b[0] * P.dt, L0, ga, w1, col, o0, m0);
+            sep_vectors<T, QS, BS, false>(I, 0, idx[0], b[0] * P.dt, L0, ga, w1, col, o0, m0, x0);
         } else {
-            sep_vectors<T, QS, BS, true>(I, 0, idx[0], b[0] * P.dt, L0, ga, w1, col, o0, m0);
-            emass = wsum * wsum - m0 * m1;
+            sep_vectors<T, QS, BS, true>(I, 0, idx[0], b[0] * P.dt, L0, ga, w1, col, o0, m0, x0);
+            emass = x0 * wsum + m0 * x1;
         }
         const int s0 = (int)I.stride[0], n0 = I.n[0], n1 = I.n[1];
         const int per0 = I.periodic[0], per1 = I.periodic[1];
@@ -536,16 +541,16 @@ __global__ void __launch_bounds__(BS) k_step_sep3(
         const int L0 = UN ? L : min(I.sep_l[0], L), L1 = UN ? L : min(I.sep_l[1], L);
         const int L2 = UN ? L : min(I.sep_l[2], L);
         int o0, o1, o2;
-        T m0, m1, m2, emass = T(0);
+        T m0, m1, m2, x0, x1, x2, emass = T(0);
         T V2_[L], S2_[L];
-        auto vectors = [&](int a, int La, V2 *col, int &o, T &m) {
+        auto vectors = [&](int a, int La, V2 *col, int &o, T &m, T &x) {
             if (interior || I.periodic[a])
-                sep_vectors<T, QS, BS, false>(I, a, idx[a], b[a] * P.dt, La, ga, w1, col, o, m);
+                sep_vectors<T, QS, BS, false>(I, a, idx[a], b[a] * P.dt, La, ga, w1, col, o, m, x);
             else
-                sep_vectors<T, QS, BS, true>(I, a, idx[a], b[a] * P.dt, La, ga, w1, col, o, m);
+                sep_vectors<T, QS, BS, true>(I, a, idx[a], b[a] * P.dt, La, ga, w1, col, o, m, x);
             if (I.periodic[a]) m = wsum;
         };
-        vectors(2, L2, cA, o2, m2);
+        vectors(2, L2, cA, o2, m2, x2);
         const T h0 = (T)I.step[0], h1 = (T)I.step[1], h2 = (T)I.step[2];
 #pragma unroll
         for (int k = 0; k < L; ++k) {
@@ -557,9 +562,9 @@ __global__ void __launch_bounds__(BS) k_step_sep3(
                 S2_[k] = e.y * h2;
             }
         }
-        vectors(0, L0, cA, o0, m0);
-        vectors(1, L1, cB, o1, m1);
-        if (!interior) emass = wsum * wsum * wsum - m0 * m1 * m2;
+        vectors(0, L0, cA, o0, m0, x0);
+        vectors(1, L1, cB, o1, m1, x1);
+        if (!interior) emass = x0 * wsum * wsum + m0 * (x1 * wsum + m1 * x2);
         const int s0 = (int)I.stride[0], s1 = (int)I.stride[1];
         const int n0 = I.n[0], n1 = I.n[1], n2 = I.n[2];
         const int per0 = I.periodic[0], per1 = I.periodic[1], per2 = I.periodic[2];
