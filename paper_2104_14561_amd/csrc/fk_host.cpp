@@ -221,7 +221,7 @@ struct fk_plan {
     std::map<std::string, Region> reg;
     size_t ws_bytes = 0;
     size_t ws_fwd_bytes = 0;   // prefix of the workspace that a forward pass uses
-    size_t ws_opt_bytes = 0;   // of it, lists and tables of the specialised steps (beside the common ones)
+    size_t ws_opt_bytes = 0;   // of it, lists, tables and pieces of the specialised steps (beside the common ones)
     size_t n_coords = 0;       // axis coordinates at the head of coords, bucket tables behind them
     unsigned char *ws = nullptr;
     fk::PlanDev dev{};
@@ -677,10 +677,10 @@ fk_status build_plan(fk_plan *p)
     std::vector<fk::WorkItem> tables;
     long long ell_total = 0, ell_wmax = 0, ell_rows_w = 0;
     std::vector<std::vector<int>> inst_sep, inst_rest;
-    std::vector<int> inst_cls, inst_lneed, inst_wraps;
+    std::vector<int> inst_cls;
     std::vector<std::vector<unsigned char>> inst_inner;   // per node: no landing point can exit
     std::vector<std::vector<unsigned char>> inst_seprow;  // per active row: separable
-    std::vector<std::array<int, 3>> inst_dils, inst_halo;
+    std::vector<std::array<int, 3>> inst_halo, inst_last;
     p->node_off.assign(p->n_inst + 1, 0);
     p->act_count.assign(p->n_inst, 0);
     long long coord_total = 0;
@@ -799,7 +799,7 @@ fk_status build_plan(fk_plan *p)
         // slope records are needed only where landing cells of active nodes can
         // reach: the active bounding box widened by the reach plus the corner
         int blo[3] = {0, 0, 0}, bhi[3] = {0, 0, 0};
-        int dils[3] = {0, 0, 0}, halo[3] = {0, 0, 0};
+        int dils[3] = {0, 0, 0}, halo[3] = {0, 0, 0}, lead[3] = {0, 0, 0}, last[3] = {0, 0, 0};
         for (int a = 0; a < pr.d; ++a) {
             double hmin = 1e300;
             for (int k = 1; k < pr.ax[a].n; ++k)
@@ -815,6 +815,11 @@ fk_status build_plan(fk_plan *p)
             // the nodes of the landing cells themselves lie within floor(reach / h) + 1
             // (with a margin for the rounding of the positions)
             halo[a] = (int)std::min<double>(std::floor(reach / hmin * (1.0 + 1e-9) + 1e-9) + 1.0, pr.ax[a].n);
+            // a footprint's first node lies at most `lead` nodes past its own node
+            // (upwards with a margin for the rounding)
+            const double first = std::floor((drift_bound(pr, a) * pr.dt - I.S * amax) / hmin + 1e-6);
+            lead[a] = (int)std::max(-1e9, std::min(1e9, first));
+            last[a] = amax_i[a] + lead[a];
             if (pr.ax[a].periodic || na == 0) {
                 blo[a] = 0;
                 bhi[a] = pr.ax[a].n - 1;
@@ -838,20 +843,26 @@ fk_status build_plan(fk_plan *p)
         // whose landing points stay strictly inside it (the box of half lengths
         // reach_a around the node lies inside)
         {
-            int Lneed = 0;
+            int Lneed = 0, La[3] = {0, 0, 0};
             bool wraps = false;   // a landing cell more than one period away
             for (int a = 0; a < pr.d; ++a) {
                 double hmin = 1e300;
                 for (int k = 1; k < pr.ax[a].n; ++k)
                     hmin = std::min(hmin, pr.ax[a].nodes[k] - pr.ax[a].nodes[k - 1]);
-                const int La = footprint(I.S * amax, hmin);
-                Lneed = std::max(Lneed, La);
-                wraps = wraps || (pr.ax[a].periodic && dils[a] + La > pr.ax[a].n - 2);
+                La[a] = footprint(I.S * amax, hmin);
+                Lneed = std::max(Lneed, La[a]);
+                wraps = wraps || (pr.ax[a].periodic && dils[a] + La[a] > pr.ax[a].n - 2);
             }
             p->wraps = p->wraps || wraps;
             int cls_box = -1;
             for (int c2 = 0; c2 < fk::kBoxClasses && !wraps; ++c2)
                 if (Lneed <= fk::box_len(pr.d, c2)) { cls_box = c2; break; }
+            // a periodic index wraps once: columns read past a short axis' footprint
+            // may not reach further than that
+            for (int a = 0; a < pr.d && cls_box >= 0; ++a) {
+                const int reads = fk::sep_reads(pr.d, fk::box_len(pr.d, cls_box), a, La);
+                if (pr.ax[a].periodic && lead[a] + reads - 1 > pr.ax[a].n) cls_box = -1;
+            }
             std::vector<int> sep, rest;
             std::vector<unsigned char> inner(J, 0);
             std::vector<unsigned char> seprow(na, 0);
@@ -890,11 +901,9 @@ fk_status build_plan(fk_plan *p)
             inst_sep.push_back(sep);
             inst_rest.push_back(rest);
             inst_cls.push_back(cls_box);
-            inst_lneed.push_back(Lneed);
-            inst_wraps.push_back(wraps ? 1 : 0);
         }
         build_work(p->row_work, i, na, kBlock);
-        inst_dils.push_back({dils[0], dils[1], dils[2]});
+        inst_last.push_back({last[0], last[1], last[2]});
         inst_halo.push_back({halo[0], halo[1], halo[2]});
         build_work(p->split_work, i, na, kBlock / std::max(2, group_of(p->qs)));
         p->n_nodes += J;
@@ -1411,17 +1420,33 @@ fk_status build_plan(fk_plan *p)
     // round is nearly empty, 24.4 and 48 us, pieces of 512 24.6 and 38, of 256 31
     // and 42)
     {
-        long long box_nodes_all = 0;
+        long long box_nodes_all = 0, narrow = 0;
         std::vector<long long> box_n(p->n_inst, 0);
+        std::vector<char> box_form(p->n_inst, 0);   // some step of it is separable
+        for (const fk::WorkItem &it : p->box_work) box_form[it.inst] = 1;
+        for (const fk::WorkItem &it : p->adj.box_work) box_form[it.inst] = 1;
         for (int i = 0; i < p->n_inst; ++i) {
-            if (p->inst[i].blen[0] == 0) continue;
+            fk::DevInst &I = p->inst[i];
+            if (I.blen[0] == 0) continue;
+            long long nn = 1;
+            for (int a = 0; a < p->d; ++a) nn *= I.blen[a];
+            narrow += (nn + kBlock - 1) / kBlock;
+            // the boxes also hold the columns that the separable kernels read
+            // past a footprint, so that every record they read is written
+            for (int a = 0; a < p->d && box_form[i]; ++a) {
+                const int reads = fk::sep_reads(p->d, fk::box_len(p->d, inst_cls[i]), a, I.sep_l);
+                const int end = std::min(I.n[a], inst_last[i][a] + reads);
+                I.blen[a] = std::max(I.blen[a], end - I.blo[a]);
+            }
             box_n[i] = 1;
-            for (int a = 0; a < p->d; ++a) box_n[i] *= p->inst[i].blen[a];
+            for (int a = 0; a < p->d; ++a) box_n[i] *= I.blen[a];
             box_nodes_all += box_n[i];
         }
         const int piece = box_nodes_all >= 1024LL * 256 * 8 ? 2 * kBlock : kBlock;
         p->slope_work = tables;
         for (int i = 0; i < p->n_inst; ++i) build_work(p->slope_work, i, (int)box_n[i], piece);
+        const long long pieces = (long long)(p->slope_work.size() - tables.size());
+        p->ws_opt_bytes = sizeof(fk::WorkItem) * (size_t)std::max(0LL, pieces - narrow);
     }
     p->n_table_work = (int)tables.size();
 
@@ -1600,7 +1625,7 @@ fk_status build_plan(fk_plan *p)
         add_region(p, "box_nodes", sizeof(int) * std::max<size_t>(p->box_nodes.size(), 1));
         add_region(p, "box_work", sizeof(fk::WorkItem) * std::max<size_t>(p->box_work.size(), 1));
     }
-    p->ws_opt_bytes = p->ws_bytes - opt0 + sizeof(double) * (p->coords.size() - p->n_coords);
+    p->ws_opt_bytes += p->ws_bytes - opt0 + sizeof(double) * (p->coords.size() - p->n_coords);
     add_region(p, "fw_nodes", sizeof(int) * std::max<size_t>(p->fw_nodes.size(), 1));
     add_region(p, "fw_work", sizeof(fk::WorkItem) * std::max<size_t>(p->fw_work.size(), 1));
     add_region(p, "fw_split_work", sizeof(fk::WorkItem) * std::max<size_t>(p->fw_split_work.size(), 1));

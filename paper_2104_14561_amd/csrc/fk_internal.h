@@ -39,6 +39,17 @@ inline int box_len(int d, int c)
     constexpr int l2[kBoxClasses] = {6, 9, 12, 15, 0}, l3[kBoxClasses] = {3, 4, 6, 9, 12};
     return d == 2 ? l2[c] : l3[c];
 }
+// Nodes that the separable kernels of class length L read along axis a from a
+// footprint's first node: the instance's own footprint on the axes they loop
+// over, the unrolled length on the others (in 2D axis 1, read in threes up to 6;
+// in 3D axis 2, and every axis up to 4).  The columns past the footprint carry no
+// weight, but their records must exist.
+inline int sep_reads(int d, int L, int a, const int *sep_l)
+{
+    const int own = sep_l[a] < L ? sep_l[a] : L;
+    if (d == 2) return a == 0 ? own : (L > 6 || own > 3 ? L : 3);
+    return L <= 4 || a == 2 ? L : own;
+}
 constexpr int adj_threads(int d, int L, bool f32)
 {
     return d == 3 && L > 6 && !f32 ? 128 : 256;
@@ -83,8 +94,9 @@ struct DevInst {
     long long out_off;
     int face[kMaxDim][2];          // FK_FACE_* per axis and side
     int sdiff;                     // diffusion depends on the node (runaway model)
-    int blo[kMaxDim];              // reachable box (the nodes a step's gathers can touch):
-    int blen[kMaxDim];             // first node and length per axis (0 without active nodes)
+    int blo[kMaxDim];              // reachable box (the nodes a step's gathers can touch, with
+    int blen[kMaxDim];             // or without weight): first node and length per axis (0
+                                   // without active nodes)
     int sep_l[kMaxDim];            // footprint nodes per axis of one node's landing cells
     // axes that are not uniform: cell lookup by buckets of the smallest spacing,
     // lut_n entries of the coordinate array from lut_off (0 entries: bisection)
