@@ -80,8 +80,11 @@ __global__ void __launch_bounds__(kLineThreads) k_line_steps(
         f1[i] = wq[i] * h * d1;
         zq[i] = I.S * P.gh_a[q];
     }
+    bool odd = false;   // some value of the first field is not finite
     for (int j = tid; j < n; j += kLineThreads) {
-        recs[j].x = u_in[I.node_off + j];
+        const T u = u_in[I.node_off + j];
+        odd = odd || !isfinite((double)u);
+        recs[j].x = u;
         cls[j] = P.chi[I.node_off + j];
     }
     for (int j = grp; j < n; j += NG) {
@@ -97,8 +100,21 @@ __global__ void __launch_bounds__(kLineThreads) k_line_steps(
         }
         mask[j * G + lane] = (unsigned char)m;
     }
-    __syncthreads();
+    const int any_odd = __builtin_amdgcn_readfirstlane(__syncthreads_or(odd));
     if constexpr (ONE) {
+        // the value of node j's inside landing point q
+        auto point = [&](const V2 *r, int j, int q, T uref) -> T {
+            const double t = fma_t(P.gh_a[q], I.S * I.inv_h[0], bdt * I.inv_h[0]);
+            const double fl = floor(t);
+            T v0, v1, d0, d1;
+            unit_basis<T>((T)(t - fl), v0, v1, d0, d1);
+            int k = j + (int)fl;
+            if (per) k += k < 0 ? n - 1 : (k > n - 2 ? 1 - n : 0);
+            const V2 a = r[min(max(k, 0), n - 2)], b = r[min(max(k, 0), n - 2) + 1];
+            if (k < 0) return w1[q] * (a.x - uref);
+            if (k > n - 2) return w1[q] * (b.x - uref);
+            return w1[q] * (v0 * (a.x - uref) + v1 * (b.x - uref) + h * (d0 * a.y + d1 * b.y));
+        };
         const int j = grp;
         const bool act = j < n && cls[j] == 0;
         int kc[NQ];
@@ -124,37 +140,53 @@ __global__ void __launch_bounds__(kLineThreads) k_line_steps(
         const bool image = lane == 0 && per && j == 0 && act;
         const T fix = j < n && (cls[j] & 5) == 1 ? T(1) : T(0);
         em = quad_sum(em);
-        int cur = 0;
-        for (int m = n_hi - 1; m >= n_lo; --m) {
-            V2 *r = recs + cur * nmax, *rn = recs + (1 - cur) * nmax;
-            if (tid < n) r[tid].y = pchip<T>(r[il].x, r[ic].x, r[ir].x, ih, ih);
-            __syncthreads();
-            const T uref = act ? r[j].x : T(0);
-            T acc = T(0);
-#pragma unroll
-            for (int i = 0; i < NQ; ++i) {
-                const V2 a = r[kc[i]], b = r[kc[i] + 1];
-                acc = fma_t(y0[i], a.x - uref, fma_t(y1[i], b.x - uref, fma_t(f0[i], a.y, fma_t(f1[i], b.y, acc))));
-            }
-            acc = quad_sum(acc);
-            if (writes) {
-                const T v = act ? uref + acc + em * (T(1) - uref) : fix;
-                flag_nonfinite(P.flags, v);
-                rn[j].x = v;
-                if (image) rn[n - 1].x = v;
-                if (store != nullptr && m % every == 0) {
-                    T *out = store + (long long)(m / every - shift) * stride + I.node_off;
-                    out[j] = v;
-                    if (image) out[n - 1] = v;
+        // all steps; check: the first field holds values that are not finite
+        auto steps = [&](auto check) {
+            int cur = 0;
+            for (int m = n_hi - 1; m >= n_lo; --m) {
+                V2 *r = recs + cur * nmax, *rn = recs + (1 - cur) * nmax;
+                if (tid < n) r[tid].y = pchip<T>(r[il].x, r[ic].x, r[ir].x, ih, ih);
+                __syncthreads();
+                const T uref = act ? r[j].x : T(0);
+                T acc = T(0);
+    #pragma unroll
+                for (int i = 0; i < NQ; ++i) {
+                    const V2 a = r[kc[i]], b = r[kc[i] + 1];
+                    acc = fma_t(y0[i], a.x - uref, fma_t(y1[i], b.x - uref, fma_t(f0[i], a.y, fma_t(f1[i], b.y, acc))));
                 }
-                if (u_out != nullptr && m == n_lo) {
-                    u_out[I.node_off + j] = v;
-                    if (image) u_out[I.node_off + n - 1] = v;
+                acc = quad_sum(acc);
+                if (check.value && act && !isfinite((double)acc)) {
+                    // a record without weight may have held a value that is not finite:
+                    // the inside points alone
+                    acc = T(0);
+    #pragma unroll 1
+                    for (int q = lane, i = 0; q < QS; q += G, ++i) {
+                        if ((mask[j * G + lane] >> i) & 1u) continue;
+                        acc += point(r, j, q, uref);
+                    }
+                    acc = quad_sum(acc);
                 }
+                if (writes) {
+                    const T v = act ? uref + acc + em * (T(1) - uref) : fix;
+                    flag_nonfinite(P.flags, v);
+                    rn[j].x = v;
+                    if (image) rn[n - 1].x = v;
+                    if (store != nullptr && m % every == 0) {
+                        T *out = store + (long long)(m / every - shift) * stride + I.node_off;
+                        out[j] = v;
+                        if (image) out[n - 1] = v;
+                    }
+                    if (u_out != nullptr && m == n_lo) {
+                        u_out[I.node_off + j] = v;
+                        if (image) u_out[I.node_off + n - 1] = v;
+                    }
+                }
+                __syncthreads();
+                cur = 1 - cur;
             }
-            __syncthreads();
-            cur = 1 - cur;
-        }
+        };
+        if (any_odd) steps(std::true_type{});
+        else steps(std::false_type{});
         return;
     }
     // value of an inactive node (an exit node's, 0 or 1; an image of an active

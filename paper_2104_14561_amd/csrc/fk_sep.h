@@ -103,6 +103,112 @@ __device__ inline void sep_vectors(const DevInst &I, int a, int idx, double bdt,
     }
 }
 
+// A node's value over its inside landing points alone, one after another, on the
+// coordinates of affine axes.  The separable kernels also read records without
+// weight, exiting points' own among them in the grouped ones, and 0 times a value
+// that is not finite is NaN: nodes whose sum is not finite are taken again so
+// (retake), and depend on the records their points touch and no others (a caller's
+// field may hold NaN or infinity outside the region).
+template <typename T, int D, int QS, bool TW>
+__device__ inline T point_value(const PlanDev &P, int n, int inst, const DevInst &I, int node,
+                                const double2 *__restrict__ trig, const T *__restrict__ packed)
+{
+#pragma clang fp contract(off)
+    using R = typename RecT<T, 4>::type;
+    const R *ri = reinterpret_cast<const R *>(packed) + I.node_off;
+    const R *qi = TW && D == 3 ? reinterpret_cast<const R *>(P.packed2) + I.node_off : nullptr;
+    int idx[3];
+    split_node<D>(I, node, idx);
+    const T uref = ri[node].x;
+    double b[3];
+    drift<D>(I, time_factors(P, n, inst), trig, idx, b);
+    const double *ga = P.gh_a;
+    const T *w1 = weights1<T>(P);
+    double c[3];
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+        c[a] = ((idx[a] == I.n[a] - 1) ? I.hi[a] : (double)idx[a] * I.step[a] + I.lo[a]) + b[a] * P.dt;
+    const bool ball = I.region_kind == 1;
+    T acc = T(0), em = T(0);
+#pragma unroll 1
+    for (int q = 0; q < P.n_quad; ++q) {
+        int qq[3], r = q;
+#pragma unroll
+        for (int a = D - 1; a >= 0; --a) {
+            qq[a] = r % QS;
+            r /= QS;
+        }
+        T w = T(1);
+        bool ex = false;
+        double d2 = 0.0;
+        int base = 0;
+        Basis<T> B[3];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            const AxisEval e = eval_axis_affine(I, a, c[a], ga[qq[a]]);
+            w *= w1[qq[a]];
+            ex = ex || e.ex;
+            d2 = a == 0 ? e.dz2 : d2 + e.dz2;
+            base += e.k * (a == D - 1 ? 1 : (int)I.stride[a]);
+            B[a] = hermite<T>(e.s, e.h);
+        }
+        if (ex || (ball && d2 >= I.r2)) {
+            em += w;
+            continue;
+        }
+        // corner by corner: its records times the bases of the axes' sides
+        T pt = T(0);
+#pragma unroll 1
+        for (int k = 0; k < (1 << D); ++k) {
+            const bool c0 = (k >> (D - 1)) & 1, c1 = (k >> (D - 2)) & 1, c2 = D == 3 && (k & 1);
+            const int at = base + (c0 ? (int)I.stride[0] : 0) + (c1 ? (D == 3 ? (int)I.stride[1] : 1) : 0) + (c2 ? 1 : 0);
+            const T v0 = c0 ? B[0].v1 : B[0].v0, d0 = c0 ? B[0].d1 : B[0].d0;
+            const T v1 = c1 ? B[1].v1 : B[1].v0, d1 = c1 ? B[1].d1 : B[1].d0;
+            const R r = ri[at];
+            if constexpr (D == 2) {
+                pt += v1 * (v0 * (r.x - uref) + d0 * r.y) + d1 * (v0 * r.z + (TW ? d0 * r.w : T(0)));
+            } else {
+                const T v2 = c2 ? B[2].v1 : B[2].v0, d2_ = c2 ? B[2].d1 : B[2].d0;
+                T a0 = v0 * (r.x - uref) + d0 * r.y, a1 = v0 * r.z, a2 = v0 * r.w, a12 = T(0);
+                if constexpr (TW) {
+                    const R t = qi[at];   // (t01, t02, t12, t012)
+                    a1 += d0 * t.x;
+                    a2 += d0 * t.y;
+                    a12 = v0 * t.z + d0 * t.w;
+                }
+                pt += v2 * (v1 * a0 + d1 * a1) + d2_ * (v1 * a2 + d1 * a12);
+            }
+        }
+        acc += w * pt;
+    }
+    return uref + acc + em * (T(1) - uref);
+}
+
+// The nodes of this thread whose stored value is not finite, once more.  A loop of
+// its own behind the step's, which finite fields never enter: inside that loop it
+// takes 4 to 30 registers and up to a wave per SIMD.  NPB threads' nodes per
+// workgroup, NS workgroups to a work item, this thread's number `slot`.
+template <typename T, int D, int QS, bool TW, int NPB, int NS>
+__device__ inline void retake(const PlanDev &P, int n, int n_work, int slot, const DevInst *__restrict__ insts,
+                              const WorkItem *__restrict__ work, const int *__restrict__ nodes,
+                              const double2 *__restrict__ trig, const T *__restrict__ packed, T *u_out)
+{
+    const WorkRange wr = work_range(0, n_work * NS);
+    for (int w = wr.begin; w < wr.end; w += wr.step) {
+        const WorkItem it = work[w / NS];
+        const int t = (w % NS) * NPB + slot;
+        if (t >= it.count) continue;
+        const DevInst &I = insts[it.inst];
+        const int node = nodes[it.first + t];
+        if (isfinite((double)u_out[I.node_off + node])) continue;
+        const T v = point_value<T, D, QS, TW>(P, n, it.inst, I, node, trig, packed);
+        flag_nonfinite(P.flags, v);
+        int idx[3];
+        split_node<D>(I, node, idx);
+        store_node<D, T>(I, idx, node, v, u_out);
+    }
+}
+
 // Thread per node.  The axis-1 vectors move from the thread's LDS column to
 // registers, the axis-0 vectors then take the column's place and are read one
 // row at a time; a row is L1 records against the axis-1 vectors, its loop
@@ -139,6 +245,7 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
     for (int q = 0; q < QS; ++q) wsum += w1[q];
     // BS < 256: consecutive workgroups take the parts of a work item
     constexpr int NS = kBlock / BS;
+    bool bad = false;
     const WorkRange wr = work_range(0, n_work * NS);
     for (int w = wr.begin; w < wr.end; w += wr.step) {
         const WorkItem it = work[w / NS];
@@ -207,9 +314,10 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
         if (L > 6 || L1 > 3) rows(std::integral_constant<int, L>{});
         else rows(std::integral_constant<int, 3>{});
         const T v = uref + acc + emass * (T(1) - uref);
-        flag_nonfinite(P.flags, v);
+        bad = bad || !isfinite((double)v);
         store_node<2, T>(I, idx, node, v, u_out);
     }
+    if (__builtin_expect(bad, 0)) retake<T, 2, QS, TW, BS, kBlock / BS>(P, n, n_work, threadIdx.x, insts, work, nodes, trig, packed, u_out);
 }
 
 // Q*^2 landing points by a group of GL = pow2(Q*) lanes per node, lane l taking
@@ -249,6 +357,7 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
     const int q = lane < QS ? lane : QS - 1;   // idle lanes repeat the last one, unweighted
     const double gq = P.gh_a[q];
     const T wq = lane < QS ? weights1<T>(P)[q] : T(0);
+    bool bad = false;
     const WorkRange wr = work_range(0, n_work);
     for (int w = wr.begin; w < wr.end; w += wr.step) {
         const WorkItem it = work[w];
@@ -341,9 +450,10 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
         }
         if (!valid || lane != 0) continue;
         const T v = uref + acc + emass * (T(1) - uref);
-        flag_nonfinite(P.flags, v);
+        bad = bad || !isfinite((double)v);
         store_node<2, T>(I, idx, node, v, u_out);
     }
+    if (__builtin_expect(bad, 0)) retake<T, 2, QS, TW, NPB, 1>(P, n, n_work, slot, insts, work, nodes, trig, packed, u_out);
 }
 
 // A whole backward step of a small 2D plan in one launch: a workgroup takes a
@@ -435,9 +545,9 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     const double r2 = ball ? I.r2 : HUGE_VAL;
     // one landing coordinate: cell (unwrapped, inside the tile), position,
     // squared distance (infinite: exit)
-    auto axis = [&](int a, int &k, T &s, double &d2) {
+    auto axis = [&](int a, double g, int &k, T &s, double &d2) {
         const double x = (idx[a] == I.n[a] - 1) ? I.hi[a] : (double)idx[a] * I.step[a] + I.lo[a];
-        const AxisEval e = eval_axis_affine(I, a, x + b[a] * P.dt, gq);
+        const AxisEval e = eval_axis_affine(I, a, x + b[a] * P.dt, g);
         int kk = e.k;
         if (I.periodic[a]) kk += kk < tb.lo[a] ? I.n[a] - 1 : (kk > tb.lo[a] + tb.ext[a] - 2 ? 1 - I.n[a] : 0);
         k = min(max(kk, tb.lo[a]), tb.lo[a] + tb.ext[a] - 2) - tb.lo[a];
@@ -447,13 +557,13 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     int k0, k1;
     T s, v0, v1, f0, f1;
     double d2;
-    axis(0, k0, s, d2);
+    axis(0, gq, k0, s, d2);
     unit_basis<T>(s, v0, v1, f0, f1);
     const T wh = wq * (T)I.step[0];
     rows[slot][lane] = {wq * v0, wq * v1, wh * f0, wh * f1};
     rd2[slot][lane] = d2;
     roff[slot][lane] = k0 * e1;
-    axis(1, k1, s, d2);
+    axis(1, gq, k1, s, d2);
     unit_basis<T>(s, v0, v1, f0, f1);
     // lanes of a node belong to one wave: its LDS writes precede its reads
     __builtin_amdgcn_wave_barrier();
@@ -492,7 +602,38 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     acc = group_sum<GL>(acc);
     emass = group_sum<GL>(emass);
     if (!valid || lane != 0) return;
-    const T v = uref + acc + emass * (T(1) - uref);
+    T v = uref + acc + emass * (T(1) - uref);
+    if (!isfinite((double)v)) {
+        // the inside points alone (see point_value)
+        acc = emass = T(0);
+#pragma unroll 1
+        for (int q1 = 0; q1 < QS; ++q1) {
+            axis(1, P.gh_a[q1], k1, s, d2);
+            unit_basis<T>(s, v0, v1, f0, f1);
+            const T h1 = (T)I.step[1], w1 = weights1<T>(P)[q1];
+            T part = T(0);
+#pragma unroll 1
+            for (int q0 = 0; q0 < QS; ++q0) {
+                const Row rw = rows[slot][q0];
+                if (rd2[slot][q0] + d2 >= r2) {
+                    emass += w1 * (rw.x0 + rw.x1);
+                    continue;
+                }
+                const R *p = rec + (roff[slot][q0] + k1);
+                const R p00 = p[0], p01 = p[1], p10 = p[e1], p11 = p[e1 + 1];
+                const T u0 = rw.x0 * (p00.x - uref) + rw.x1 * (p10.x - uref) + rw.d0 * p00.y + rw.d1 * p10.y;
+                const T u1 = rw.x0 * (p01.x - uref) + rw.x1 * (p11.x - uref) + rw.d0 * p01.y + rw.d1 * p11.y;
+                T y0 = rw.x0 * p00.z + rw.x1 * p10.z, y1 = rw.x0 * p01.z + rw.x1 * p11.z;
+                if constexpr (TW) {
+                    y0 += rw.d0 * p00.w + rw.d1 * p10.w;
+                    y1 += rw.d0 * p01.w + rw.d1 * p11.w;
+                }
+                part += v0 * u0 + v1 * u1 + h1 * (f0 * y0 + f1 * y1);
+            }
+            acc += w1 * part;
+        }
+        v = uref + acc + emass * (T(1) - uref);
+    }
     flag_nonfinite(P.flags, v);
     store_node<2, T>(I, idx, node, v, u_out);
 }
@@ -507,7 +648,7 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
 // points; 65^3 with the R2 interpolant 18 us against 457 us over the landing
 // points; 65^3 in FP64 with 6 x 6 x 9 footprints 116 against 597 us.
 template <typename T, int QS, int L, int BS, bool TW>
-__global__ void __launch_bounds__(BS) k_step_sep3(
+__global__ void __launch_bounds__(BS, sizeof(T) == 8 && L == 4 && TW ? 2 : 1) k_step_sep3(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
     const WorkItem *__restrict__ work, const int *__restrict__ nodes,
     const double2 *__restrict__ trig, const T *__restrict__ packed, T *__restrict__ u_out)
@@ -523,6 +664,7 @@ __global__ void __launch_bounds__(BS) k_step_sep3(
 #pragma unroll
     for (int q = 0; q < QS; ++q) wsum += w1[q];
     constexpr int NS = kBlock / BS;
+    bool bad = false;
     const WorkRange wr = work_range(0, n_work * NS);
     for (int w = wr.begin; w < wr.end; w += wr.step) {
         const WorkItem it = work[w / NS];
@@ -615,9 +757,10 @@ __global__ void __launch_bounds__(BS) k_step_sep3(
         if (__all(o2 >= 0 && o2 + L <= n2)) contract(o2, [](int k) { return k; });
         else contract(0, [&](int k) { return wrap_index(o2 + k, n2, per2); });
         const T v = uref + acc + emass * (T(1) - uref);
-        flag_nonfinite(P.flags, v);
+        bad = bad || !isfinite((double)v);
         store_node<3, T>(I, idx, node, v, u_out);
     }
+    if (__builtin_expect(bad, 0)) retake<T, 3, QS, TW, BS, kBlock / BS>(P, n, n_work, threadIdx.x, insts, work, nodes, trig, packed, u_out);
 }
 
 }  // namespace
