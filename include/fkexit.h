@@ -88,9 +88,9 @@ enum { FK_COEF_CONST = 0, FK_COEF_CELLULAR2D = 1, FK_COEF_ABC3D = 2, FK_COEF_ROL
  * decides (low face before high face), then the ball.  Plans with a face other
  * than FK_FACE_EXIT1 (and FK_COEF_RUNAWAY3D plans) run the fused form and the
  * forward calls only, in the thread-per-node step layouts (fk_options
- * .step_kernel 0, 1 or 3; 4 falls back to 1), in 3D box regions the separable
- * step over shared entries where that reads fewer records, or the lane-group
- * one (2, and with FK_HERMITE_R2). */
+ * .step_kernel 0, 1, 3 or 4, which is 1 there), in 3D box regions with 0 and 4
+ * the separable step over shared entries where that reads fewer records, or the
+ * lane-group one (2, and with FK_HERMITE_R2). */
 enum { FK_FACE_EXIT1 = 0, FK_FACE_EXIT0 = 1, FK_FACE_REFLECT = 2 };
 
 /* Exit region (paper Section 2: D is an open box; a disc or ball target, such
@@ -167,21 +167,20 @@ typedef struct {
     int block;       /* threads per workgroup, 0 = library default */
     int step_kernel; /* fused step layout: 0 = auto; 1 = one thread per node;
                         2 = a lane group per node over the tensor points (any gh_q);
-                        3 = Q* lanes per node over the outermost axis;
+                        3 = Q* lanes per node over the outermost axis (2D: the whole
+                        step in one launch where its records fit the LDS; 1D on an
+                        affine axis of up to 4096 nodes: many steps in one launch);
                         4 = separable box form for nodes whose landing points
                         cannot reach a ball boundary (footprint up to 15 nodes
                         per axis in 2D, 12 in 3D; d >= 2 on affine axes), per
                         landing point for the others.  1, 3 and 4 exist for
                         d=1: gh_q 2..8,10,12,16; d=2: 2..8; d=3: 2..6
                         (FK_ERR_UNSUPPORTED otherwise).  auto picks 4 for 2D
-                        and 3D plans with many active nodes, 1 for other large
-                        plans, 3 for small ones (2D: the whole step in one
-                        launch where its records fit the LDS; 1D on an affine
-                        axis of up to 4096 nodes: many steps in one launch), 2
-                        when the others are not compiled for gh_q; fk_tune
-                        measures them instead.  Plans with faces other than
-                        exit-1 (or the runaway model) take 4 as 1, and with
-                        FK_HERMITE_R2 always run 2 */
+                        plans with many active nodes and for 3D plans, 1 for
+                        other large plans, 3 for small and 1D ones, 2 when the
+                        others are not compiled for gh_q; fk_tune measures them
+                        instead.  Plans with faces other than exit-1 (or the
+                        runaway model) run 2 with FK_HERMITE_R2 */
     int columns;     /* fk_forward_horizons: most columns one launch of the
                         FK_FORM_ELL product takes (1..4; 0 = 1); the workspace
                         holds that many record planes */
@@ -209,10 +208,11 @@ typedef struct fk_plan fk_plan;
 /* Result of fk_tune: the fastest step layout and the measured mean duration
  * of one backward step (slope pass + step pass) per layout, in milliseconds
  * (0 where the layout was not timed: not compiled for the plan, or the same
- * lists as one already timed). */
+ * kernels and lists as one already timed; the default, 0, is timed after the
+ * others). */
 typedef struct {
     int step_kernel;          /* value for fk_options.step_kernel */
-    double ms_per_step[5];    /* indexed by step_kernel 0..4 (0 unused) */
+    double ms_per_step[5];    /* indexed by step_kernel 0..4 */
 } fk_tune_result;
 
 /* Message of the last error on this thread ("" if none).  Library plumbing:
@@ -390,7 +390,7 @@ fk_status fk_adjoint(fk_plan *p, const void *lam0, double *grad, void *lamN,
 
 /* Autotuner for batched plans (an engineering addition; the paper has no
  * counterpart): builds a trial plan for each step layout
- * (fk_options.step_kernel 1..4) of the problems with n_steps replaced by
+ * (fk_options.step_kernel 1..4, then 0) of the problems with n_steps replaced by
  * trial_steps (the cost of a step does not depend on n), runs its backward
  * pass twice on stream with the caller's other options, and returns the
  * layout with the shortest second run in out (host).  workspace (device,

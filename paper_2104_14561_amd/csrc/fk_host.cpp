@@ -970,8 +970,10 @@ fk_status build_plan(fk_plan *p)
             for (int a = 0; a < p->d; ++a) affine = affine && I.affine[a];
         // faces (other than exit-1) with the R2 interpolant: the lane-group step
         const bool faces_r2 = p->faces && p->opt.hermite == FK_HERMITE_R2;
+        // (4 takes the nodes that are not separable as the default does)
+        const bool box4 = sk == 4 && affine && !p->faces && fk::box_compiled(p->d, p->qs);
         if (sk == 2 || !node_ok || faces_r2) p->step_kind = 1;
-        else if (sk == 3 || (sk == 0 && !large)) p->step_kind = 2;
+        else if (sk == 3 || ((sk == 0 || box4) && !large)) p->step_kind = 2;
         else p->step_kind = 0;
         // the separable form by default: a node's Q*^d points gather 2^d
         // corners each, against the product of its footprint's lengths.  In 3D
@@ -1018,7 +1020,7 @@ fk_status build_plan(fk_plan *p)
         // 1D: one workgroup takes an instance through many steps when its axis
         // fits the LDS (measured on 201 nodes, Q* = 16, FP64: 16 us per step in
         // two launches, 0.9 us inside one)
-        if (p->d == 1 && sk == 0 && node_ok && affine && !p->wraps && !p->faces &&
+        if (p->d == 1 && (sk == 0 || sk == 3) && node_ok && affine && !p->wraps && !p->faces &&
             p->opt.form == FK_FORM_FUSED) {
             int nmax = 0;
             for (const fk::DevInst &I : p->inst) nmax = std::max(nmax, I.n[0]);
@@ -1095,7 +1097,8 @@ fk_status build_plan(fk_plan *p)
                 points += (long long)inst_rest[i].size() +
                           (!p->use_box || inst_cls[i] < 0 || p->dual ? (long long)inst_sep[i].size() : 0);
             const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
-            p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && (p->step_kind != 0 || points < most);
+            p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && sk != 1 &&
+                           (p->step_kind != 0 || points < most);
         }
         for (int i = 0; i < p->n_inst; ++i) {
             const fk_problem &pr = p->probs[i];
@@ -1161,7 +1164,7 @@ fk_status build_plan(fk_plan *p)
         bool short_axes = true;   // entries hold 16-bit node indices
         for (const fk::DevInst &I : p->inst)
             for (int a = 0; a < p->d; ++a) short_axes = short_axes && I.n[a] <= 65536;
-        bool ent = p->d == 3 && p->step_kind != 1 && node_ok && (p->faces || !affine) && !p->wraps &&
+        bool ent = p->d == 3 && (sk == 0 || sk == 4) && p->step_kind != 1 && node_ok && (p->faces || !affine) && !p->wraps &&
                    p->opt.form == FK_FORM_FUSED && p->opt.hermite == FK_HERMITE_R1 &&
                    p->probs[0].region_kind == FK_REGION_BOX && short_axes;
         if (ent) {
@@ -2674,8 +2677,10 @@ fk_status fk_tune(const fk_problem *probs, int n_inst, const fk_options *opt, in
     base.ckpt_every = 0;
     std::memset(out, 0, sizeof(*out));
     double best = 1e300;
-    std::vector<std::pair<int, int>> seen;   // (step_kind, use_box) already timed
-    for (int sk = 1; sk <= 4; ++sk) {
+    // what a layout runs: layouts of the same kernels and lists are timed once; the
+    // default (0) last, where it is none of the others
+    std::vector<std::array<int, 6>> seen;
+    for (int sk : {1, 2, 3, 4, 0}) {
         fk_options o = base;
         o.step_kernel = sk;
         fk_plan *p = nullptr;
@@ -2683,7 +2688,9 @@ fk_status fk_tune(const fk_problem *probs, int n_inst, const fk_options *opt, in
             g_err.clear();   // layout not compiled for this plan: skip it
             continue;
         }
-        const std::pair<int, int> key{p->step_kind, p->use_box ? 1 : 0};
+        const std::array<int, 6> key{p->step_kind, p->use_box ? 1 : 0, p->line_nmax > 0 ? 1 : 0,
+                                     p->small_work.empty() ? 0 : 1, p->ent_work.empty() ? 0 : 1,
+                                     p->pt_groups ? 1 : 0};
         bool dup = false;
         for (const auto &k : seen) dup = dup || k == key;
         if (dup) {
@@ -2720,7 +2727,7 @@ fk_status fk_tune(const fk_problem *probs, int n_inst, const fk_options *opt, in
             out->step_kernel = sk;
         }
     }
-    if (out->step_kernel == 0) return fail(FK_ERR_UNSUPPORTED, "no step layout could be built");
+    if (seen.empty()) return fail(FK_ERR_UNSUPPORTED, "no step layout could be built");
     return FK_OK;
 }
 

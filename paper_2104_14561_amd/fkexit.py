@@ -444,7 +444,7 @@ def tune(problems, precision: str = "f64", form: str = "fused", use_graph: bool 
     del keep, ws
     names = {v: k for k, v in STEP_KERNEL.items()}
     return {"step_kernel": names[res.step_kernel],
-            "ms_per_step": {names[k]: float(res.ms_per_step[k]) for k in range(1, 5)
+            "ms_per_step": {names[k]: float(res.ms_per_step[k]) for k in range(5)
                             if res.ms_per_step[k] > 0}}
 
 
