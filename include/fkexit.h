@@ -441,8 +441,9 @@ fk_status fk_probe_precision(const fk_problem *probs, int n_inst, const fk_optio
  * stream, with HIP events around every kernel launch, and returns the mean
  * duration in milliseconds per launch of each pass kind in ms[4] (host):
  * [0] slope pass, [1] fused step pass, [2] ELL assembly, [3] ELL product
- * (0 for kinds the plan's form does not launch); counts[4] (host) receives the
- * number of launches timed.  Synchronises stream. */
+ * (0 for kinds the plan's form does not launch; where the whole step is one
+ * launch that is [1], and in 1D a launch of up to 4096 steps); counts[4] (host)
+ * receives the number of launches timed.  Synchronises stream. */
 fk_status fk_profile_pass(fk_plan *p, double *ms, int *counts, void *stream);
 
 /* Measurement hook for the adjoint (the reverse sweep of Eq. (e36), timed):

@@ -1852,15 +1852,16 @@ fk_status enqueue_step(fk_plan *p, int n, const void *u_next, void *u_out, hipSt
     return FK_OK;
 }
 
+constexpr int kLineSteps = 4096;   // most steps of a 1D launch
+
 // 1D plans (line_nmax > 0): steps hi - 1 .. lo from src, u^{lo} to dst and
 // u^m to store + (m / every - shift) fields (each may be null), a launch per
-// 4096 steps.  A launch that is not the last writes to the other work field.
+// kLineSteps.  A launch that is not the last writes to the other work field.
 fk_status enqueue_line(fk_plan *p, int hi, int lo, const void *src, void *dst, void *store, int every,
                        int shift, hipStream_t s)
 {
-    constexpr int kChunk = 4096;
     while (hi > lo) {
-        const int to = std::max(lo, hi - kChunk);
+        const int to = std::max(lo, hi - kLineSteps);
         void *out = to == lo ? dst : (src == p->at("uA") ? p->at("uB") : p->at("uA"));
         FK_LAUNCH(fk::launch_line_steps(p->dev, p->f32, p->line_nmax, hi, to, src, out, store, every, shift, s));
         src = out;
@@ -2628,8 +2629,22 @@ fk_status fk_profile_pass(fk_plan *p, double *ms, int *counts, void *stream)
     FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, ua, s));
     FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, ub, s));
     void *cur = ua, *nxt = ub;
-    for (int n = p->N - 1; n >= 0; --n) {
+    // the launches of a pass (enqueue_pass): many steps, one step, or its parts
+    for (int n = p->N; n > 0 && p->line_nmax > 0; n -= kLineSteps) {
+        const int to = std::max(0, n - kLineSteps);
         FK_TRY(rec(-1));
+        FK_TRY(enqueue_line(p, n, to, cur, nxt, nullptr, 1, 0, s));
+        FK_TRY(rec(1));
+        std::swap(cur, nxt);
+    }
+    for (int n = p->N - 1; n >= 0 && p->line_nmax == 0; --n) {
+        FK_TRY(rec(-1));
+        if (p->dev.n_small_work > 0) {
+            FK_TRY(enqueue_step(p, n, cur, nxt, s, true));
+            FK_TRY(rec(1));
+            std::swap(cur, nxt);
+            continue;
+        }
         FK_LAUNCH(fk::launch_slopes(p->dev, p->f32, n, cur, packed, s));
         FK_TRY(rec(0));
         if (p->opt.form == FK_FORM_ELL) {

@@ -385,7 +385,9 @@ class Plan:
 
     def profile_pass(self, stream=None):
         """Mean per-launch durations (ms) of the slope pass, fused step, ELL
-        assembly and ELL product over one pass, timed with HIP events."""
+        assembly and ELL product over one pass, timed with HIP events, and the
+        number of launches (no slope pass where a step is one launch; in 1D a
+        launch takes up to 4096 steps)."""
         ms = (ctypes.c_double * 4)()
         cnt = (ctypes.c_int * 4)()
         _check(load().fk_profile_pass(self._h, ms, cnt, ctypes.c_void_p(_stream(stream))))

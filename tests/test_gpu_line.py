@@ -81,3 +81,40 @@ def test_checkpoints_and_recomputed_segments(n, K):
     assert np.abs(plan.split(u0)[0][0].cpu().numpy() - oracle.solve(p, snaps=[0])[0]).max() <= 1e-12
     assert np.abs(g - g_ref).max() <= 1e-10 * np.abs(g_ref).max()
     plan.close()
+
+
+# a step is an average (a contraction up to the slopes' limiter), so that the stored
+# values' rounding adds up: at most half a unit in the last place of 1 per step, on
+# the library's side and, in FP64, on the oracle's
+@pytest.mark.parametrize("prec,bar", [("f64", 2 * 9000 * 2.0 ** -53), ("f32", 9000 * 2.0 ** -24)])
+@pytest.mark.parametrize("n,use_graph", [(33, False), (33, True), (301, False)])
+def test_more_steps_than_a_launch_takes(n, use_graph, prec, bar):
+    """4096 steps to a launch: passes of 9000 with snapshots amid the launches,
+    at their ends and beside them."""
+    p = _problem(n, 5, steps=9000).replace(D=2e-4, dt=1e-3)
+    snaps = [0, 808, 4904, 4903, 6001, 9000]
+    ref = oracle.solve(p, snaps=snaps)
+    plan = Plan(p, precision=prec, use_graph=use_graph)
+    for _ in range(2):
+        got = plan.split(plan.forward(snaps))[0].double().cpu().numpy()
+        assert np.abs(got - ref).max() <= bar
+    hz = plan.split(plan.forward_horizons([9000, 4097, 4096]))[0].double().cpu().numpy()
+    assert np.abs(hz - oracle.solve(p, snaps=[0, 4903, 4904])).max() <= bar
+    assert plan.check_flags() == 0
+    plan.close()
+
+
+def test_profile_times_the_launches_of_a_pass():
+    """fk_profile_pass: 1D plans launch many steps at once, small 2D plans one."""
+    plan = Plan(_problem(64, 8, steps=4100), precision="f64")
+    prof = plan.profile_pass()
+    plan.close()
+    assert prof["slopes"] == (0.0, 0) and prof["step_fused"][1] == 2 and prof["step_fused"][0] > 0.0
+    plan = Plan(W.paper2d().replace(n_steps=9), precision="f64")
+    prof = plan.profile_pass()
+    plan.close()
+    assert prof["slopes"] == (0.0, 0) and prof["step_fused"][1] == 9 and prof["step_fused"][0] > 0.0
+    plan = Plan(W.abc3d(n=9, n_steps=4), precision="f64")
+    prof = plan.profile_pass()
+    plan.close()
+    assert prof["slopes"][1] == prof["step_fused"][1] == 4
