@@ -196,6 +196,7 @@ struct fk_plan {
     // on their originals, which those forms read interchangeably, so it takes
     // the per-point form for its step (fw lists of every node beside the box ones)
     bool periodic = false, dual = false;
+    bool reads_images = false;   // its box form takes a caller's field too
     bool pt_groups = false;   // 2D landing points by lane groups (k_step_pt2)
     // 3D plans in entry form (faces, axes that are not affine; box region)
     std::vector<int> ent_nodes;
@@ -1011,9 +1012,9 @@ fk_status build_plan(fk_plan *p)
             for (int a = 0; a < p->d; ++a) lmax = std::max(lmax, I.sep_l[a]);
         // (a caller who asks for the box form, and large 3D plans of narrow
         // footprints, always read image nodes as their originals)
-        const bool reads_images = p->opt.hermite == FK_HERMITE_R1 &&
+        p->reads_images = p->opt.hermite == FK_HERMITE_R1 &&
                                   ((sk == 4 && lmax <= 8) || (sk == 0 && p->d == 3 && large && lmax <= 5));
-        if (p->use_box && p->periodic && !reads_images) {
+        if (p->use_box && p->periodic && !p->reads_images) {
             if (all_sep) p->dual = true;
             else p->use_box = false;
         }
@@ -2456,7 +2457,12 @@ fk_status fk_apply_step(fk_plan *p, int n, int transpose, const void *x, void *y
         FK_LAUNCH(fk::launch_masked_diff(p->dev, p->f32, x, nullptr, la, s));
         FK_LAUNCH(fk::launch_zero(mu, fb * rec_stride(p->d), s));
         FK_LAUNCH(fk::launch_zero(g, sizeof(double) * fk::kThetaSlots * p->n_inst, s));
-        FK_LAUNCH(fk::launch_adjoint_step(p->dev, p->f32, n, packed, la, mu, g, s));
+        // where the step reads image nodes as nodes of their own (step_dev), so does
+        // the transpose: a separable box adds to whichever of the two its indices
+        // meet, the lane groups to the landing cell's own corners
+        fk::PlanDev D = p->dev;
+        if (p->periodic && !(p->use_box && p->reads_images)) D.step_kind = 1;
+        FK_LAUNCH(fk::launch_adjoint_step(D, p->f32, n, packed, la, mu, g, s));
         FK_LAUNCH(fk::launch_unpack_fields(p->dev, p->f32, mu, y, s));
         FK_LAUNCH(fk::launch_zero(mu, fb * rec_stride(p->d), s));
     }

@@ -174,3 +174,21 @@ def test_transposed_step_is_the_transpose(name, L, prec, bar):
     plan.close()
     lhs, rhs = float((ax * y).sum()), float((x * aty).sum())
     assert abs(lhs - rhs) <= bar * float((np.abs(x) * np.abs(aty)).sum())
+
+
+@pytest.mark.parametrize("prec,bar", [("f64", 1e-12), ("f32", 1e-5)])
+@pytest.mark.parametrize("kernel", ["auto", "split", "box"])
+@pytest.mark.parametrize("name,L", [("rolls", 4), ("rolls", 9), ("rolls", 14), ("abc", 3), ("abc", 9)])
+def test_transposed_step_with_image_nodes_of_their_own(name, L, kernel, prec, bar):
+    """The same on periodic axes with fields whose images hold other values than
+    their originals: both sides take them as the same nodes."""
+    p = _rolls(L) if name == "rolls" else _abc(L, n=23)
+    plan = Plan(p, precision=prec, ckpt_every=1, step_kernel=kernel)
+    rng = np.random.default_rng(11)
+    x = rng.uniform(-1.0, 1.0, size=(p.d + 1, p.n_nodes))
+    y = rng.uniform(-1.0, 1.0, size=p.n_nodes)
+    ax = plan.apply_step(1, torch.from_numpy(x)).double().cpu().numpy()
+    aty = plan.apply_step(1, torch.from_numpy(y), transpose=True).double().cpu().numpy()
+    plan.close()
+    lhs, rhs = float((ax * y).sum()), float((x * aty).sum())
+    assert abs(lhs - rhs) <= bar * float((np.abs(x) * np.abs(aty)).sum())
