@@ -1257,7 +1257,7 @@ fk_status build_plan(fk_plan *p)
         // d + 1 field planes, innermost axis padded to pitch_wave's pitch
         const int NF = p->d + 1;
         const size_t elt_b = 8;   // tiles accumulate in FP64 in both precisions
-        const size_t budget = 60 * 1024;   // plus static LDS, within 64 KB per workgroup
+        const size_t budget = fk::kTileLdsMax;   // plus static LDS
         // wrap: a periodic axis' tile may run past the seam (unwrapped indices,
         // less than one period long); the kernel then indexes it unwrapped.
         // ext: the node box widened by h; pitch of the innermost axis chosen by
@@ -1396,7 +1396,7 @@ fk_status build_plan(fk_plan *p)
             }
             // per landing point: by tile bytes (eight, four and two workgroups per
             // CU), a tile that does not fit in the last class
-            static const size_t kTileLds[fk::kTileClasses] = {20 * 1024, 40 * 1024, 60 * 1024};
+            static const size_t kTileLds[fk::kTileClasses] = {20 * 1024, 40 * 1024, fk::kTileLdsMax};
             std::vector<std::vector<fk::WorkItem>> fww(fk::kTileClasses);
             std::vector<std::vector<fk::TileBox>> fwt(fk::kTileClasses);
             for (const fk::WorkItem &it : p->adj.fw_work) {

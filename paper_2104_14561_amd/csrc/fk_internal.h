@@ -15,6 +15,7 @@ constexpr int kBoxClasses = 5;    // separable-form footprint classes
 
 constexpr int kTileClasses = 3;   // classes of the per-point transposed step's tiles
 constexpr int kAdjLdsMax = 159 * 1024;   // dynamic LDS of a transposed step, of a CU's 160 KB
+constexpr int kTileLdsMax = 60 * 1024;   // of a per-point transposed step's tile
 
 // The one-launch step of small 2D plans: lanes per node, and the patch of 256 /
 // lanes nodes that a workgroup takes (rows x columns, at most kSmallPatch each).
@@ -354,7 +355,7 @@ hipError_t launch_lds_atomic_probe(bool f32, int blocks, int iters, double *out,
 hipError_t launch_line_steps(const PlanDev &P, bool f32, int nmax, int n_hi, int n_lo, const void *u_in,
                              void *u_out, void *store, int every, int shift, hipStream_t s);
 constexpr int kLineNodes = 4096;   // its longest axis: two record buffers and the masks in LDS
-inline size_t line_lds(int nmax, bool f32) { return (size_t)nmax * (2 * 2 * (f32 ? 4 : 8) + 5); }
+constexpr size_t line_lds(int nmax, bool f32) { return (size_t)nmax * (2 * 2 * (f32 ? 4 : 8) + 5); }
 
 // Device address of the static scratch array on the current device (taken
 // with hipGetSymbolAddress on the first call per device).

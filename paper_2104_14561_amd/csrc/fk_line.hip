@@ -256,9 +256,11 @@ hipError_t line_launch(const PlanDev &P, int nmax, int n_hi, int n_lo, const voi
             P, n_hi, n_lo, nmax, (const T *)u_in, (T *)u_out, (T *)store, every, shift, P.n_nodes);
         return hipGetLastError();
     }
+    // (the limit is the process': every plan sets the same value, the longest axis')
     if (lds > 64 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_line_steps<T, QS, false>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                  hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)line_lds(kLineNodes, sizeof(T) == 4));
     k_line_steps<T, QS, false><<<P.n_inst, kLineThreads, lds, s>>>(
         P, n_hi, n_lo, nmax, (const T *)u_in, (T *)u_out, (T *)store, every, shift, P.n_nodes);
     return hipGetLastError();

@@ -122,9 +122,10 @@ void adjoint_node_launch(const PlanDev &P, int n, const void *packed, const void
         if constexpr (D == 2)
             if (P.rel_ok) {
                 // the rows' static LDS on top of the tile: raise the limit past 64 KB
+                // (to the same value for every plan: it is the process')
                 if (A.fw_lds[c] + 40 * 1024 > 64 * 1024)
                     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_adjoint_pt2<T, QS>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, A.fw_lds[c]);
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, kTileLdsMax);
                 k_adjoint_pt2<T, QS><<<A.fw_grid[c], 64 * QS, A.fw_lds[c], s>>>(
                     P, n, A.n_fw_work[c], P.inst, wk, tl, A.fw_nodes, P.trig, (const T *)packed,
                     (const T *)lam, (T *)mu, grad);

@@ -118,3 +118,35 @@ def test_profile_times_the_launches_of_a_pass():
     prof = plan.profile_pass()
     plan.close()
     assert prof["slopes"][1] == prof["step_fused"][1] == 4
+
+
+def test_plans_of_different_lengths_on_two_threads():
+    """The kernel's LDS limit is the process': plans of 81 and 151 KB launched by
+    two threads, each on its own stream."""
+    import threading
+    probs = [_problem(n, 4, steps=3) for n in (2200, 4096)]
+    refs = [oracle.solve(p, snaps=[0])[0] for p in probs]
+    errs = [None, None]
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                plan = Plan(probs[i], precision="f64")
+                worst = 0.0
+                for _ in range(200):
+                    out = plan.forward([0])
+                worst = np.abs(plan.split(out)[0].cpu().numpy()[0] - refs[i]).max()
+                stream.synchronize()
+                plan.close()
+            errs[i] = worst
+        except Exception as e:   # a refused launch fails the test, not the thread
+            errs[i] = e
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(isinstance(e, float) or np.isscalar(e) for e in errs), errs
+    assert max(errs) <= 1e-12
