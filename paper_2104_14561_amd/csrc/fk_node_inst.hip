@@ -131,8 +131,12 @@ void adjoint_node_launch(const PlanDev &P, int n, const void *packed, const void
                     (const T *)lam, (T *)mu, grad);
                 done = true;
             }
-        if (!done)
-            k_adjoint_node<T, D, QS><<<A.fw_grid[c], kBlock, A.fw_lds[c], s>>>(
+        if (!done && P.all_affine)
+            k_adjoint_node<T, D, QS, true><<<A.fw_grid[c], kBlock, A.fw_lds[c], s>>>(
+                P, n, A.n_fw_work[c], P.inst, wk, tl, A.fw_nodes, P.trig, P.coords,
+                (const T *)packed, (const T *)lam, (T *)mu, grad);
+        else if (!done)
+            k_adjoint_node<T, D, QS, false><<<A.fw_grid[c], kBlock, A.fw_lds[c], s>>>(
                 P, n, A.n_fw_work[c], P.inst, wk, tl, A.fw_nodes, P.trig, P.coords,
                 (const T *)packed, (const T *)lam, (T *)mu, grad);
     }
