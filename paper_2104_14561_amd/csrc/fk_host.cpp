@@ -1408,6 +1408,20 @@ fk_status build_plan(fk_plan *p)
                 fwt[c2].push_back(tb);
                 if (tb.use_lds) p->adj.fw_lds[c2] = std::max(p->adj.fw_lds[c2], (int)b);
             }
+            // classes that are resident together anyway (two workgroups per CU) are
+            // one launch: its time is one workgroup's chain, whichever the class
+            // (45^3 ball, 1950 nodes in two classes, Q* = 4, FP64: 173 us in two launches, 88
+            // in one; 129 x 65 disc, Q* = 6, FP32: 54 and 30)
+            for (int c2 = 0; c2 < fk::kTileClasses; ++c2)
+                for (int c3 = c2 + 1; c3 < fk::kTileClasses && !fww[c2].empty(); ++c3) {
+                    if (fww[c3].empty()) continue;
+                    if (fww[c2].size() + fww[c3].size() > 512) break;
+                    fww[c3].insert(fww[c3].end(), fww[c2].begin(), fww[c2].end());
+                    fwt[c3].insert(fwt[c3].end(), fwt[c2].begin(), fwt[c2].end());
+                    p->adj.fw_lds[c3] = std::max(p->adj.fw_lds[c3], p->adj.fw_lds[c2]);
+                    fww[c2].clear();
+                    fwt[c2].clear();
+                }
             p->adj.fw_work.clear();
             for (int c2 = 0; c2 < fk::kTileClasses; ++c2) {
                 p->adj.fw_work_off[c2] = (int)p->adj.fw_work.size();
