@@ -1029,10 +1029,14 @@ fk_status build_plan(fk_plan *p)
         }
         const int gs = std::max(2, group_of(p->qs));
         std::vector<std::vector<fk::WorkItem>> bw(fk::kBoxClasses);
-        // node lists in patch order (16x16 in 2D, 4x4x16 in 3D, 256 in 1D):
-        // a work item never straddles a patch, so its landing footprint (and
-        // the adjoint's LDS tile of mu) stays compact
+        // node lists in patch order (16x16 in 2D, 4x8x8 or 4x4x16 in 3D, 256 in
+        // 1D): a work item never straddles a patch, so its landing footprint (and
+        // the adjoint's LDS tile of mu) stays compact.  3D: rows of 16 for the
+        // adjoint's LDS adds (pitch_wave) and for a thread per node, of 8 for Q* lanes
+        // per node (33^3 ball, Q* = 4, FP64: 51 us a step in rows of 16, 34 of 8; the 79^3
+        // ball, 6-node footprints, Q* = 6, FP32: 163 a thread per node, 183)
         static const int kPatch[3][3] = {{256, 1, 1}, {16, 16, 1}, {4, 4, 16}};
+        static const int kLanePatch[3] = {4, 8, 8};
         auto patch_sort = [&](std::vector<int> &list, const fk_problem &pr,
                               std::vector<long long> &keys, const int *pd = nullptr) {
             if (!pd) pd = kPatch[pr.d - 1];
@@ -1122,7 +1126,7 @@ fk_status build_plan(fk_plan *p)
                     bi[t].kind = all ? 1 : 0;
                 }
             }
-            patch_sort(fw, pr, keys);
+            patch_sort(fw, pr, keys, p->d == 3 && p->step_kind == 2 ? kLanePatch : nullptr);
             const int f1 = (int)p->fw_nodes.size();
             p->fw_nodes.insert(p->fw_nodes.end(), fw.begin(), fw.end());
             const size_t w0 = p->fw_work.size(), ws0 = p->fw_split_work.size();
