@@ -514,6 +514,38 @@ double ent_share(const fk_problem &pr, const std::vector<double> &gh, const std:
     return corners > 0.0 ? sum / corners : 0.0;
 }
 
+// Records that the separable form of class c reads per node, as a share of the
+// corners of the node's landing points, which the point form reads.
+double sep_share(int d, int qs, int c, const int *sep_l)
+{
+    double share = 1.0;
+    for (int a = 0; a < d; ++a) share *= fk::sep_reads(d, fk::box_len(d, c), a, sep_l) / (2.0 * qs);
+    return share;
+}
+
+// 3D step kernels, estimated microseconds: a workgroup's chain and, past as many
+// nodes as run side by side, the reads.  Least squares over 840 boxes and balls of
+// 23^3 to 79^3 nodes, Q* 2 to 6, footprints 3 to 14 (rms of the logarithms 0.07 to
+// 0.16); the layout they choose takes 1.006 times the best one's time in the mean,
+// 1.3 times at most.
+double sep3_us(bool f32, int c, double rows, double nodes, double reads)
+{
+    const int L = fk::box_len(3, c);
+    const double chain = L == 3 ? (f32 ? 7.5 : 9.5) : L == 4 ? (f32 ? 9.0 : 12.5) : (f32 ? 2.5 + 0.45 * rows : 2.3 + 0.53 * rows);
+    return chain + std::max(0.0, nodes - (f32 ? 74e3 : 35e3)) * reads * (f32 ? 0.66e-6 : 1.28e-6);
+}
+// Landing points, Q* lanes per node (split) or a thread.
+double pt3_us(bool f32, int qs, int lmax, double nodes, bool split, bool ball)
+{
+    static const double ch_split[2][5] = {{8, 10, 11, 16, 13}, {7, 9, 9.5, 12.5, 11}};
+    static const double ch_node[2][5] = {{12, 21.5, 40, 68, 108}, {10, 17, 28.5, 47, 72}};
+    if (nodes <= 0.0) return 0.0;
+    const int q = std::min(std::max(qs, 2), 6) - 2, f = f32 ? 1 : 0;
+    const double corners = 1e-6 * nodes * 8.0 * qs * qs * qs;
+    if (split) return ch_split[f][q] + corners * (f32 ? (lmax >= 5 ? 1.45 : 0.95) : (lmax >= 5 ? 2.9 : 1.9));
+    return ch_node[f][q] + corners * (f32 ? 0.52 : 1.17) * (ball ? 1.22 : 1.0);
+}
+
 void add_region(fk_plan *p, const char *name, size_t bytes)
 {
     Region r;
@@ -987,24 +1019,74 @@ fk_status build_plan(fk_plan *p)
         // (257 x 129, Q* = 8, FP64: 11.4 against 10.0 us with 3-node footprints, 12.5
         // against 14.7 with 7; 361^2: 30.6 against 14.7 and 32 against 22; 361^2,
         // Q* = 4: 14.1 against 11.4, where the rule still takes the one launch)
+        //
+        // Either way the form has to read less than the points do (sep_share; a
+        // caller who asks for it gets it).  2D, per step of 494 thousand nodes: FP64
+        // shares of 0.56 to 0.92 take 0.83 to 0.97 of the points' time, 1.0 to 1.2 1.01
+        // to 1.13; FP32 0.56 to 0.83 take 0.83 to 1.0, 0.88 to 1.2 1.09 to 1.18.  In 3D
+        // the estimates decide, the launch for the remaining nodes counted (33^3,
+        // Q* = 3, FP32: 5- and 12-node footprints 22.7 and 74.9 us, the points 22.4)
+        std::vector<int> fwd_cls = inst_cls;
+        if (sk != 4 && p->d == 2)
+            for (int i = 0; i < p->n_inst; ++i)
+                if (fwd_cls[i] >= 0 && sep_share(2, p->qs, fwd_cls[i], p->inst[i].sep_l) > (p->f32 ? 0.82 : 0.95))
+                    fwd_cls[i] = -1;
+        if (sk != 4 && p->d == 3) {
+            double nodes[fk::kBoxClasses] = {}, reads[fk::kBoxClasses] = {}, rows[fk::kBoxClasses] = {};
+            double rest = 0.0, all = 0.0, sep = 0.0;
+            int lmax = 0;
+            for (int i = 0; i < p->n_inst; ++i) {
+                const int c = inst_cls[i], *L = p->inst[i].sep_l;
+                const double ns = (double)inst_sep[i].size();
+                rest += (double)inst_rest[i].size() + (c < 0 ? ns : 0.0);
+                for (int a = 0; a < 3; ++a) lmax = std::max(lmax, L[a]);
+                if (c < 0 || ns == 0.0) continue;
+                const int Lc = fk::box_len(3, c);
+                const double r = (double)fk::sep_reads(3, Lc, 0, L) * fk::sep_reads(3, Lc, 1, L);
+                nodes[c] += ns;
+                rows[c] = std::max(rows[c], r);
+                reads[c] = std::max(reads[c], r * fk::sep_reads(3, Lc, 2, L));
+            }
+            for (int c = 0; c < fk::kBoxClasses; ++c) {
+                all += nodes[c];
+                if (nodes[c] > 0.0) sep += sep3_us(p->f32, c, rows[c], nodes[c], reads[c]);
+            }
+            // the points by lanes or threads, whichever takes the list in hand faster
+            const bool ball = p->probs[0].region_kind == FK_REGION_BALL;
+            const auto points = [&](double n) {
+                return std::min(pt3_us(p->f32, p->qs, lmax, n, true, ball), pt3_us(p->f32, p->qs, lmax, n, false, ball));
+            };
+            const double apart = sep + points(rest) + (rest > 0.0 ? 3.0 : 0.0);
+            const bool pays = all > 0.0 && apart <= 0.95 * points(rest + all);
+            if (!pays)
+                for (int i = 0; i < p->n_inst; ++i)
+                    // (footprints up to 4 without other nodes are never slower)
+                    if (fwd_cls[i] >= 0 && (rest > 0.0 || fk::box_len(3, fwd_cls[i]) > 4)) fwd_cls[i] = -1;
+            if (sk == 0 && p->step_kind != 1 && affine && !p->faces) {
+                const double n = pays && rest > 0.0 ? rest : rest + all;
+                p->step_kind = pt3_us(p->f32, p->qs, lmax, n, true, ball) < pt3_us(p->f32, p->qs, lmax, n, false, ball) ? 2 : 0;
+            }
+        }
+        bool any_cls = sk == 4;
+        for (int i = 0; i < p->n_inst; ++i) any_cls = any_cls || (fwd_cls[i] >= 0 && !inst_sep[i].empty());
         bool sep2d = false;
         if (p->d == 2 && sk == 0 && !large) {
             double gain = 0.0;
             bool rest = false;
             for (int i = 0; i < p->n_inst; ++i) {
-                rest = rest || !inst_rest[i].empty() || (inst_cls[i] < 0 && !inst_sep[i].empty());
-                if (inst_cls[i] < 0) continue;
+                rest = rest || !inst_rest[i].empty() || (fwd_cls[i] < 0 && !inst_sep[i].empty());
+                if (fwd_cls[i] < 0) continue;
                 const double points = (p->f32 ? 1.6 : 3.0) * p->qs * p->qs;
                 const double records = (p->f32 ? 1.1 : 2.4) * p->inst[i].sep_l[0] * p->inst[i].sep_l[1];
                 gain += 1e-6 * (double)inst_sep[i].size() * (points - records);
             }
             sep2d = gain > (rest ? 9.0 : 4.5);
         }
-        p->use_box = node_ok && affine && !p->faces && fk::box_compiled(p->d, p->qs) &&
+        p->use_box = node_ok && affine && !p->faces && any_cls && fk::box_compiled(p->d, p->qs) &&
                      (sk == 4 || (sk == 0 && (large || sep2d || p->d == 3)));
         bool all_sep = true;
         for (int i = 0; i < p->n_inst; ++i) {
-            all_sep = all_sep && inst_rest[i].empty() && (inst_cls[i] >= 0 || inst_sep[i].empty());
+            all_sep = all_sep && inst_rest[i].empty() && (fwd_cls[i] >= 0 || inst_sep[i].empty());
             for (int a = 0; a < p->d; ++a) p->periodic = p->periodic || p->probs[i].ax[a].periodic != 0;
         }
         int lmax = 0;
@@ -1100,7 +1182,7 @@ fk_status build_plan(fk_plan *p)
             long long points = 0;
             for (int i = 0; i < p->n_inst; ++i)
                 points += (long long)inst_rest[i].size() +
-                          (!p->use_box || inst_cls[i] < 0 || p->dual ? (long long)inst_sep[i].size() : 0);
+                          (!p->use_box || fwd_cls[i] < 0 || p->dual ? (long long)inst_sep[i].size() : 0);
             const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
             p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && sk != 1 &&
                            (p->step_kind != 0 || points < most);
@@ -1108,14 +1190,14 @@ fk_status build_plan(fk_plan *p)
         for (int i = 0; i < p->n_inst; ++i) {
             const fk_problem &pr = p->probs[i];
             std::vector<int> fw = inst_rest[i];
-            if (!p->use_box || inst_cls[i] < 0 || p->dual)
+            if (!p->use_box || fwd_cls[i] < 0 || p->dual)
                 fw.insert(fw.end(), inst_sep[i].begin(), inst_sep[i].end());
-            if (p->use_box && inst_cls[i] >= 0) {
+            if (p->use_box && fwd_cls[i] >= 0) {
                 std::vector<int> sep = inst_sep[i];
                 patch_sort(sep, pr, keys);
                 const int f0 = (int)p->box_nodes.size();
                 p->box_nodes.insert(p->box_nodes.end(), sep.begin(), sep.end());
-                std::vector<fk::WorkItem> &bi = bw[inst_cls[i]];
+                std::vector<fk::WorkItem> &bi = bw[fwd_cls[i]];
                 const size_t b0 = bi.size();
                 // full workgroups, across patches (the step keeps no tile)
                 build_work(bi, i, (int)sep.size(), kBlock, f0);
@@ -1320,9 +1402,15 @@ fk_status build_plan(fk_plan *p)
             return c <= std::max(last + 3, last * 5 / 4) ? c : last;
         };
         // adjoint lists: separable nodes by footprint class in the separable
-        // form, up to 15 nodes per axis in 2D (wider footprints add more
-        // entries than 12 per landing point) and 12 in 3D, the others per
-        // landing point
+        // form, up to 15 nodes per axis in 2D and 12 in 3D, the others per landing
+        // point; a default plan's only where the form adds few entries beside the
+        // points (sep_share; 2D gradients of 7 to 494 thousand nodes, against all per
+        // landing point: classes 6 and 9 take 0.3 to 1.05 of the time up to shares of
+        // 1.8 and up to 1.6 past it; class 12 0.7 to 1.03 up to 1.2, past it 1.0 to 1.7;
+        // class 15 in FP64 1.05 to 2.6, in FP32 0.73 to 1.0 from 126 thousand nodes on up
+        // to shares of 1.1, 1.0 to 1.8 otherwise.  3D: of the 9- and 12-node classes,
+        // whose points' tile does not fit either, 12 nodes with Q* = 3 1.4 to 2.3, Q* = 4
+        // 0.6 to 1.1; 9 with Q* = 2 0.5 to 0.9, and 2.5 at 17^3)
         if (p->opt.ckpt_every > 0) {
             const bool abox = node_ok && affine && p->d >= 2 && fk::box_compiled(p->d, p->qs) &&
                               sk != 1 && sk != 2 && p->step_kind != 1;
@@ -1332,6 +1420,16 @@ fk_status build_plan(fk_plan *p)
                 const fk_problem &pr = p->probs[i];
                 const int cls = inst_cls[i];
                 bool sep_form = abox && cls >= 0 && !inst_sep[i].empty();
+                if (sep_form && sk != 4) {
+                    const double share = sep_share(p->d, p->qs, cls, p->inst[i].sep_l);
+                    const int Lc = fk::box_len(p->d, cls);
+                    if (p->d == 2)
+                        sep_form = Lc <= 9 ? share <= 1.8
+                                           : (Lc <= 12 ? share <= 1.2
+                                                       : p->f32 && share <= 1.1 && p->n_active >= 100000);
+                    else
+                        sep_form = Lc <= 6 || share <= 3.5 || (Lc <= 9 && p->n_active >= 16384);
+                }
                 std::vector<int> fw = inst_rest[i];
                 // the columns of a workgroup's threads; patches halved along their
                 // longest axis until columns, tile and slack fit the LDS

@@ -131,10 +131,12 @@ def test_one_launch_step_2d_r2(q):
     _check_step(_flow2d(7, "ball", q), "f64", "auto", "r2")
 
 
-def _check_gradient(p, prec, bar):
+def _check_gradient(p, prec, bar, kernel="auto"):
     lam = W.region_mean_weights(p)
     g_ref, _ = oracle.adjoint(p, lam)
-    plan = Plan(p, precision=prec, ckpt_every=2)
+    plan = Plan(p, precision=prec, ckpt_every=2, step_kernel=kernel)
+    if kernel == "box":
+        assert plan.info.adj_box_nodes > 0
     g, _ = plan.adjoint(torch.from_numpy(lam.reshape(-1)))
     g = g.cpu().numpy()[0]
     plan.close()
@@ -192,3 +194,24 @@ def test_transposed_step_with_image_nodes_of_their_own(name, L, kernel, prec, ba
     plan.close()
     lhs, rhs = float((ax * y).sum()), float((x * aty).sum())
     assert abs(lhs - rhs) <= bar * float((np.abs(x) * np.abs(aty)).sum())
+
+
+@pytest.mark.parametrize("prec,bar", [("f64", 1e-10), ("f32", 1e-4)])
+@pytest.mark.parametrize("flow,L", [("2d", 9), ("2d", 12), ("2d", 13), ("2d", 15), ("3d", 6), ("3d", 9), ("3d", 12)])
+def test_gradient_in_separable_form(flow, L, prec, bar):
+    """The classes' transposed steps also where a default plan goes per landing
+    point (footprints wide beside Q*)."""
+    _check_gradient(_flow2d(L, "ball") if flow == "2d" else _abc(L), prec, bar, "box")
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("q,L,region", [(2, 6, "box"), (3, 5, "ball"), (3, 9, "box"), (6, 8, "ball"), (6, 11, "box")])
+def test_default_layouts_3d(q, L, region, prec):
+    """Default plans on both sides of the rule between separable nodes and points
+    by lanes or threads."""
+    h = 1.0 / 22
+    p = W.Problem(axes=[W.uniform_axis(0.0, 22 * h, n) for n in (23, 21, 25)], coef_kind="const",
+                  coef=(0.3, -0.2, 0.1), D=_spread(L, q, h, 1e-3), gh_q=q, dt=1e-3, n_steps=2)
+    if region == "ball":
+        p = p.replace(region_kind="ball", center=(0.5, 0.5, 0.5), radius=0.46)
+    _check_step(p, prec, "auto")
