@@ -524,6 +524,7 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     }
     __syncthreads();
     const int lane = threadIdx.x % GL, slot = threadIdx.x / GL;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int q = lane < QS ? lane : QS - 1;   // idle lanes repeat the last one, unweighted
     const double gq = P.gh_a[q];
     const T wq = lane < QS ? weights1<T>(P)[q] : T(0);
@@ -545,9 +546,9 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     const double r2 = ball ? I.r2 : HUGE_VAL;
     // one landing coordinate: cell (unwrapped, inside the tile), position,
     // squared distance (infinite: exit)
-    auto axis = [&](int a, double g, int &k, T &s, double &d2) {
+    auto axis = [&](int a, int &k, T &s, double &d2) {
         const double x = (idx[a] == I.n[a] - 1) ? I.hi[a] : (double)idx[a] * I.step[a] + I.lo[a];
-        const AxisEval e = eval_axis_affine(I, a, x + b[a] * P.dt, g);
+        const AxisEval e = eval_axis_affine(I, a, x + b[a] * P.dt, gq);
         int kk = e.k;
         if (I.periodic[a]) kk += kk < tb.lo[a] ? I.n[a] - 1 : (kk > tb.lo[a] + tb.ext[a] - 2 ? 1 - I.n[a] : 0);
         k = min(max(kk, tb.lo[a]), tb.lo[a] + tb.ext[a] - 2) - tb.lo[a];
@@ -557,13 +558,13 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     int k0, k1;
     T s, v0, v1, f0, f1;
     double d2;
-    axis(0, gq, k0, s, d2);
+    axis(0, k0, s, d2);
     unit_basis<T>(s, v0, v1, f0, f1);
     const T wh = wq * (T)I.step[0];
     rows[slot][lane] = {wq * v0, wq * v1, wh * f0, wh * f1};
     rd2[slot][lane] = d2;
     roff[slot][lane] = k0 * e1;
-    axis(1, gq, k1, s, d2);
+    axis(1, k1, s, d2);
     unit_basis<T>(s, v0, v1, f0, f1);
     // lanes of a node belong to one wave: its LDS writes precede its reads
     __builtin_amdgcn_wave_barrier();
@@ -602,40 +603,59 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
     acc = group_sum<GL>(acc);
     emass = group_sum<GL>(emass);
     if (!valid || lane != 0) return;
-    T v = uref + acc + emass * (T(1) - uref);
-    if (!isfinite((double)v)) {
-        // the inside points alone (see point_value)
-        acc = emass = T(0);
-#pragma unroll 1
-        for (int q1 = 0; q1 < QS; ++q1) {
-            axis(1, P.gh_a[q1], k1, s, d2);
-            unit_basis<T>(s, v0, v1, f0, f1);
-            const T h1 = (T)I.step[1], w1 = weights1<T>(P)[q1];
-            T part = T(0);
-#pragma unroll 1
-            for (int q0 = 0; q0 < QS; ++q0) {
-                const Row rw = rows[slot][q0];
-                if (rd2[slot][q0] + d2 >= r2) {
-                    emass += w1 * (rw.x0 + rw.x1);
-                    continue;
-                }
-                const R *p = rec + (roff[slot][q0] + k1);
-                const R p00 = p[0], p01 = p[1], p10 = p[e1], p11 = p[e1 + 1];
-                const T u0 = rw.x0 * (p00.x - uref) + rw.x1 * (p10.x - uref) + rw.d0 * p00.y + rw.d1 * p10.y;
-                const T u1 = rw.x0 * (p01.x - uref) + rw.x1 * (p11.x - uref) + rw.d0 * p01.y + rw.d1 * p11.y;
-                T y0 = rw.x0 * p00.z + rw.x1 * p10.z, y1 = rw.x0 * p01.z + rw.x1 * p11.z;
-                if constexpr (TW) {
-                    y0 += rw.d0 * p00.w + rw.d1 * p10.w;
-                    y1 += rw.d0 * p01.w + rw.d1 * p11.w;
-                }
-                part += v0 * u0 + v1 * u1 + h1 * (f0 * y0 + f1 * y1);
-            }
-            acc += w1 * part;
-        }
-        v = uref + acc + emass * (T(1) - uref);
-    }
-    flag_nonfinite(P.flags, v);
+    const T v = uref + acc + emass * (T(1) - uref);
     store_node<2, T>(I, idx, node, v, u_out);
+    if (__builtin_expect(!isfinite((double)v), 0)) {
+        // the inside points alone (see point_value); all of it anew from the wave's and
+        // the workgroup's number, so that no vector register is held for it before
+        int wg = blockIdx.x;
+        asm volatile("" : "+s"(wg));
+        const int again = (wave * kWave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))) / GL;
+        const WorkItem jt = work[wg];
+        const TileBox tc = tiles[wg];
+        const DevInst &J = insts[jt.inst];
+        const int nd = nodes[jt.first + again];
+        int id[3];
+        split_node<2>(J, nd, id);
+        const T u0 = rec[(id[0] - tc.lo[0]) * tc.ext[1] + (id[1] - tc.lo[1])].x;
+        double bb[2];
+        if (J.coef_kind == 0) {
+            bb[0] = J.coef[0];
+            bb[1] = J.coef[1];
+        } else {
+            drift_2d(J, time_factors(P, n, jt.inst), trig[0][id[0] - tc.pad], trig[1][id[1] - tc.soff], bb);
+        }
+        T sum = T(0), em = T(0);
+#pragma unroll 1
+        for (int q = 0; q < QS * QS; ++q) {
+            const int q0 = q / QS, q1 = q - q0 * QS;
+            const double x = (id[1] == J.n[1] - 1) ? J.hi[1] : (double)id[1] * J.step[1] + J.lo[1];
+            const AxisEval e = eval_axis_affine(J, 1, x + bb[1] * P.dt, P.gh_a[q1]);
+            const Row rw = rows[again][q0];
+            const T w = weights1<T>(P)[q1];
+            if (e.ex || (J.region_kind == 1 && rd2[again][q0] + e.dz2 >= J.r2) || rd2[again][q0] == HUGE_VAL) {
+                em += w * (rw.x0 + rw.x1);
+                continue;
+            }
+            int k = e.k;
+            if (J.periodic[1]) k += k < tc.lo[1] ? J.n[1] - 1 : (k > tc.lo[1] + tc.ext[1] - 2 ? 1 - J.n[1] : 0);
+            k = min(max(k, tc.lo[1]), tc.lo[1] + tc.ext[1] - 2) - tc.lo[1];
+            const Basis<T> Y = hermite<T>(e.s, e.h);
+            const R *p = rec + (roff[again][q0] + k);
+            T pt = T(0);
+#pragma unroll 1
+            for (int c = 0; c < 4; ++c) {
+                const R r = p[(c & 1) + (c >> 1) * tc.ext[1]];
+                const T X = c & 2 ? rw.x1 : rw.x0, Xd = c & 2 ? rw.d1 : rw.d0;
+                const T Yv = c & 1 ? Y.v1 : Y.v0, Yd = c & 1 ? Y.d1 : Y.d0;
+                pt += Yv * (X * (r.x - u0) + Xd * r.y) + Yd * (X * r.z + (TW ? Xd * r.w : T(0)));
+            }
+            sum += w * pt;
+        }
+        const T v1 = u0 + sum + em * (T(1) - u0);
+        flag_nonfinite(P.flags, v1);
+        store_node<2, T>(J, id, nd, v1, u_out);
+    }
 }
 
 // The separable step in three dimensions.  The axis-2 vectors are in registers, those of
