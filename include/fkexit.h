@@ -177,9 +177,12 @@ typedef struct {
                         d=1: gh_q 2..8,10,12,16; d=2: 2..8; d=3: 2..6
                         (FK_ERR_UNSUPPORTED otherwise).  auto picks 4 for 2D
                         plans with many active nodes and for 3D plans, 1 for
-                        other large plans, 3 for small and 1D ones, 2 when the
-                        others are not compiled for gh_q; fk_tune measures them
-                        instead.  Plans with faces other than exit-1 (or the
+                        other large plans, 3 for small and 1D ones (past
+                        3072 nodes on an axis, FP32 3584, in two launches a
+                        step), 2 when the others are not compiled for gh_q;
+                        2D and 3D nodes whose boxes hold more records than the
+                        points' corners go per landing point.  fk_tune measures
+                        the layouts instead.  Plans with faces other than exit-1 (or the
                         runaway model) run 2 with FK_HERMITE_R2 */
     int columns;     /* fk_forward_horizons: most columns one launch of the
                         FK_FORM_ELL product takes (1..4; 0 = 1); the workspace

@@ -1102,12 +1102,17 @@ fk_status build_plan(fk_plan *p)
         }
         // 1D: one workgroup takes an instance through many steps when its axis
         // fits the LDS (measured on 201 nodes, Q* = 16, FP64: 16 us per step in
-        // two launches, 0.9 us inside one)
+        // two launches, 0.9 us inside one); by default up to the length at which the
+        // two launches of the whole chip are as fast, or with many instances (Q* = 4,
+        // 8 and 16, FP64, 2305 nodes: 0.8 of their time, 3201: 1.0 to 1.07, 4096: 1.3 to
+        // 1.44; FP32 3201: 0.7 to 0.88, 4096: 0.94 to 1.16; 16 instances of 4096 nodes,
+        // Q* = 8 and 16: 0.35 to 0.8)
         if (p->d == 1 && (sk == 0 || sk == 3) && node_ok && affine && !p->wraps && !p->faces &&
             p->opt.form == FK_FORM_FUSED) {
             int nmax = 0;
             for (const fk::DevInst &I : p->inst) nmax = std::max(nmax, I.n[0]);
-            if (nmax <= fk::kLineNodes) p->line_nmax = nmax;
+            const bool pays = nmax <= (p->f32 ? 3584 : 3072) || (p->n_active >= 49152 && p->qs >= 8);
+            if (nmax <= fk::kLineNodes && (sk == 3 || pays)) p->line_nmax = nmax;
         }
         const int gs = std::max(2, group_of(p->qs));
         std::vector<std::vector<fk::WorkItem>> bw(fk::kBoxClasses);

@@ -132,7 +132,7 @@ def test_plans_of_different_lengths_on_two_threads():
         try:
             stream = torch.cuda.Stream()
             with torch.cuda.stream(stream):
-                plan = Plan(probs[i], precision="f64")
+                plan = Plan(probs[i], precision="f64", step_kernel="split")
                 worst = 0.0
                 for _ in range(200):
                     out = plan.forward([0])
@@ -150,3 +150,27 @@ def test_plans_of_different_lengths_on_two_threads():
         t.join()
     assert all(isinstance(e, float) or np.isscalar(e) for e in errs), errs
     assert max(errs) <= 1e-12
+
+
+@pytest.mark.parametrize("prec,bar", [("f64", 1e-12), ("f32", 1e-5)])
+@pytest.mark.parametrize("n,q,kind", [(3073, 5, "box"), (3585, 8, "periodic"), (4096, 4, "ball"), (4096, 16, "box")])
+def test_longest_axes_of_a_launch(n, q, kind, prec, bar):
+    """Axes that a default plan takes in two launches a step and step_kernel
+    "split" still in one."""
+    p = _problem(n, q, kind=kind)
+    u = np.random.default_rng(3).uniform(size=n)
+    if kind == "periodic":
+        u[-1] = u[0]
+    else:   # exit nodes hold 1
+        u[oracle.solve(p.replace(n_steps=1), snaps=[1])[0] == 1.0] = 1.0
+    ref = u
+    for m in range(4, -1, -1):
+        ref = oracle.step(p, m, ref)
+    for kernel in ("split", "auto"):
+        plan = Plan(p, precision=prec, step_kernel=kernel)
+        got = plan.split(plan.forward_from(torch.from_numpy(u), 5, [0]))[0].double().cpu().numpy()[0]
+        launches = plan.profile_pass()["slopes"][1]
+        plan.close()
+        assert np.abs(got - ref).max() <= bar
+        if kernel == "split":
+            assert launches == 0
