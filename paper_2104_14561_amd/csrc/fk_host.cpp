@@ -1188,7 +1188,11 @@ fk_status build_plan(fk_plan *p)
             for (int i = 0; i < p->n_inst; ++i)
                 points += (long long)inst_rest[i].size() +
                           (!p->use_box || fwd_cls[i] < 0 || p->dual ? (long long)inst_sep[i].size() : 0);
-            const long long most = p->qs <= 4 ? 192 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
+            // (Q* = 5 and 6 leave lanes of a group of eight idle: Q* = 6, 701 x 503 FP64 98
+            // against 79, FP32 62 against 51; its disc of 174 thousand nodes 57 and 48, 35
+            // and 31)
+            const long long most = p->qs <= 4 ? 192 * 1024
+                                 : p->qs <= 6 ? 128 * 1024 : (p->f32 ? 768 * 1024 : 400 * 1024);
             p->pt_groups = p->d == 2 && affine && !p->wraps && !p->faces && sk != 1 &&
                            (p->step_kind != 0 || points < most);
         }
