@@ -1027,10 +1027,23 @@ fk_status build_plan(fk_plan *p)
         // the estimates decide, the launch for the remaining nodes counted (33^3,
         // Q* = 3, FP32: 5- and 12-node footprints 22.7 and 74.9 us, the points 22.4)
         std::vector<int> fwd_cls = inst_cls;
-        if (sk != 4 && p->d == 2)
-            for (int i = 0; i < p->n_inst; ++i)
-                if (fwd_cls[i] >= 0 && sep_share(2, p->qs, fwd_cls[i], p->inst[i].sep_l) > (p->f32 ? 0.82 : 0.95))
-                    fwd_cls[i] = -1;
+        if (sk != 4 && p->d == 2) {
+            // (a large plan's remaining nodes are a launch more, for which the records
+            // have to save something: 701 x 503 disc, Q* = 2, 3-node footprints, FP64
+            // 21.3 against 18.2 us; per million nodes and point corner 1.26 us in FP64,
+            // 0.57 in FP32, per record 1.36 and 0.75)
+            double gain = 0.0;
+            bool rest = false;
+            for (int i = 0; i < p->n_inst; ++i) {
+                const double share = fwd_cls[i] < 0 ? 2.0 : sep_share(2, p->qs, fwd_cls[i], p->inst[i].sep_l);
+                if (share > (p->f32 ? 0.85 : 0.95)) fwd_cls[i] = -1;
+                rest = rest || !inst_rest[i].empty() || (fwd_cls[i] < 0 && !inst_sep[i].empty());
+                if (fwd_cls[i] < 0) continue;
+                const double corners = 4e-6 * p->qs * p->qs * (double)inst_sep[i].size();
+                gain += corners * (p->f32 ? 0.57 - 0.75 * share : 1.26 - 1.36 * share);
+            }
+            if (large && rest && gain < 4.5) fwd_cls.assign(p->n_inst, -1);
+        }
         if (sk != 4 && p->d == 3) {
             double nodes[fk::kBoxClasses] = {}, reads[fk::kBoxClasses] = {}, rows[fk::kBoxClasses] = {};
             double rest = 0.0, all = 0.0, sep = 0.0;
