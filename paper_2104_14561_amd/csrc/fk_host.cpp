@@ -2017,15 +2017,15 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
     const size_t fb = elt(p) * (size_t)p->n_nodes;
     void *ua = p->at("uA"), *ub = p->at("uB");
     FK_LAUNCH(fk::launch_clear_flags(p->dev, s));
-    // both buffers hold 1 on exit nodes (and chi elsewhere)
+    // both buffers hold their values on exit nodes (and chi elsewhere): a caller's
+    // state, which may hold others there, is read in place by its own step
     FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, ub, s));
-    if (u_start && p->conv) {
+    const bool in_place = u_start && !p->conv;
+    if (u_start && p->conv)
         FK_LAUNCH(fk::launch_convert_in(p->dev, (const float *)u_start, (double *)ua, s));
-    } else if (u_start) {
-        FK_HIP(hipMemcpyAsync(ua, u_start, fb, hipMemcpyDeviceToDevice, s));
-    } else {
+    else
         FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, ua, s));
-    }
+    void *cur = in_place ? const_cast<void *>(u_start) : ua;
     auto snap_copy = [&](int n, const void *u) -> fk_status {
         for (int k = 0; k < n_snap; ++k) {
             if (snaps[k] != n) continue;
@@ -2049,8 +2049,8 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
                                   hipMemcpyDeviceToDevice, s));
         return FK_OK;
     };
-    FK_TRY(snap_copy(start, ua));
-    FK_TRY(ckpt_copy(start, ua));
+    FK_TRY(snap_copy(start, cur));
+    FK_TRY(ckpt_copy(start, cur));
     // a step whose state is a checkpoint writes it straight into its slot
     // (the slots hold 1 on exit nodes since the workspace was set); the others
     // alternate between the two work fields
@@ -2058,7 +2058,6 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
         if (!store_ckpt || n == p->N || n % p->opt.ckpt_every != 0) return nullptr;
         return (unsigned char *)p->at("ckpt") + (size_t)(n / p->opt.ckpt_every) * fb;
     };
-    void *cur = ua;
     if (p->line_nmax > 0) {
         // as far as the next snapshot in one go
         for (int n = start; n > 0;) {
@@ -2078,6 +2077,7 @@ fk_status enqueue_pass(fk_plan *p, const void *u_start, int start, const int *sn
         void *dst = slot_of(n);
         if (!dst) dst = (cur == ua) ? ub : ua;
         FK_TRY(enqueue_step(p, n, cur, dst, s, !u_start || n < start - 1));
+        if (u_start && p->conv && n == start - 1) FK_LAUNCH(fk::launch_init_field(p->dev, p->f32, ua, s));
         cur = dst;
         FK_TRY(snap_copy(n, cur));
     }
