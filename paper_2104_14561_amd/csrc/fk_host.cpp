@@ -1432,7 +1432,9 @@ fk_status build_plan(fk_plan *p)
         // class 15 in FP64 1.05 to 2.6, in FP32 0.73 to 1.0 from 126 thousand nodes on up
         // to shares of 1.1, 1.0 to 1.8 otherwise.  3D: of the 9- and 12-node classes,
         // whose points' tile does not fit either, 12 nodes with Q* = 3 1.4 to 2.3, Q* = 4
-        // 0.6 to 1.1; 9 with Q* = 2 0.5 to 0.9, and 2.5 at 17^3)
+        // 0.6 to 1.1; 9 with Q* = 2 0.5 to 0.9, and 2.5 at 17^3).  On periodic axes always:
+        // the points' tiles stop at the seam, past which their adds go to global memory
+        // (rolls of 65 x 33 to 513 x 257, 12- and 14-node footprints: 0.4 to 0.9)
         if (p->opt.ckpt_every > 0) {
             const bool abox = node_ok && affine && p->d >= 2 && fk::box_compiled(p->d, p->qs) &&
                               sk != 1 && sk != 2 && p->step_kind != 1;
@@ -1442,7 +1444,9 @@ fk_status build_plan(fk_plan *p)
                 const fk_problem &pr = p->probs[i];
                 const int cls = inst_cls[i];
                 bool sep_form = abox && cls >= 0 && !inst_sep[i].empty();
-                if (sep_form && sk != 4) {
+                bool seam = false;   // a periodic axis
+                for (int a = 0; a < p->d; ++a) seam = seam || pr.ax[a].periodic != 0;
+                if (sep_form && sk != 4 && !seam) {
                     const double share = sep_share(p->d, p->qs, cls, p->inst[i].sep_l);
                     const int Lc = fk::box_len(p->d, cls);
                     if (p->d == 2)
