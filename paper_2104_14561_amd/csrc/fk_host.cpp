@@ -1039,11 +1039,13 @@ fk_status build_plan(fk_plan *p)
         // included, FP32) 18.6 against 12.3 us at 9^3, Q* = 4, 57 against 13.4 at
         // 33^3, Q* = 6, 149 against 15 at 49^3, and 19.3 against 19.4 at worst
         // (17^3, Q* = 4, 9-node footprints).  In 2D a step in one launch is better
-        // until its points cost more than the second launch: per million points
-        // 1.6 us in FP32, 3.0 in FP64, per million footprint records 1.1 and 2.4
-        // (257 x 129, Q* = 8, FP64: 11.4 against 10.0 us with 3-node footprints, 12.5
-        // against 14.7 with 7; 361^2: 30.6 against 14.7 and 32 against 22; 361^2,
-        // Q* = 4: 14.1 against 11.4, where the rule still takes the one launch)
+        // until it costs more than the second launch: per million nodes 30 us, and
+        // 1.25 (FP32) or 1.75 (FP64) per point of its lanes, Q* times the power of two
+        // above it, against 0.75 per record (257 x 129, Q* = 8, FP64: 12.6 against 12.8 us
+        // with 5-node footprints; 361^2: 33 against 16.6, Q* = 5: 25.9 against 15.8,
+        // Q* = 4: 16.0 against 15.3; over 1812 boxes, discs, batches and rolls of 2 to 129
+        // thousand nodes, Q* 2 to 8, footprints 3 to 12, the choice takes 1.002 times the
+        // better one's time in the mean, 1.25 at most)
         //
         // Either way the form has to read less than the points do (sep_share; a
         // caller who asks for it gets it).  2D, per step of 494 thousand nodes: FP64
@@ -1114,11 +1116,12 @@ fk_status build_plan(fk_plan *p)
             for (int i = 0; i < p->n_inst; ++i) {
                 rest = rest || !inst_rest[i].empty() || (fwd_cls[i] < 0 && !inst_sep[i].empty());
                 if (fwd_cls[i] < 0) continue;
-                const double points = (p->f32 ? 1.6 : 3.0) * p->qs * p->qs;
-                const double records = (p->f32 ? 1.1 : 2.4) * p->inst[i].sep_l[0] * p->inst[i].sep_l[1];
+                const int lanes = std::max(2, group_of(p->qs));
+                const double points = 30.0 + (p->f32 ? 1.25 : 1.75) * lanes * p->qs;
+                const double records = 0.75 * p->inst[i].sep_l[0] * ((p->inst[i].sep_l[1] + 2) / 3 * 3);
                 gain += 1e-6 * (double)inst_sep[i].size() * (points - records);
             }
-            sep2d = gain > (rest ? 9.0 : 4.5);
+            sep2d = gain > (rest ? 9.0 : (p->f32 ? 4.5 : 4.3));
         }
         p->use_box = node_ok && affine && !p->faces && any_cls && fk::box_compiled(p->d, p->qs) &&
                      (sk == 4 || (sk == 0 && (large || sep2d || p->d == 3)));
