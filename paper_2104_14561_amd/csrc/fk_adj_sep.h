@@ -387,14 +387,18 @@ __global__ void __launch_bounds__(64 * QS, sizeof(T) == 4 ? 6 : 2) k_adjoint_pt2
 // row, one of (V1, S1) and one of the sums (A1, B1); the axis-2 vectors and
 // sums are registers.  Footprints up to 4 nodes (UN) unroll the rows and keep
 // (A1, B1) in registers too; in FP32 with 3-node footprints four workgroups fit
-// a CU (126 VGPRs, 40 KB).  Bound: vector issue (1970 instructions per node's
-// wave, 100 us of the 162 below at 129^3), then the adds: a wave takes 4 rows
-// of 16 nodes (8 rows of 8 met two by two on the LDS banks, 16.4 cycles per add).
+// a CU (126 VGPRs, 40 KB).  Bound at 129^3: vector issue (1917 vector
+// instructions per wave of 64 nodes, at 4 cycles 102 of the 162 us below), then
+// the adds: a wave takes 4 rows of 16 nodes (8 rows of 8 met two by two on the LDS
+// banks, 16.4 cycles per add).
 // 129^3 ABC flow (3-node footprints) in FP32: 369 us with derivative vectors per
 // axis (224 VGPRs), 208 with sums, 182 in rows of 16 and a cell's fields flushed
 // together, 162 with the fourth workgroup; 65^3 in FP64 with 6 x 6 x 9 footprints
-// 386 us against 47.7 ms per landing point (a tile of that reach did not fit LDS,
-// and every add went to global memory).
+// 390 us against 47.7 ms per landing point (a tile of that reach did not fit LDS,
+// and every add went to global memory).  Columns and tile leave room for one
+// workgroup of 128 threads a CU there, two waves on four SIMDs with nothing to
+// hide a latency behind: the vector issue alone is 106 us on the two SIMDs, the
+// 27 thousand LDS instructions of a CU 95 to 124 us at 8.4 to 11 cycles.
 template <typename T, int QS, int L, int BS>
 __global__ void __launch_bounds__(BS, (sizeof(T) == 4 && L == 3) ? 4 : 1) k_adjoint_sep3(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,

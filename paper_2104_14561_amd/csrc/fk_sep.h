@@ -221,12 +221,12 @@ __device__ inline void retake(const PlanDev &P, int n, int n_work, int slot, con
 //
 // Bound: the L1 record reads, 16 cycles of a CU per 16-byte record of a wave
 // (FP64 32), L0 L1 of them per node against 4 Q*^2 in the per-point form, and
-// about as much VALU issue.  64-instance batch, per step: 0.91 million
-// separable nodes in FP32 73 us and 0.51 million in FP64 107 us over the
-// classes; a thread per node over the landing points took 182 us for the FP32
-// part with the 0.24 million other nodes (which now take 48 us, see
-// k_step_pt2), 223 us for the FP64 part (30 us now for its others).  From 16
-// nodes per axis on a footprint holds more records than the points read.
+// about as much VALU issue.  64-instance batch (Q* = 8), per step: the FP32 part
+// 63 us over the classes and 62 by points for the nodes near the discs and those
+// of about 15 nodes on both axes (k_step_pt2), the FP64 part 109 and 29 us; a
+// thread per node over the landing points took 182 and 223 us for all of them.
+// From 16 nodes per axis on a footprint holds more records than the points read;
+// the host draws the line where the form stops being faster.
 template <typename T, int QS, int L, int BS, bool TW>
 __global__ void __launch_bounds__(BS) k_step_sep2(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
@@ -322,7 +322,7 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
 
 // Q*^2 landing points by a group of GL = pow2(Q*) lanes per node, lane l taking
 // the axis-1 GH node l, for the nodes that the separable form does not take (a
-// landing point can reach the ball, or a footprint of more than 15 nodes).  A
+// landing point can reach the ball, or the footprint holds too many records).  A
 // lane evaluates one landing coordinate per axis; the axis-0 ones (cell row,
 // weighted bases, squared distance) are shared through LDS and walked in
 // order, the lane's own column bases applied once at the end, 16 multiply-adds
@@ -334,9 +334,9 @@ __global__ void __launch_bounds__(BS) k_step_sep2(
 // A lane holds one column's data instead of Q* (a thread per node takes 108 to
 // 156 VGPRs, three to four waves per SIMD).  Lanes next to each other take
 // nodes next to each other, the same GH node, so that their records share
-// lines (57 us with a node's lanes side by side in FP32, 48 so; 301^2, points
-// spread over 45 cells: 25 and 20 us).  The batch's non-separable nodes: FP64 52
-// us a thread per node, 30 us now; FP32 54 and 48 us.
+// lines (the nodes near the discs of the 64-instance batch in FP32, 57 us with a
+// node's lanes side by side, 48 so; 301^2, points spread over 45 cells: 25 and 20
+// us).  The same nodes a thread per node: FP32 54, FP64 52 us, here 48 and 29.
 template <typename T, int QS, bool TW>
 __global__ void __launch_bounds__(kBlock) k_step_pt2(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,
@@ -465,8 +465,8 @@ __global__ void __launch_bounds__(kBlock) k_step_pt2(
 // workgroup that needs them, which costs less than the launch that would share
 // them as long as the reach is a few patches.
 // Bound: the chain of one workgroup (one item each) and the launch (4 us).
-// 513 x 257 with a disc (28 thousand active nodes, Q* = 8) in FP32: 7.4 us against
-// 5.1 + 10.5 us in two launches; 129 x 33 periodic in FP64 6.1 against 4.1 + 7.9 us.
+// 513 x 257 with a disc (28 thousand active nodes, Q* = 8) in FP32: 6.8 us against
+// 5.1 + 10.5 us in two launches; 129 x 33 periodic in FP64 6.0 against 4.1 + 7.9 us.
 template <typename T, int QS, bool TW>
 __global__ void __launch_bounds__(kBlock) k_step_small2(
     const PlanDev P, int n, const DevInst *__restrict__ insts, const WorkItem *__restrict__ work,
@@ -663,10 +663,12 @@ __global__ void __launch_bounds__(kBlock) k_step_small2(
 // records against the axis-2 vectors.  Footprints up to 4 nodes (UN) unroll
 // the rows, wider ones loop over the instance's own L0 x L1.  TW: the R2
 // interpolant, the nodes' twist records beside the others.
-// 129^3 ABC flow (3-node footprints, Q* = 6) in FP32: 64 us, 116 us with the
+// Bound: vector issue (3170 vector instructions for a wave's four nodes per lane
+// at 129^3, 42 of the 67 us below at 4 cycles each), then the record gathers.
+// 129^3 ABC flow (3-node footprints, Q* = 6) in FP32: 67 us, 116 us with the
 // vectors selected by cell in registers and the coordinate form of the landing
-// points; 65^3 with the R2 interpolant 18 us against 457 us over the landing
-// points; 65^3 in FP64 with 6 x 6 x 9 footprints 116 against 597 us.
+// points; 65^3 with the R2 interpolant 16 us against 457 us over the landing
+// points; 65^3 in FP64 with 6 x 6 x 9 footprints 114 against 597 us.
 template <typename T, int QS, int L, int BS, bool TW>
 __global__ void __launch_bounds__(BS, sizeof(T) == 8 && L == 4 && TW ? 2 : 1) k_step_sep3(
     const PlanDev P, int n, int n_work, const DevInst *__restrict__ insts,

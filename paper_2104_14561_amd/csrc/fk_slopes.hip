@@ -56,8 +56,8 @@ template <int D> struct BoxItem {
 // inverses (one division per axis is left, of the harmonic mean); the box is
 // numbered across its rows, so that rows of 129 nodes do not leave half of a
 // 256-thread workgroup idle.  129^3 FP32: 57 us with a workgroup per row and
-// three divisions per axis, 24 us now; the FP32 part of the 64-instance batch
-// 31 us, now 22 us.
+// three divisions per axis, 23 us now; the FP32 part of the 64-instance batch
+// 31 us, now 20 us with u in the L2 and 24 without.
 //
 // Several columns (Algorithm 1) in one launch: column c = blockIdx.y, its field
 // at u + c * ustride, its records at packed + c * pstride.
@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(kBlock) k_slopes(PlanDev P, int n, int first, 
 // 3D) and the nine slope derivatives of a node.  It was three launches (value,
 // scatter with nine atomic adds per node, fold) which also cleared mu for the
 // next step; the gather of the tiles now stores instead of adding.  129^3 in
-// FP32: 75 us in three launches, 41 now, the gather 41 and 31 us; the FP32 part
+// FP32: 75 us in three launches, 42 now, the gather 41 and 30 us; the FP32 part
 // of the 64-instance batch 49 and 18.5 us.
 template <typename T, int D>
 __global__ void __launch_bounds__(kBlock) k_slopes_T(PlanDev P, int first, int count,
