@@ -131,15 +131,17 @@ def traffic_table():
     return t["kernels"]
 
 
-def measured_traffic(kernels):
-    """Calibrated HBM bytes of one launch of each named kernel, summed (the
-    kernels one timed group launches once each), or None."""
+def measured_traffic(kernels, n_steps=None):
+    """Calibrated HBM bytes of one launch of each named kernel, summed, or None;
+    n_steps: of their launches in one of the n_steps time steps of a bench step
+    (a list of several classes is launched once per class)."""
     t = traffic_table()
     if isinstance(kernels, str):
         kernels = [kernels]
     if not t or any(k not in t for k in kernels):
         return None
-    return sum(t[k]["fetch_bytes_per_launch"] + t[k]["write_bytes_per_launch"] for k in kernels)
+    return round(sum((t[k]["fetch_bytes_per_launch"] + t[k]["write_bytes_per_launch"])
+                     * (t[k]["launches_per_step"] / n_steps if n_steps else 1) for k in kernels))
 
 
 def disc_mean_weights(probs, dtype, device):
@@ -353,7 +355,7 @@ def extra_rows_leg(stream, log):
         ("cell2d_513x257_r2", W.cell2d().replace(hermite="r2"), {"hermite": "r2"}, ("f32",)),
         ("abc3d_65_r1", W.abc3d(n=65, n_steps=100), {}, ("f32",)),
         ("abc3d_65_r2", W.abc3d(n=65, n_steps=100).replace(hermite="r2"),
-         {"hermite": "r2", "step_kernel": "node"}, ("f32",)),
+         {"hermite": "r2"}, ("f32",)),
         ("runaway3d", W.runaway3d(), {}, ("f64", "f32")),
     ]
     out = {}
@@ -398,6 +400,10 @@ def main():
     ap.add_argument("--no-profile", action="store_true",
                     help="skip the per-kernel profiling passes and the roofline (counter runs: "
                          "every kernel then runs in exactly two backward passes and two adjoints)")
+    ap.add_argument("--time-steps", type=int, default=None,
+                    help="time steps of the batch instead of its 1000 (counter runs, with "
+                         "--no-profile: the launches of a time step do not depend on their "
+                         "number); not the headline workload")
     ap.add_argument("--copy-probe", action="store_true",
                     help="first copy 1 GiB device-to-device once (a kernel of known traffic "
                          "that scales the HBM byte counters of a profiled run)")
@@ -426,6 +432,10 @@ def main():
         del src, dst
         torch.cuda.empty_cache()
     probs = W.cell2d_batch()
+    if args.time_steps is not None:
+        if not (args.no_profile or args.ell_only):
+            ap.error("--time-steps is for counter runs: give --no-profile")
+        probs = [p.replace(n_steps=args.time_steps) for p in probs]
     N = probs[0].n_steps
     if args.ell_only:
         print(json.dumps({"ell_batched": ell_batched(probs, stream)}), flush=True)
@@ -490,7 +500,12 @@ def main():
     n_recomp = prof_a["recompute_step"][1]
     t_step_kernel = prof_f["step_fused"][0] * (N + n_recomp)
     t_adj_kernel = prof_a["adjoint_step"][0] * prof_a["adjoint_step"][1]
-    n_point = int(plan.info.adj_point_nodes)
+    # (the profile times the FP32 launches; the nodes that they work on)
+    own = Plan([p for p, f in zip(probs, force) if not f], precision="f32", ckpt_every=ckpt,
+               allocate=False) if any(force) and not all(force) else plan
+    n_point, n_step = int(own.info.adj_point_nodes), int(own.info.n_active)
+    if own is not plan:
+        own.close()
     if t_adj_kernel >= t_step_kernel:
         ms_k = prof_a["adjoint_step"][0]
         roof = scope_roofline(d, Q, n_point, ms_k, ADJOINT_FACTOR, plan.precision,
@@ -517,13 +532,13 @@ def main():
         share = t_adj_kernel / ms_step
     else:
         ms_k = prof_f["step_fused"][0]
-        roof = scope_roofline(d, Q, Ja, ms_k, 1, plan.precision,
+        roof = scope_roofline(d, Q, n_step, ms_k, 1, plan.precision,
                               "k_step_sep2 and k_step_pt2 (fused step: separable nodes by footprint class, "
                               "the others per landing point)")
         kname = [f"void k_step_sep2<float, 8, {n}, 256, false>" for n in (6, 9, 12, 15)] + [
             "void k_step_pt2<float, 8, false>"]
         share = t_step_kernel / ms_step
-    roof["traffic"] = measured_traffic(kname)
+    roof["traffic"] = measured_traffic(kname, N)
     roof["share_of_step"] = round(share, 4)
     t = traffic_table()
     step_hbm = None
